@@ -70,8 +70,8 @@ extern "C" {
 #define DFPR_FTOL_ADAPTIVE (-1.0)
 
 /* iteration drivers (dfpr_params.loop) */
-#define DFPR_LOOP_LAUNCHES 0 /* one launch pair per iteration                   */
-#define DFPR_LOOP_DEVICE 1   /* small frontiers iterate inside one launch       */
+#define DFPR_LOOP_LAUNCHES 0 /* the library's choice                            */
+#define DFPR_LOOP_DEVICE 1   /* only small frontiers iterate inside one launch  */
 
 typedef struct dfpr_graph dfpr_graph;
 
@@ -101,15 +101,14 @@ typedef struct {
                               are not bitwise reproducible; it applies to the
                               FP64 iterations (not to the FP32 phase) and is
                               ignored by the serving calls.                    */
-    int32_t loop;          /* DFPR_LOOP_LAUNCHES (default): every iteration
-                              is its own launch pair (pull, then fold);
-                              DFPR_LOOP_DEVICE: while a Dynamic Frontier
-                              call's frontier is small, its iterations run
-                              inside one cooperative launch (Algorithm 1's
-                              loop on the device, a grid barrier between the
-                              pull and the fold).  Results are bitwise the
-                              same either way; on MI355X the launch pairs are
-                              as fast or faster at every frontier measured. */
+    int32_t loop;          /* DFPR_LOOP_LAUNCHES (default): the library picks
+                              what is fastest, a launch pair per iteration
+                              (pull, then fold) or many iterations inside one
+                              launch; DFPR_LOOP_DEVICE: a launch pair per
+                              iteration except while a Dynamic Frontier call's
+                              frontier is small (these iterations are counted
+                              in dfpr_stats.loop_iterations).  Results are
+                              bitwise the same either way.                     */
 } dfpr_params;
 
 typedef struct {
@@ -118,8 +117,8 @@ typedef struct {
     int32_t converged;          /* 1 if the L-inf change reached <= tol;
                                    reaching max_iters is not an error         */
     int32_t refine_sweeps;      /* FP64 iterations after the FP32 phase       */
-    int32_t loop_iterations;    /* iterations run inside the small-frontier
-                                   loop (see dfpr_params.loop)                */
+    int32_t loop_iterations;    /* DFPR_LOOP_DEVICE: iterations run inside one
+                                   launch while the frontier was small        */
     double final_linf;          /* L-inf change of the last iteration          */
     double ms_device;           /* device time of the call (HIP events)        */
     int64_t affected_initial;   /* vertices marked by the initial marking      */
@@ -240,8 +239,7 @@ int dfpr_pagerank_dynamic_frontier_device(dfpr_graph *g, const dfpr_params *p,
  * ends) instead of a buffer it grows on demand, so the call makes no
  * allocation.  n_del + n_ins may be at most 1048576 (DFPR_E_LIMIT beyond,
  * nothing changed).  Every call on a GPU shares that array: calls that
- * overlap on one GPU race.  Iterations run as launch pairs whatever
- * p->loop asks for. */
+ * overlap on one GPU race.  p->loop is taken as DFPR_LOOP_LAUNCHES. */
 int dfpr_pagerank_dynamic_frontier_device_noalloc(dfpr_graph *g, const dfpr_params *p,
                                                   int64_t n_del, const int32_t *del_src,
                                                   const int32_t *del_dst, int64_t n_ins,
@@ -303,6 +301,7 @@ int dfpr_export_csr(const dfpr_graph *g, int out_orientation, int64_t *offsets,
 
 /* Profile of the iteration kernel (the pull, Delta r, L-inf and expansion
  * of one iteration), summed over every call made while profiling is on.
+ * Calls made then take a launch pair per iteration on every graph.
  * ms is measured with HIP events recorded on the graph's stream right
  * before and after each iteration-kernel launch (timing-only events, with
  * no system-scope fence).  bytes is the algorithmic traffic of those

@@ -23,6 +23,9 @@ constexpr int kCounters = 4;
 // reads 256 slots instead of one partial per workgroup.
 constexpr int kFoldSlots = 256;           // rows, in-edges, expanded rows, their out-edges
 constexpr int kLoopChunk = 64;         // most iteration launches between two host looks
+constexpr int kLoopLaunches = 8;       // most launches of the resident loop in one call
+constexpr int kHubSteps = 6;           // sizes of its LDS copy of contributions
+constexpr int kResBytes = 32768;       // words its workgroups exchange (ResWords)
 
 // In-degree classes.  A row of class b < 6 is reduced by a group of
 // group_of(b) lanes of one wave; class 6 rows take a whole workgroup.
@@ -84,9 +87,10 @@ struct Ctl {
     unsigned long long reach0;  // out-edges of the vertices the initial marking marked
     double ftol_used;           // frontier tolerance of the call (the adaptive rule's
                                 // choice when the parameter asks for it)
-    uint32_t bar[2];            // arrivals at the grid barriers of the small-frontier
-                                // loop, one counter per loop phase of a call
-    uint32_t loop_fail;         // a grid barrier of that loop timed out
+    uint32_t loop_go[kLoopLaunches];   // resident loop: per launch of the call, 1 once every
+                                // workgroup was running, 2 if one gave up waiting first
+    uint32_t loop_ran;          //   tag of the last launch that ran
+    uint32_t loop_fail;         //   a barrier timed out
 };
 
 // One orientation of the graph: row r holds cnt[r] sorted ids in
@@ -108,6 +112,9 @@ struct IterBufs {
     double *dr_part = nullptr;                // L-inf of Delta r (atomic max on the bits)
     double *rmax_part = nullptr;              // largest rank (atomic max on the bits)
     unsigned long long *cnt_part = nullptr;   // counters (kCounters per slot)
+    // resident loop: what its workgroups hand to workgroup 0 and back
+    // (ResWords in rank.hip); tags make clearing unnecessary
+    unsigned long long *res = nullptr;
 };
 
 // Host-side profile of the iteration kernel (see dfpr_profile in dfpr.h).
@@ -192,7 +199,11 @@ struct dfpr_graph {
     int grid = 1024;                  // iteration-kernel workgroups
     int grid_wide = 1024;             //   ... of the wide full-sweep kernel
     int grid_wide_df = 1024;          //   ... of the wide Dynamic Frontier kernel
-    int coop = 0;                     // the device takes cooperative launches
+    double hub_share[dfpr::kHubSteps] = {};   // part of the in-edges (at load) whose source is
+                                      // below 1024 << k
+    int cus = 0;                      // compute units: workgroups of a resident loop at most
+    uint32_t res_tag = 0;             // last barrier tag handed to a resident loop
+    int res_used = 0;                 // resident launches of the current call
     uint32_t sparse_limit = 0;        // frontier size that switches to the full schedule
 };
 

@@ -264,6 +264,8 @@ static int load_impl(int32_t n, int64_t m, const int32_t *src, const int32_t *ds
     }
     std::vector<int32_t>().swap(oraw);
     g->m = (int64_t)oidx.size();
+    for (int k = 0; k < kHubSteps; k++)
+        g->hub_share[k] = (double)oc[std::min<int64_t>(int64_t(1024) << k, n)] / (double)g->m;
     // in-rows: stable counting sort of the out-rows by destination; visiting
     // sources in increasing order leaves every in-row sorted
     std::vector<uint64_t> ic(n + 1, 0);
@@ -327,6 +329,7 @@ void dfpr_free_graph(dfpr_graph *g)
     (void)hipFree(g->it.dr_part);
     (void)hipFree(g->it.rmax_part);
     (void)hipFree(g->it.cnt_part);
+    (void)hipFree(g->it.res);
     for (int o = 0; o < 2; o++) {
         for (int k = 0; k < 2; k++) (void)hipFree(g->ap.keys[o][k]);
         (void)hipFree(g->ap.tiny_list[o]);
@@ -388,8 +391,10 @@ int dfpr_load_graph(int32_t n, int64_t m, const int32_t *src, const int32_t *dst
         if (!rc) rc = al((void **)&g->C32[0], (size_t)n * 4);
         if (!rc) rc = al((void **)&g->C32[1], (size_t)n * 4);
         if (!rc) rc = al((void **)&g->it.cnt_part, (size_t)kFoldSlots * kCounters * 8);
+        if (!rc) rc = al((void **)&g->it.res, kResBytes);
         // the fold slots start cleared; every fold clears them again
-        if (!rc && (hipMemset(g->it.dr_part, 0, kFoldSlots * 8) != hipSuccess ||
+        if (!rc && (hipMemset(g->it.res, 0, kResBytes) != hipSuccess ||
+                    hipMemset(g->it.dr_part, 0, kFoldSlots * 8) != hipSuccess ||
                     hipMemset(g->it.rmax_part, 0, kFoldSlots * 8) != hipSuccess ||
                     hipMemset(g->it.cnt_part, 0, (size_t)kFoldSlots * kCounters * 8) != hipSuccess))
             rc = set_error(DFPR_E_DEVICE, "hipMemset of the fold slots failed");
@@ -430,16 +435,12 @@ int dfpr_load_graph(int32_t n, int64_t m, const int32_t *src, const int32_t *dst
     if (!rc) {
         (void)hipGetDevice(&g->device);
         hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, g->device) == hipSuccess && prop.multiProcessorCount > 0)
-        {
+        if (hipGetDeviceProperties(&prop, g->device) == hipSuccess && prop.multiProcessorCount > 0) {
             g->grid = std::min(kMaxGrid, prop.multiProcessorCount * kGridPerCU);
             g->grid_wide = std::min(kMaxGrid, prop.multiProcessorCount * kWideGridPerCU);
             g->grid_wide_df = std::min(kMaxGrid, prop.multiProcessorCount * kWideDfGridPerCU);
         }
-        int coop = 0;
-        if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, g->device) ==
-            hipSuccess)
-            g->coop = coop ? 1 : 0;
+        g->cus = std::min(256, prop.multiProcessorCount);
     }
     if (!rc) {
         Ctl c0;

@@ -3,6 +3,8 @@
 // layout and the marking rules are described at the top of rank.hip.
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace dfpr {
@@ -27,15 +29,37 @@ namespace dfpr {
 #endif
 constexpr int kUnroll = DFPR_UNROLL;   // loads in flight per lane and round
 
-// Streamed index loads: marked non-temporal so that they do not displace
-// gathered contributions from L2.
+// Data that other workgroups change during the launch that reads it.  A
+// launch per iteration reads and writes it with ordinary accesses, the
+// kernel boundary making one iteration's writes visible to the next (COH
+// false).  The resident loop (k_resident in rank.hip) runs many iterations
+// in one launch and uses relaxed agent-scope accesses (COH true): they pass
+// over the vector L1, and a barrier between iterations needs no cache
+// write-back or invalidate.  Random 8-byte gathers of this kind run at the
+// speed of ordinary ones (205 against 212 G/s from 512 KB, equal from 8 MB).
+template <bool COH, class T>
+__device__ __forceinline__ T ld(const T *p)
+{
+    if constexpr (COH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else return *p;
+}
+template <bool COH, class T>
+__device__ __forceinline__ void st(T *p, T v)
+{
+    if constexpr (COH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
+
+// Index loads.  In a launch per iteration they are streamed: marked
+// non-temporal so that they do not displace gathered contributions from L2.
+// The resident loop reads the same indices every iteration and keeps them.
+template <bool COH = false>
 __device__ __forceinline__ int32_t load_idx(const int32_t *p)
 {
 #if DFPR_NT_IDX
-    return __builtin_nontemporal_load(p);
-#else
-    return *p;
+    if constexpr (!COH) return __builtin_nontemporal_load(p);
 #endif
+    return *p;
 }
 
 // Contributions of the first kHubRows vertices (the highest in-degrees, and
@@ -81,6 +105,7 @@ struct IterArgs {
     int32_t it, max_iters;
     int32_t n_stride;
     uint32_t hub;               // contributions to copy into LDS (0: none)
+    struct Stage *stage;        // resident loop: the workgroup's new list entries
 };
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
@@ -109,7 +134,7 @@ struct Acc {
 // ... < cnt, added in that order.  FP64, or (F32) FP32 contributions added
 // with Kahan's compensated summation and returned as sum - compensation in
 // FP64.
-template <bool F32>
+template <bool F32, bool COH>
 __device__ __forceinline__ double gather_sum(const IterArgs &a, const Hub &hub, const int32_t *idx,
                                     uint32_t first, uint32_t step, uint32_t cnt)
 {
@@ -120,12 +145,12 @@ __device__ __forceinline__ double gather_sum(const IterArgs &a, const Hub &hub, 
 #pragma unroll
             for (int j = 0; j < kUnroll; j++) {
                 const uint32_t k = k0 + j * step;
-                i[j] = k < cnt ? load_idx(idx + k) : -1;
+                i[j] = k < cnt ? load_idx<COH>(idx + k) : -1;
             }
             double c[kUnroll];
 #pragma unroll
             for (int j = 0; j < kUnroll; j++)
-                c[j] = i[j] < 0 ? 0.0 : (uint32_t)i[j] < hub.n ? hub.d[i[j]] : a.Cc[i[j]];
+                c[j] = i[j] < 0 ? 0.0 : (uint32_t)i[j] < hub.n ? hub.d[i[j]] : ld<COH>(a.Cc + i[j]);
 #pragma unroll
             for (int j = 0; j < kUnroll; j++)
                 if (i[j] >= 0) s += c[j];
@@ -138,12 +163,13 @@ __device__ __forceinline__ double gather_sum(const IterArgs &a, const Hub &hub, 
 #pragma unroll
             for (int j = 0; j < kUnroll; j++) {
                 const uint32_t k = k0 + j * step;
-                i[j] = k < cnt ? load_idx(idx + k) : -1;
+                i[j] = k < cnt ? load_idx<COH>(idx + k) : -1;
             }
             float c[kUnroll];
 #pragma unroll
             for (int j = 0; j < kUnroll; j++)
-                c[j] = i[j] < 0 ? 0.0f : (uint32_t)i[j] < hub.n ? hub.f[i[j]] : a.C32c[i[j]];
+                c[j] = i[j] < 0 ? 0.0f : (uint32_t)i[j] < hub.n ? hub.f[i[j]]
+                                                              : ld<COH>(a.C32c + i[j]);
 #pragma unroll
             for (int j = 0; j < kUnroll; j++) {
                 if (i[j] >= 0) {
@@ -158,11 +184,36 @@ __device__ __forceinline__ double gather_sum(const IterArgs &a, const Hub &hub, 
     }
 }
 
+// New entries of the class lists of one workgroup of the resident loop, kept
+// in LDS until the workgroup has processed its rows: one atomic per class and
+// workgroup on the list lengths instead of one per wave, round and class
+// (atomics on one address take 13 ns each).
+struct Stage {
+    uint32_t cnt[kBins];        // entries per class
+    uint32_t n;                 // all entries
+    uint32_t cap;               // room in item
+    uint32_t base[kBins];
+    uint2 *item;                // vertex, class << 28 | position among the class's entries
+};
+
 // Wave-aggregated append of the lanes with `take` set to the class lists.
 // Every lane of the wave calls it.
+template <bool COH = false>
 __device__ __forceinline__ void append_to_bins(bool take, int32_t x, int cls, Ctl *ctl, int32_t *bins,
-                                      uint32_t stride)
+                                      uint32_t stride, Stage *stage = nullptr)
 {
+    if constexpr (COH) {
+        if (take) {
+            const uint32_t at = atomicAdd(&stage->n, 1u);
+            if (at < stage->cap) {
+                const uint32_t k = atomicAdd(&stage->cnt[cls], 1u);
+                stage->item[at] = make_uint2((uint32_t)x, (uint32_t)cls << 28 | k);
+            } else {
+                st<true>(&bins[(size_t)cls * stride + atomicAdd(&ctl->live[cls], 1u)], x);
+            }
+        }
+        return;
+    }
     unsigned long long pend = __ballot(take);
     const int lane = lane_id();
     const unsigned long long below = (1ull << lane) - 1ull;
@@ -173,7 +224,7 @@ __device__ __forceinline__ void append_to_bins(bool take, int32_t x, int cls, Ct
         uint32_t base = 0;
         if (lane == leader) base = atomicAdd(&ctl->live[c], (uint32_t)__popcll(mine));
         base = __shfl(base, leader);
-        if (take && cls == c) bins[(size_t)c * stride + base + __popcll(mine & below)] = x;
+        if (take && cls == c) st<COH>(&bins[(size_t)c * stride + base + __popcll(mine & below)], x);
         pend &= ~mine;
     }
 }
@@ -181,7 +232,7 @@ __device__ __forceinline__ void append_to_bins(bool take, int32_t x, int cls, Ct
 // Mark the out-neighbours of w with stamp `sv`.  The calling lanes take
 // positions lane0, lane0 + step, ... (lane0 < step); every lane of every
 // calling wave runs the same number of rounds.
-template <bool SPARSE>
+template <bool SPARSE, bool COH>
 __device__ __forceinline__ void mark_out_row(const IterArgs &a, int32_t w, uint32_t lane0, uint32_t step,
                                     uint32_t sv)
 {
@@ -191,21 +242,23 @@ __device__ __forceinline__ void mark_out_row(const IterArgs &a, int32_t w, uint3
 #pragma unroll
         for (int j = 0; j < kUnroll; j++) {
             const uint32_t k = k0 + lane0 + j * step;
-            x[j] = k < oc ? load_idx(a.out_idx + ob + k) : -1;
+            x[j] = k < oc ? load_idx<COH>(a.out_idx + ob + k) : -1;
         }
-        uint32_t st[kUnroll];
+        uint32_t sx[kUnroll];
 #pragma unroll
-        for (int j = 0; j < kUnroll; j++) st[j] = x[j] >= 0 ? a.stamp[x[j]] : 0xFFFFFFFFu;
+        for (int j = 0; j < kUnroll; j++)
+            sx[j] = x[j] < 0 ? 0xFFFFFFFFu
+                    : SPARSE && COH ? atomicMax(&a.stamp[x[j]], sv) : ld<COH>(a.stamp + x[j]);
 #pragma unroll
         for (int j = 0; j < kUnroll; j++) {
             bool nw = false;
-            if (st[j] < a.sbase) {
-                if (SPARSE) nw = atomicMax(&a.stamp[x[j]], sv) < a.sbase;
-                else a.stamp[x[j]] = sv;
+            if (sx[j] < a.sbase) {
+                if (SPARSE) nw = COH || atomicMax(&a.stamp[x[j]], sv) < a.sbase;
+                else st<COH>(a.stamp + x[j], sv);
             }
             if (SPARSE) {
                 const int cls = nw ? class_of_id(a, x[j]) : 0;
-                append_to_bins(nw, x[j], cls, a.ctl, a.bins, a.n_stride);
+                append_to_bins<COH>(nw, x[j], cls, a.ctl, a.bins, a.n_stride, a.stage);
             }
         }
     }
@@ -226,7 +279,7 @@ __device__ __forceinline__ bool heavy_in_sparse(const IterArgs &a, uint32_t oc)
 // `total` its last value): every lane takes one out-edge per round, so
 // rows with few out-edges share rounds and list appends.  Every lane of
 // the wave calls it with the same `total`.
-template <bool SPARSE>
+template <bool SPARSE, bool COH>
 __device__ __forceinline__ void expand_rows(const IterArgs &a, uint32_t incl, uint32_t deg, uint32_t ob,
                                    uint32_t total, uint32_t sv)
 {
@@ -241,36 +294,39 @@ __device__ __forceinline__ void expand_rows(const IterArgs &a, uint32_t incl, ui
             if (__shfl(incl, j + step - 1) <= tt) j += step;
         const uint32_t first = __shfl(incl, j) - __shfl(deg, j);
         const uint32_t base = __shfl(ob, j);
-        const int32_t x = t < total ? load_idx(a.out_idx + base + (tt - first)) : -1;
-        const uint32_t st = x >= 0 ? a.stamp[x] : 0xFFFFFFFFu;
+        const int32_t x = t < total ? load_idx<COH>(a.out_idx + base + (tt - first)) : -1;
+        // the resident loop's class lists are short: claim at once instead of
+        // looking first (one dependent access less)
+        const uint32_t sx = x < 0 ? 0xFFFFFFFFu
+                            : SPARSE && COH ? atomicMax(&a.stamp[x], sv) : ld<COH>(a.stamp + x);
         bool nw = false;
-        if (st < a.sbase) {
-            if (SPARSE) nw = atomicMax(&a.stamp[x], sv) < a.sbase;
-            else a.stamp[x] = sv;
+        if (sx < a.sbase) {
+            if (SPARSE) nw = COH || atomicMax(&a.stamp[x], sv) < a.sbase;
+            else st<COH>(a.stamp + x, sv);
         }
         if (SPARSE) {
             const int cls = nw ? class_of_id(a, x) : 0;
-            append_to_bins(nw, x, cls, a.ctl, a.bins, a.n_stride);
+            append_to_bins<COH>(nw, x, cls, a.ctl, a.bins, a.n_stride, a.stage);
         }
     }
 }
 
 // Finish one row: Eq. 1, Delta r, writes; returns whether it must expand.
-template <bool DF, bool F32>
+template <bool DF, bool F32, bool COH>
 __device__ __forceinline__ bool finish_row(const IterArgs &a, int32_t v, uint32_t cnt, double s, double rc,
                                   uint32_t oc, Acc &acc)
 {
     const double r = a.base_rank + a.alpha * s;
     const double dr = fabs(r - rc);
-    a.Rn[v] = r;
-    if (F32) a.C32n[v] = (float)(r / (double)oc);
-    else a.Cn[v] = r / (double)oc;
+    st<COH>(a.Rn + v, r);
+    if (F32) st<COH>(a.C32n + v, (float)(r / (double)oc));
+    else st<COH>(a.Cn + v, r / (double)oc);
     acc.dr_max = fmax(acc.dr_max, dr);
     acc.r_max = fmax(acc.r_max, r);
     acc.c[0] += 1;
     acc.c[1] += cnt;
-    if (DF && dr > acc.ftol && a.xstamp[v] != a.sbase) {
-        a.xstamp[v] = a.sbase;
+    if (DF && dr > acc.ftol && ld<COH>(a.xstamp + v) != a.sbase) {
+        st<COH>(a.xstamp + v, a.sbase);
         acc.c[2] += 1;
         acc.c[3] += oc;
         return true;
@@ -278,35 +334,45 @@ __device__ __forceinline__ bool finish_row(const IterArgs &a, int32_t v, uint32_
     return false;
 }
 
-// One wave unit: 64/G rows of a class list (`list`), or of the id range
+// A lane's row of a wave unit: in-edges, out-degree, previous rank, the sum
+// of Eq. 1, and whether this lane finishes it (the row's first lane).
+struct UnitRow {
+    int32_t v;
+    uint32_t cnt, oc;
+    double rc, s;
+    bool mine;
+};
+
+// One wave unit: 64/G rows (COH: at most `per` of them) of a class list (`list`), or of the id range
 // starting at `id0` when `list` is NULL, G lanes per row.  LOOP (G = 1): the
 // id range of rows whose only in-entry was the self-loop at load; few of
 // them are marked, so their stamp is read first, and a row that has since
 // gained in-edges is summed like any class-0 row.
-template <int G, bool DF, bool F32, bool LOOP = false>
-__device__ __forceinline__ void wave_unit(const IterArgs &a, const Hub &hub, const int32_t *list,
-                                          uint32_t id0, uint32_t count, uint32_t first,
-                                          bool check, bool sparse, Acc &acc)
+template <int G, bool DF, bool F32, bool COH, bool LOOP = false>
+__device__ __forceinline__ UnitRow wave_unit(const IterArgs &a, const Hub &hub, const int32_t *list,
+                                          uint32_t id0, uint32_t count, uint32_t first, uint32_t per,
+                                          bool check)
 {
     const int lane = lane_id();
     const int sub = lane & (G - 1);
+    if constexpr (COH) count = min(count, first + per);
     const uint32_t pos = first + lane / G;
     bool active = false;
     int32_t v = 0;
     uint32_t beg = 0, cnt = 0, oc = 1;
     double rc = 0.0;
     if (pos < count) {
-        v = list ? list[pos] : (int32_t)(id0 + pos);
+        v = list ? ld<COH>(list + pos) : (int32_t)(id0 + pos);
         active = true;
         if (LOOP) {
             if (DF && check) {
-                const uint32_t st = a.stamp[v];
-                active = st >= a.sbase && st <= a.sbase + (uint32_t)a.it;
+                const uint32_t sx = ld<COH>(a.stamp + v);
+                active = sx >= a.sbase && sx <= a.sbase + (uint32_t)a.it;
             }
             if (active) {
                 cnt = a.in_cnt[v];
                 beg = a.in_beg[v];
-                rc = a.Rc[v];
+                rc = ld<COH>(a.Rc + v);
                 oc = a.out_cnt[v];
             }
         } else {
@@ -318,12 +384,12 @@ __device__ __forceinline__ void wave_unit(const IterArgs &a, const Hub &hub, con
             beg = a.in_beg[v];
             cnt = a.in_cnt[v];
             if (sub == 0) {
-                rc = a.Rc[v];
+                rc = ld<COH>(a.Rc + v);
                 oc = a.out_cnt[v];
             }
             if (DF && check) {
-                const uint32_t st = a.stamp[v];
-                active = st >= a.sbase && st <= a.sbase + (uint32_t)a.it;
+                const uint32_t sx = ld<COH>(a.stamp + v);
+                active = sx >= a.sbase && sx <= a.sbase + (uint32_t)a.it;
             }
         }
     }
@@ -331,30 +397,42 @@ __device__ __forceinline__ void wave_unit(const IterArgs &a, const Hub &hub, con
     if (active) {
         if (cnt == 1) {
             // the self-loop is the only in-edge
-            if (sub == 0) s = F32 ? (double)a.C32c[v] : a.Cc[v];
+            if (sub == 0) s = F32 ? (double)ld<COH>(a.C32c + v) : ld<COH>(a.Cc + v);
         } else if (LOOP) {
             // a self-loop row that has gained in-edges since the load: rare,
             // summed in index order by its lane (as gather_sum with G = 1)
             if (F32) {
                 float ks = 0.0f, kc = 0.0f;
                 for (uint32_t k = 0; k < cnt; k++) {
-                    const float y = a.C32c[load_idx(a.in_idx + beg + k)] - kc;
+                    const float y = ld<COH>(a.C32c + load_idx<COH>(a.in_idx + beg + k)) - kc;
                     const float t = ks + y;
                     kc = (t - ks) - y;
                     ks = t;
                 }
                 s = (double)ks - (double)kc;
             } else {
-                for (uint32_t k = 0; k < cnt; k++) s += a.Cc[load_idx(a.in_idx + beg + k)];
+                for (uint32_t k = 0; k < cnt; k++)
+                    s += ld<COH>(a.Cc + load_idx<COH>(a.in_idx + beg + k));
             }
         } else {
-            s = gather_sum<F32>(a, hub, a.in_idx + beg, sub, G, cnt);
+            s = gather_sum<F32, COH>(a, hub, a.in_idx + beg, sub, G, cnt);
         }
     }
 #pragma unroll
     for (int off = G / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, G);
+    return {v, cnt, oc, rc, s, active && sub == 0};
+}
+
+// The rest of a wave unit, once its rows are summed: the same code for every
+// class.
+template <bool DF, bool F32, bool COH>
+__device__ __forceinline__ void finish_unit(const IterArgs &a, const UnitRow &row, bool sparse, Acc &acc)
+{
+    const int lane = lane_id();
+    const int32_t v = row.v;
+    const uint32_t oc = row.oc;
     bool expand = false;
-    if (active && sub == 0) expand = finish_row<DF, F32>(a, v, cnt, s, rc, oc, acc);
+    if (row.mine) expand = finish_row<DF, F32, COH>(a, v, row.cnt, row.s, row.rc, oc, acc);
     // Rows with fewer out-edges than a wave has lanes expand together, one
     // out-edge per lane and round; longer rows one at a time with the whole
     // wave and kUnroll loads in flight per lane.
@@ -372,10 +450,10 @@ __device__ __forceinline__ void wave_unit(const IterArgs &a, const Hub &hub, con
             }
             const uint32_t total = __shfl(incl, kWave - 1);
             if (sparse && !acc.plain) {
-                expand_rows<true>(a, incl, deg, ob, total, sv);
+                expand_rows<true, COH>(a, incl, deg, ob, total, sv);
             } else {
-                if (sparse && lane == 0) a.ctl->force_dense = 1;
-                expand_rows<false>(a, incl, deg, ob, total, sv);
+                if (sparse && lane == 0) st<COH>(&a.ctl->force_dense, 1u);
+                expand_rows<false, COH>(a, incl, deg, ob, total, sv);
             }
         }
         unsigned long long q = __ballot(expand && !small);
@@ -384,57 +462,86 @@ __device__ __forceinline__ void wave_unit(const IterArgs &a, const Hub &hub, con
             const int32_t w = __shfl(v, l);
             const uint32_t wc = __shfl(oc, l);
             if (sparse && !acc.plain && !heavy_in_sparse(a, wc)) {
-                mark_out_row<true>(a, w, lane, kWave, sv);
+                mark_out_row<true, COH>(a, w, lane, kWave, sv);
             } else {
-                if (sparse && lane == 0) a.ctl->force_dense = 1;
-                mark_out_row<false>(a, w, lane, kWave, sv);
+                if (sparse && lane == 0) st<COH>(&a.ctl->force_dense, 1u);
+                mark_out_row<false, COH>(a, w, lane, kWave, sv);
             }
             q &= q - 1;
         }
     }
 }
 
-// One row of more than 1024 in-edges, the whole workgroup.  All threads
-// call it with the same v.
-template <bool DF, bool F32>
+// Rows of more than 1024 in-edges (by their class).  The sum of such a row is
+// that of strided parts, part p adding entries p, p + parts, ... in order: the
+// parts of 64 neighbours fold with the butterfly of a wave, and the folds are
+// added in order.  A row has kBlock parts, or, in FP64 with more than kLongRow
+// in-edges, kLongParts.  The resident loop gives such a long row a workgroup
+// of kLongParts threads, because one of 10^4 in-edges in 256 parts was the
+// last thing every iteration waited for (13 us of 26 on R-MAT scale 18);
+// kBlock threads take its parts in four passes, which sums the same bits.
+// The line at 2048 against 1024 / 4096, per update pair: R-MAT scale 16
+// 1.94 against 1.84 / 2.03 ms, scale 20 9.47 against 10.06 / 9.41, scale 22
+// (launches) 29.97 against 30.80 / 30.03.
+// The FP32 form keeps kBlock parts: with more, its Kahan sums would round
+// differently.
+constexpr uint32_t kLongRow = 2048;
+constexpr int kLongParts = 1024;
+constexpr int kLongFolds = kLongParts / kWave;
+
+// T threads per row, kBlock or kLongParts; a workgroup of more threads sums
+// one row per T of them (its sub-blocks).  Every thread calls it, whether its
+// sub-block has a row (`valid`) or not.
+template <bool DF, bool F32, bool COH, int T>
 __device__ __forceinline__ void block_row(const IterArgs &a, const Hub &hub, int32_t v, bool valid,
                                  bool check, bool sparse, Acc &acc, double *red, int *flag)
 {
-    // A row of this class is summed by kBlock threads; a workgroup of more
-    // threads sums one such row per kBlock of them (its sub-blocks), each
-    // with the same partition and order as a kBlock workgroup.  Every
-    // thread reaches the barriers, whether its sub-block has a row or not.
-    const uint32_t t = threadIdx.x % kBlock;
+    const uint32_t t = threadIdx.x % T;
     bool active = valid;
     if (active && DF && check) {
-        const uint32_t st = a.stamp[v];
-        active = st >= a.sbase && st <= a.sbase + (uint32_t)a.it;
+        const uint32_t sx = ld<COH>(a.stamp + v);
+        active = sx >= a.sbase && sx <= a.sbase + (uint32_t)a.it;
     }
     uint32_t cnt = 0;
     if (active) {
-        const uint32_t beg = a.in_beg[v];
         cnt = a.in_cnt[v];
-        double s = gather_sum<F32>(a, hub, a.in_idx + beg, t, kBlock, cnt);
+    }
+    const bool lng = !F32 && cnt > kLongRow;
+    if (active) {
+        const int32_t *idx = a.in_idx + a.in_beg[v];
+        auto pass = [&](uint32_t q, auto step) {
+            double s = gather_sum<F32, COH>(a, hub, idx, q * T + t, decltype(step)::value, cnt);
 #pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
-        if (lane_id() == 0) red[t / kWave] = s;
+            for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
+            if (lane_id() == 0) red[q * (T / kWave) + t / kWave] = s;
+        };
+        if (!lng) {
+            if (T == kBlock || t < kBlock) pass(0, std::integral_constant<uint32_t, kBlock>());
+        } else {
+#pragma unroll 1
+            for (uint32_t q = 0; q < kLongParts / T; q++)
+                pass(q, std::integral_constant<uint32_t, kLongParts>());
+        }
     }
     __syncthreads();
     if (t == 0) {
         *flag = 0;
         if (active) {
-            const double r = ((red[0] + red[1]) + red[2]) + red[3];
-            *flag = finish_row<DF, F32>(a, v, cnt, r, a.Rc[v], a.out_cnt[v], acc) ? 1 : 0;
+            double r = ((red[0] + red[1]) + red[2]) + red[3];
+            if (lng)
+                for (int w = kBlock / kWave; w < kLongFolds; w++) r += red[w];
+            *flag = finish_row<DF, F32, COH>(a, v, cnt, r, ld<COH>(a.Rc + v), a.out_cnt[v], acc)
+                        ? 1 : 0;
         }
     }
     __syncthreads();
     if (DF && *flag) {
         const uint32_t sv = a.sbase + (uint32_t)a.it + 1;
         if (sparse && !acc.plain && !heavy_in_sparse(a, a.out_cnt[v])) {
-            mark_out_row<true>(a, v, t, kBlock, sv);
+            mark_out_row<true, COH>(a, v, t, T, sv);
         } else {
-            if (sparse && t == 0) a.ctl->force_dense = 1;
-            mark_out_row<false>(a, v, t, kBlock, sv);
+            if (sparse && t == 0) st<COH>(&a.ctl->force_dense, 1u);
+            mark_out_row<false, COH>(a, v, t, T, sv);
         }
     }
     __syncthreads();
@@ -477,6 +584,7 @@ __device__ __forceinline__ void block_fold(double &dr, double &rm, unsigned long
 // of classes 5..0 and then of the self-loop-only rows (their own id
 // range; class lists hold them in class 0), in that order; block units are
 // the class-6 rows.
+constexpr uint32_t kSkips = 8;
 struct Plan {
     double ftol;                // frontier tolerance in effect
     uint32_t plain;             // Ctl::plain_marks
@@ -486,18 +594,22 @@ struct Plan {
     uint32_t loop_cnt;          // the self-loop rows' id range (full schedule, DF)
     uint32_t loop_id0;
     uint32_t ustart[kBins];     // k < kBins - 1: class kBins - 2 - k; kBins - 1: loop rows
+    uint32_t per[kBins];        // resident loop: rows of a wave unit of each class
+    uint32_t lo[kSkips];        //   workgroups that sit out each of the first rounds
     uint32_t nwu, nbu;
+    uint32_t nlong;             // resident loop: block rows after which none is long
 };
 
-__device__ __forceinline__ void make_plan(const IterArgs &a, const Ctl *ctl, bool sparse, bool df, int par,
-                                 Plan &p)
+// `snap`: the lengths of the class lists this iteration processes (sparse).
+__device__ __forceinline__ void make_plan(const IterArgs &a, const Ctl *ctl, bool sparse, bool df,
+                                          const uint32_t *snap, Plan &p)
 {
     // a negative frontier tolerance asks for the call's adaptive choice
     p.ftol = a.ftol >= 0.0 ? a.ftol : ctl->ftol_used;
     p.plain = ctl->plain_marks;
     for (int b = 0; b < kBins; b++) {
         if (sparse) {
-            p.cnt[b] = ctl->snap[par][b];
+            p.cnt[b] = snap[b];
             p.list[b] = a.bins + (size_t)b * a.n_stride;
             p.id0[b] = 0;
         } else {
@@ -528,6 +640,102 @@ __device__ __forceinline__ void make_plan(const IterArgs &a, const Ctl *ctl, boo
     p.nbu = p.cnt[kBins - 1];
 }
 
+// log2 of the rows of a full wave unit of class b < kBins - 1.
+__device__ __forceinline__ int lg_rows(int b)
+{
+    return b < 4 ? 6 - b : 5 - b;
+}
+
+// The same by one wave, for `waves` waves.  While the class lists hold fewer
+// rows than the waves could take, a wave unit takes fewer rows: a wave's
+// rows expand one round of out-edges after another, so a small frontier is
+// done soonest when it is spread over all waves.  p.ftol and p.plain are
+// left alone (they hold for the whole call).
+// On the full schedule block rows follow decreasing in-degree too: workgroup
+// b of G has long rows b, b + G, ..., and four of the others at a time, so the
+// first ones are busy longest.  A long row takes about as long as
+// 1 + in-edges / 16384 rounds of wave units (R-MAT scales 16 and 18), four of
+// the others one; a workgroup sits out as many rounds as its rows take beyond
+// those of the last workgroup.
+__device__ __forceinline__ void make_plan_wave(const IterArgs &a, const Ctl *ctl, bool sparse, bool df,
+                                               const uint32_t *snap, uint32_t G, uint32_t waves, Plan &p)
+{
+    const int lane = lane_id();
+    const int b = lane < kBins ? lane : kBins - 1;
+    uint32_t id0 = 0, cnt, loops = 0;
+    if (sparse) {
+        cnt = snap[b];
+    } else {
+        id0 = ctl->cls[kBins - 1 - b];
+        cnt = ctl->cls[kBins - b] - id0;
+        loops = ctl->cls[kBins + 1] - ctl->cls[kBins];
+        if (!df && b == 0) cnt += loops;
+        if (!df) loops = 0;
+    }
+    const bool unit = lane < kBins - 1;
+    int lg = lg_rows(b);
+    uint32_t n = unit ? (cnt + (1u << lg) - 1) >> lg : 0u;
+    if (sparse) {
+        uint32_t tot = n;
+#pragma unroll
+        for (int off = 4; off > 0; off >>= 1) tot += __shfl_xor(tot, off, 8);
+        if (tot && tot < waves) {
+            // the largest halving of the units that the waves take at once
+            int s = __clz((int)tot) - __clz((int)waves);
+            if (tot << s > waves) s--;
+            lg = max(0, lg - s);
+            n = unit ? (cnt + (1u << lg) - 1) >> lg : 0u;
+        }
+    }
+    // units of the classes above this one come first
+    uint32_t before = 0, tot = 0;
+#pragma unroll
+    for (int j = 0; j < kBins - 1; j++) {
+        const uint32_t x = __shfl(n, j);
+        tot += x;
+        if (j > b) before += x;
+    }
+    if (lane < kBins) {
+        p.cnt[b] = cnt;
+        p.list[b] = sparse ? a.bins + (size_t)b * a.n_stride : nullptr;
+        p.id0[b] = id0;
+        p.per[b] = 1u << lg;
+        p.ustart[unit ? kBins - 2 - b : kBins - 1] = unit ? before : tot;
+        if (!unit) {
+            p.loop_cnt = loops;
+            p.loop_id0 = ctl->cls[kBins];
+            p.nwu = tot + (loops + kWave - 1) / kWave;
+            p.nbu = cnt;
+        }
+    }
+    const uint32_t nbu = __shfl(cnt, kBins - 1), first = __shfl(id0, kBins - 1);
+    uint32_t lo[kSkips] = {0}, nlong = nbu;
+    if (!sparse && nbu) {
+        nlong = 0;
+        for (uint32_t u0 = 0; u0 < nbu; u0 += kWave) {
+            const unsigned long long m =
+                __ballot(u0 + lane < nbu && a.in_cnt[first + u0 + lane] > kLongRow);
+            if (m) nlong = u0 + kWave - __clzll((long long)m);
+        }
+        auto rounds = [&](uint32_t w) {
+            uint32_t c = 0;
+            for (uint32_t u = w; u < nlong; u += G) c += 1 + (a.in_cnt[first + u] >> 14);
+            for (uint32_t u = nlong + (w + G - nlong % G) % G * 4; u < nbu; u += 4 * G) c++;
+            return c;
+        };
+        const uint32_t least = rounds(G - 1);
+        for (uint32_t w0 = 0; w0 < G; w0 += kWave) {
+            const uint32_t c = w0 + lane < G ? rounds(w0 + lane) : 0u;
+#pragma unroll
+            for (uint32_t r = 0; r < kSkips; r++) lo[r] += (uint32_t)__popcll(__ballot(c > least + r));
+        }
+    }
+    if (lane == 0) p.nlong = nlong;
+#pragma unroll
+    for (uint32_t r = 0; r < kSkips; r++)
+        if (lane == 0) p.lo[r] = min(lo[r], G - 1);
+}
+
 // Workgroups that have work in an iteration: 0 .. active-1.  With no work
 // at all, workgroup 0 alone records the (empty) iteration.
 template <int NW = kWavesPerBlock>
@@ -542,7 +750,7 @@ __device__ __forceinline__ uint32_t active_blocks(const Plan &p, uint32_t grid)
 template <int NW = kWavesPerBlock>
 struct IterSharedT {
     Plan plan;
-    double red[NW];
+    double red[NW / kWavesPerBlock * kLongFolds];
     int flag[NW / kWavesPerBlock];
     double wdr[NW], wrm[NW];
     unsigned long long wc[NW][kCounters];
@@ -567,6 +775,85 @@ struct FinalShared {
     unsigned long long wc[kFinalWaves][kCounters];
 };
 
+// Workgroup blk of G processes its share of the rows of the plan in sh.  A
+// launch per iteration gives a workgroup NW neighbouring wave units at a
+// time.  The resident loop (COH) deals the units out one workgroup after the
+// other, so that a few long units, or a frontier of few units, are spread
+// over all compute units.
+template <bool DF, bool F32, int NW, bool COH>
+__device__ __forceinline__ void iter_rows(const IterArgs &a, const Hub &hub, uint32_t blk, uint32_t G,
+                                          IterSharedT<NW> &sh, bool check, bool sparse, Acc &acc)
+{
+    const uint32_t nbu = sh.plan.nbu, nwu = sh.plan.nwu;
+    const int wave = threadIdx.x / kWave;
+    auto unit_rows = [&](uint32_t u, int k) -> UnitRow {
+        if (k == kBins - 1) {
+            const uint32_t first = (u - sh.plan.ustart[k]) * kWave;
+            return wave_unit<1, DF, F32, COH, true>(a, hub, nullptr, sh.plan.loop_id0,
+                                                    sh.plan.loop_cnt, first, kWave, check);
+        }
+        const int b = kBins - 2 - k;
+        const uint32_t per = COH ? sh.plan.per[b] : kWave / group_of(b);
+        const uint32_t first = (u - sh.plan.ustart[k]) * per;
+        const int32_t *list = sh.plan.list[b];
+        const uint32_t id0 = sh.plan.id0[b];
+        const uint32_t cnt = sh.plan.cnt[b];
+        switch (b) {
+        case 0: return wave_unit<1, DF, F32, COH>(a, hub, list, id0, cnt, first, per, check);
+        case 1: return wave_unit<2, DF, F32, COH>(a, hub, list, id0, cnt, first, per, check);
+        case 2: return wave_unit<4, DF, F32, COH>(a, hub, list, id0, cnt, first, per, check);
+        case 3: return wave_unit<8, DF, F32, COH>(a, hub, list, id0, cnt, first, per, check);
+        case 4: return wave_unit<32, DF, F32, COH>(a, hub, list, id0, cnt, first, per, check);
+        default: return wave_unit<64, DF, F32, COH>(a, hub, list, id0, cnt, first, per, check);
+        }
+    };
+    const int32_t *blist = sh.plan.list[kBins - 1];
+    // sub-blocks of T threads take rows from u0 on, one each, up to n
+    auto block_rows = [&](auto threads, uint32_t u0, uint32_t n) {
+        constexpr int T = decltype(threads)::value;
+        constexpr uint32_t S = NW * kWave / T;
+        const uint32_t sub = threadIdx.x / T;
+        for (; u0 < n; u0 += G * S) {
+            const uint32_t u = u0 + sub;
+            const bool valid = u < n;
+            const int32_t v = !valid ? 0 : blist ? ld<COH>(blist + u)
+                                                 : (int32_t)(sh.plan.id0[kBins - 1] + u);
+            block_row<DF, F32, COH, T>(a, hub, v, valid, check, sparse, acc,
+                                       sh.red + sub * kLongFolds, sh.flag + sub);
+        }
+    };
+    constexpr std::integral_constant<int, kBlock> quarter{};
+    if constexpr (COH && !F32) {
+        // the long rows one per workgroup, then, from the next workgroup on,
+        // the others four at a time
+        const uint32_t nlong = sh.plan.nlong;
+        block_rows(std::integral_constant<int, kLongParts>(), blk, nlong);
+        block_rows(quarter, nlong + (blk + G - nlong % G) % G * (NW * kWave / kBlock), nbu);
+    } else {
+        block_rows(quarter, blk * (NW * kWave / kBlock), nbu);
+    }
+    auto run = [&](uint32_t u) {
+        int k = 0;
+        while (k + 1 < kBins && u >= sh.plan.ustart[k + 1]) k++;
+        const UnitRow row = unit_rows(u, k);
+        finish_unit<DF, F32, COH>(a, row, sparse, acc);
+    };
+    if constexpr (!COH) {
+        for (uint32_t u = blk * NW + wave; u < nwu; u += G * NW) run(u);
+    } else {
+        // a round is one unit per wave of workgroups lo .. G - 1; those
+        // before lo had longer block rows and sit it out
+        uint32_t r = 0;
+        for (uint32_t u0 = 0; u0 < nwu; r++) {
+            const uint32_t lo = r < kSkips ? sh.plan.lo[r] : 0u;
+            const uint32_t w = G - lo;
+            const uint32_t u = u0 + (blk - lo) + wave * w;
+            if (blk >= lo && u < nwu) run(u);
+            u0 += w * NW;
+        }
+    }
+}
+
 // One workgroup's share of an iteration of one graph: workgroup blk of the
 // G workgroups given to the graph.  Its results are folded into slot
 // blk mod kFoldSlots.
@@ -579,10 +866,9 @@ __device__ __forceinline__ void iter_body(const IterArgs &a, uint32_t blk, uint3
     const int par = a.it & 1;
     const bool sparse = DF && !ctl->dense;
     const bool check = DF && !sparse;
-    if (threadIdx.x == 0) make_plan(a, ctl, sparse, DF, par, sh.plan);
+    if (threadIdx.x == 0) make_plan(a, ctl, sparse, DF, ctl->snap[par], sh.plan);
     __syncthreads();
     if (blk >= active_blocks<NW>(sh.plan, G)) return;
-    const uint32_t nbu = sh.plan.nbu, nwu = sh.plan.nwu;
     // a sweep over the full schedule reads the hub contributions from LDS
     Hub hub{hub_lds, reinterpret_cast<const float *>(hub_lds), 0u};
     if (hub_lds && a.hub && !sparse) {
@@ -599,43 +885,7 @@ __device__ __forceinline__ void iter_body(const IterArgs &a, uint32_t blk, uint3
     Acc acc;
     acc.ftol = sh.plan.ftol;
     acc.plain = sh.plan.plain != 0;
-    const int wave = threadIdx.x / kWave;
-    auto run_unit = [&](uint32_t u, int k) {
-        if (k == kBins - 1) {
-            const uint32_t first = (u - sh.plan.ustart[k]) * kWave;
-            wave_unit<1, DF, F32, true>(a, hub, nullptr, sh.plan.loop_id0, sh.plan.loop_cnt,
-                                        first, check, sparse, acc);
-            return;
-        }
-        const int b = kBins - 2 - k;
-        const uint32_t first = (u - sh.plan.ustart[k]) * (kWave / group_of(b));
-        const int32_t *list = sh.plan.list[b];
-        const uint32_t id0 = sh.plan.id0[b];
-        const uint32_t cnt = sh.plan.cnt[b];
-        switch (b) {
-        case 0: wave_unit<1, DF, F32>(a, hub, list, id0, cnt, first, check, sparse, acc); break;
-        case 1: wave_unit<2, DF, F32>(a, hub, list, id0, cnt, first, check, sparse, acc); break;
-        case 2: wave_unit<4, DF, F32>(a, hub, list, id0, cnt, first, check, sparse, acc); break;
-        case 3: wave_unit<8, DF, F32>(a, hub, list, id0, cnt, first, check, sparse, acc); break;
-        case 4: wave_unit<32, DF, F32>(a, hub, list, id0, cnt, first, check, sparse, acc); break;
-        default: wave_unit<64, DF, F32>(a, hub, list, id0, cnt, first, check, sparse, acc); break;
-        }
-    };
-    const int32_t *blist = sh.plan.list[kBins - 1];
-    constexpr uint32_t S = NW / kWavesPerBlock;     // sub-blocks of kBlock threads
-    const uint32_t sub = threadIdx.x / kBlock;
-    for (uint32_t u0 = blk * S; u0 < nbu; u0 += G * S) {
-        const uint32_t u = u0 + sub;
-        const bool valid = u < nbu;
-        const int32_t v = !valid ? 0 : blist ? blist[u] : (int32_t)(sh.plan.id0[kBins - 1] + u);
-        block_row<DF, F32>(a, hub, v, valid, check, sparse, acc, sh.red + sub * kWavesPerBlock,
-                           sh.flag + sub);
-    }
-    for (uint32_t u = blk * NW + wave; u < nwu; u += G * NW) {
-        int k = 0;
-        while (k + 1 < kBins && u >= sh.plan.ustart[k + 1]) k++;
-        run_unit(u, k);
-    }
+    iter_rows<DF, F32, NW, false>(a, hub, blk, G, sh, check, sparse, acc);
 
     double dr = acc.dr_max, rm = acc.r_max;
     unsigned long long c[kCounters];
@@ -655,11 +905,61 @@ __device__ __forceinline__ void iter_body(const IterArgs &a, uint32_t blk, uint3
     }
 }
 
+// The state after iteration a.it, from its folded results: the control
+// block's statistics, convergence or the cap, the next iteration's class
+// lists and walk.  One thread.  In the FP32 phase of the precision form,
+// reaching tol or the FP32 resolution of the ranks ends the phase instead of
+// the call.  `lists`: the class lists' lengths and Ctl::force_dense.
+__device__ __forceinline__ void final_step(const IterArgs &a, Ctl *ctl, const uint32_t *lists, bool sparse,
+                                           bool f32, double dr, double rm)
+{
+    const int par = a.it & 1;
+    ctl->iterations = a.it + 1;
+    ctl->final_linf = dr;
+    ctl->final_rmax = rm;
+    if (sparse) {
+        unsigned long long before = 0, after = 0;
+#pragma unroll
+        for (int b = 0; b < kBins; b++) {
+            before += ctl->snap[par][b];
+            after += lists[b];
+            ctl->snap[par ^ 1][b] = lists[b];
+        }
+        ctl->marked += after - before;
+        if (after > a.sparse_limit || lists[kBins]) ctl->dense = 1;
+    }
+    if (f32) {
+        // FP32 contributions carry a relative rounding error of 2^-24;
+        // changes below about 2^-22 of the largest rank are noise.  A
+        // Delta R that stops falling counts as a stall only near that
+        // floor (early on it can rise while the frontier grows).
+        const double floor32 = rm * 0x1p-22;
+        const bool stalled = ctl->phase_iters >= 3 && dr >= 0.97 * ctl->prev_linf &&
+                             dr <= rm * 0x1p-16;
+        ctl->phase_iters += 1;
+        if (dr <= a.tol || dr <= floor32 || stalled) ctl->phase_end = 1;
+        if (a.it + 1 >= a.max_iters) ctl->done = 1;
+    } else {
+        const bool conv = dr <= a.tol;
+        if (conv) ctl->converged = 1;
+        if (conv || a.it + 1 >= a.max_iters) ctl->done = 1;
+    }
+    ctl->prev_linf = dr;
+}
+
+// The control block to a host-visible copy by one wave of a workgroup whose
+// thread 0 made the last updates, after a workgroup barrier.
+__device__ __forceinline__ void ctl_to_mirror(const Ctl *ctl, Ctl *mirror)
+{
+    constexpr int words = (int)(sizeof(Ctl) / 4);
+    const uint32_t *src = reinterpret_cast<const uint32_t *>(ctl);
+    uint32_t *dst = reinterpret_cast<uint32_t *>(mirror);
+    for (int i = threadIdx.x; i < words; i += kWave) dst[i] = ld<true>(src + i);
+}
+
 // After each iteration (one workgroup): fold the slots the iteration's
 // workgroups left, decide convergence or the cap, and prepare the next
 // iteration.  The launch boundary orders it after k_iter.
-// In the FP32 phase of the precision form, reaching tol or the FP32
-// resolution of the ranks ends the phase instead of the call.
 // The control block goes to the host mirror when `last` (the last launch
 // the host queued before it next waits) or when this step ends the call or
 // the phase: later launches then return at once.
@@ -667,7 +967,6 @@ __device__ __forceinline__ void final_body(const IterArgs &a, bool df, bool f32,
 {
     Ctl *ctl = a.ctl;
     if (ctl->done || (f32 && ctl->phase_end)) return;
-    const int par = a.it & 1;
     const bool sparse = df && !ctl->dense;
     double dr = 0.0, rm = 0.0;
     unsigned long long c[kCounters] = {0, 0, 0, 0};
@@ -688,51 +987,16 @@ __device__ __forceinline__ void final_body(const IterArgs &a, bool df, bool f32,
         ctl->edges += c[1];
         ctl->xverts += c[2];
         ctl->xedges += c[3];
-        ctl->iterations = a.it + 1;
-        ctl->final_linf = dr;
-        ctl->final_rmax = rm;
-        if (sparse) {
-            unsigned long long before = 0, after = 0;
-            for (int b = 0; b < kBins; b++) {
-                const uint32_t l = ctl->live[b];
-                before += ctl->snap[par][b];
-                after += l;
-                ctl->snap[par ^ 1][b] = l;
-            }
-            ctl->marked += after - before;
-            if (after > a.sparse_limit || ctl->force_dense) ctl->dense = 1;
-        }
-        if (f32) {
-            // FP32 contributions carry a relative rounding error of 2^-24;
-            // changes below about 2^-22 of the largest rank are noise.  A
-            // Delta R that stops falling counts as a stall only near that
-            // floor (early on it can rise while the frontier grows).
-            const double floor32 = rm * 0x1p-22;
-            const bool stalled = ctl->phase_iters >= 3 && dr >= 0.97 * ctl->prev_linf &&
-                                 dr <= rm * 0x1p-16;
-            ctl->phase_iters += 1;
-            if (dr <= a.tol || dr <= floor32 || stalled) ctl->phase_end = 1;
-            if (a.it + 1 >= a.max_iters) ctl->done = 1;
-        } else {
-            const bool conv = dr <= a.tol;
-            if (conv) ctl->converged = 1;
-            if (conv || a.it + 1 >= a.max_iters) ctl->done = 1;
-        }
-        ctl->prev_linf = dr;
+        uint32_t lists[kBins + 1];
+#pragma unroll
+        for (int b = 0; b < kBins; b++) lists[b] = ctl->live[b];
+        lists[kBins] = ctl->force_dense;
+        final_step(a, ctl, lists, sparse, f32, dr, rm);
         sh.copy = a.mirror && (last || ctl->done || (f32 && ctl->phase_end));
     }
     __syncthreads();
-    if (sh.copy && threadIdx.x < kWave) {
-        // one wave copies the words of the block (thread 0's updates are
-        // visible after the barrier)
-        constexpr int words = (int)(sizeof(Ctl) / 4);
-        const volatile uint32_t *src = reinterpret_cast<const volatile uint32_t *>(ctl);
-        uint32_t *dst = reinterpret_cast<uint32_t *>(a.mirror);
-        for (int i = threadIdx.x; i < words; i += kWave) dst[i] = src[i];
-    }
+    if (sh.copy && threadIdx.x < kWave) ctl_to_mirror(ctl, a.mirror);
 }
-
-
 
 }  // namespace dfpr
 

@@ -69,7 +69,7 @@ int dfpr_pagerank_dynamic_frontier_device_noalloc(dfpr_graph *g, const dfpr_para
     dfpr_params q;
     if (p) q = *p;
     else dfpr_params_default(&q);
-    // the cooperative small-frontier launch is left out of this path
+    // DFPR_LOOP_DEVICE is not offered on this path
     q.loop = DFPR_LOOP_LAUNCHES;
     int32_t *buf = nullptr;
     const int rc = scratch_on(g->device, &buf);

@@ -10,7 +10,9 @@
 // workgroups folded their results into and decides convergence
 // (Delta R <= tol) or the iteration cap.
 // The host enqueues iterations in chunks and reads the stop flag between
-// chunks; launches issued after the stop flag is set return at once.
+// chunks; launches issued after the stop flag is set return at once.  On
+// small graphs, and while a frontier is small, the same iterations run inside
+// one launch of k_resident instead (below).
 //
 // Work layout.  Rows are split by in-degree into classes; a class-b row is
 // reduced by group_of(b) lanes of one wave (1, 2, 4, 8, 32 or 64 lanes) or,
@@ -117,120 +119,357 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(IterArgs a, int df, int
 }
 
 // ---------------------------------------------------------------------------
-// small-frontier loop
+// resident loop
 // ---------------------------------------------------------------------------
-// While the class lists hold few rows, an iteration's two launches and their
-// kernel boundaries cost more than its rows.  k_loop runs the iterations of
-// Algorithm 1's loop inside one cooperative launch of a few workgroups
-// instead: the rows of an iteration are spread over the workgroups exactly as
-// in k_iter, a grid barrier separates the pull from the fold (workgroup 0
-// runs final_body), and a second barrier publishes the new control block.
-// The launch hands back to the host loop when the call or the FP32 phase
-// ends, when an iteration has more rows than `limit` or the call moves to
-// the full schedule, or after kLoopChunk iterations.  Every row is summed
-// as in k_iter, so the ranks do not depend on which loop ran an iteration.
-#ifndef DFPR_LOOP_GRID
-#define DFPR_LOOP_GRID 64
-#endif
-#ifndef DFPR_LOOP_ROWS
-#define DFPR_LOOP_ROWS 16384
-#endif
-constexpr int kLoopGrid = DFPR_LOOP_GRID;        // workgroups of the small-frontier loop
-constexpr uint32_t kLoopRows = DFPR_LOOP_ROWS;   // most rows of an iteration it runs
-constexpr uint32_t kSpinLimit = 1u << 22;        // polls of a grid barrier before it gives up
+// Where an iteration's rows take less time than its two launches and the
+// dispatch between them (about 20 us from one k_iter to the next on a small
+// frontier), k_resident runs the iterations of Algorithm 1's loop inside one
+// launch: one workgroup of 16 waves per compute unit at most, rows spread and
+// summed exactly as in k_iter, and a barrier between iterations that carries
+// the fold.
+//
+// What bounds it is the barrier and one chain of dependent accesses per
+// iteration.  A barrier with agent-scope release and acquire fences took
+// 9 us for 64 workgroups and 31 us for 256, because the fences write back
+// and invalidate L2; so every access to data that another workgroup writes
+// during the launch is a relaxed agent-scope one (COH, iter.h), each wave
+// waits for its own stores to be acknowledged (s_waitcnt vmcnt(0)) before
+// its workgroup arrives, and the barrier has no fence: 1.4 us for 64
+// workgroups, 1.7 us for 256.
+//
+// Arrival: a workgroup stores its Delta R and largest rank as four tagged
+// words.  Workgroup 0 polls all of them (a thread per word), folds them,
+// takes the decision of final_step on a copy of the control block in LDS, and
+// publishes the state of the next iteration as eight tagged words, in eight
+// copies so that an XCD's workgroups poll one of their own.  A word is
+// 32 bits of value and a 32-bit tag that no other barrier of the graph uses,
+// so a word is its own flag and nothing is cleared between launches.
+//
+// No cooperative launch: before anything is written, the workgroups wait a
+// bounded time until all of them run, and one compare-and-swap decides for
+// all whether they go or leave.  Other work on the device can so at worst
+// send a call back to the launch pairs.
+// Where it is used.  Graphs of up to kResEdges in-edges run whole calls in
+// it, because their full sweep is short next to the launches or gains from
+// the larger LDS copy: against launches, an update pair took 1.56 / 2.15 ms on
+// a 10,000-vertex G(n, m), 9.5 / 12.9 ms on R-MAT scale 20 and 15.1 / 16.8 ms
+// on scale 21 (35M edges).  On scale 22 (69M) its 16 waves per compute unit
+// and gathers past the vector L1 lose to k_iter_wide (32.9 / 30.1 ms), so
+// larger graphs use it only while a Dynamic Frontier call is on the class
+// lists.
+constexpr int64_t kResEdges = 40000000;
+// In the resident loop a row goes to a class list by an LDS-staged append, so
+// the lists may hold an eighth of the vertices before walking every id range
+// with its stamp is quicker (a 64th with launches): 1.57 against 2.35 ms on
+// uniform grid batches, no change on R-MAT.
+constexpr int32_t kResSparse = 8;
+constexpr uint32_t kLoopRows = 16384;            // DFPR_LOOP_DEVICE: most rows of an iteration
+constexpr int kResWaves = 16;
+constexpr int kResThreads = kResWaves * kWave;
+constexpr int kResMax = kResThreads / 4;         // workgroups: four words each to poll
+constexpr uint32_t kResHub = 16384;              // contributions in LDS (twice as many FP32)
+constexpr int kResSteps = 1024;                  // most iterations of one launch
+constexpr uint32_t kResTags = kResSteps + 4;     // tags a launch takes
+constexpr uint32_t kGoSpin = 256;                // polls before a launch gives up starting
+constexpr uint32_t kSpinLimit = 1u << 24;        // polls of a barrier before it reports failure
+constexpr int kResCopies = 8;                    // copies of the published state
 
-struct LoopArgs {
-    double *R[2], *C[2];
-    float *C32[2];
-    int32_t base;       // buffer that iteration it0 reads
-    int32_t it0;        // first iteration of the phase (buffer parity)
-    int32_t it_start;   // first iteration of this launch
-    uint32_t limit;     // rows of an iteration above which the launch hands over
-    int32_t bar;        // barrier counter of the control block
+// What the workgroups of a resident loop exchange (dfpr_graph::it.res).
+struct ResWords {
+    unsigned long long arrive[kResMax * 4];          // per workgroup: Delta R, largest rank
+    unsigned long long state[kResCopies * 8];        // flags, class list lengths
+    unsigned long long count[kResMax * kCounters];   // counters of the launch, at its end
 };
 
-// All workgroups of the launch meet here.  The counter only grows: the
-// k-th barrier of a launch waits for k * gridDim.x arrivals.  Releases and
-// acquires are at agent scope, so the rows, marks and lists one workgroup
-// wrote are visible to all after it.  Returns false if the others did not
-// arrive within kSpinLimit polls (every workgroup then leaves the loop).
-__device__ inline bool grid_barrier(uint32_t *count, uint32_t target, int *s_ok)
+static_assert(sizeof(ResWords) <= kResBytes, "kResBytes holds the exchanged words");
+
+struct ResArgs {
+    double *R[2], *C[2];
+    float *C32[2];
+    ResWords *w;
+    int base;           // buffer that iteration it0 reads
+    int it0;            // first iteration of the phase (buffer parity)
+    int it_start;       // first iteration of this launch
+    int full;           // the launch keeps going on the full schedule
+    int go;             // its entry of Ctl::loop_go
+    uint32_t limit;     // class list rows of an iteration above which it hands over
+    uint32_t tag;       // first of its tags
+};
+
+struct ResShared {
+    Ctl ctl;                            // workgroup 0: the control block
+    unsigned long long wmax[kResWaves][2];
+    double wdr[kResWaves], wrm[kResWaves];
+    unsigned long long wc[kResWaves][kCounters];
+    uint32_t state[8];
+    uint32_t lists[8];                  // class list lengths, and whether to leave the lists
+    Stage stage;
+    int go, fail;
+};
+
+__device__ __forceinline__ unsigned long long tagged(uint32_t value, uint32_t tag)
 {
-    __syncthreads();
-    if (gridDim.x == 1) return true;   // one workgroup: its barrier orders everything
-    if (threadIdx.x == 0) {
-        __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t spins = 0;
-        int ok = 1;
-        while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            __builtin_amdgcn_s_sleep(1);
-            if (++spins == kSpinLimit) {
-                ok = 0;
-                break;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        *s_ok = ok;
-    }
-    __syncthreads();
-    return *s_ok != 0;
+    return ((unsigned long long)value << 32) | tag;
 }
 
-template <bool F32>
-__global__ __launch_bounds__(kBlock) void k_loop(IterArgs a, LoopArgs L)
+// Poll a tagged word; false if its tag did not come within kSpinLimit polls.
+__device__ __forceinline__ bool await_word(const unsigned long long *p, uint32_t tag, uint32_t &value)
 {
-    __shared__ IterShared sh;
-    __shared__ FinalShared fsh;
-    __shared__ int s_go, s_ok;
-    Ctl *ctl = a.ctl;
-    uint32_t *bar = &ctl->bar[L.bar];
-    const uint32_t G = gridDim.x;
-    uint32_t passed = 0;
-    bool failed = false;
-    for (int k = 0; k < kLoopChunk; k++) {
-        const int i = L.it_start + k;
-        if (threadIdx.x == 0) {
-            // every workgroup reads the same state: it was written before
-            // the last barrier (or by an earlier launch)
-            uint32_t rows = 0;
-            for (int b = 0; b < kBins; b++) rows += ctl->snap[i & 1][b];
-            s_go = !(ctl->done || (F32 && ctl->phase_end) || ctl->dense || ctl->loop_fail) &&
-                   rows <= L.limit && i < a.max_iters;
-        }
-        __syncthreads();
-        if (!s_go) break;
-        const int src = L.base ^ ((i - L.it0) & 1);
-        IterArgs ai = a;
-        ai.it = i;
-        ai.Rc = L.R[src];
-        ai.Cc = L.C[src];
-        ai.Rn = L.R[src ^ 1];
-        ai.Cn = L.C[src ^ 1];
-        ai.C32c = L.C32[src];
-        ai.C32n = L.C32[src ^ 1];
-        iter_body<true, F32>(ai, blockIdx.x, G, sh);
-        if (!grid_barrier(bar, ++passed * G, &s_ok)) {
-            failed = true;
-            break;
-        }
-        if (blockIdx.x == 0) final_body(ai, true, F32, fsh, false);
-        if (!grid_barrier(bar, ++passed * G, &s_ok)) {
-            failed = true;
-            break;
+    for (uint32_t n = 0; n < kSpinLimit; n++) {
+        const unsigned long long x = ld<true>(p);
+        if ((uint32_t)x == tag) {
+            value = (uint32_t)(x >> 32);
+            return true;
         }
     }
-    if (failed && threadIdx.x == 0) {
-        __hip_atomic_store(&ctl->loop_fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&ctl->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return false;
+}
+
+// This wave's stores so far have reached the point where agent-scope loads
+// find them.
+__device__ __forceinline__ void drain_stores()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Whether every workgroup of the launch runs.  One compare-and-swap on the
+// launch's entry of loop_go decides it for all of them: workgroup 0 sets it
+// once all have arrived, a workgroup that has waited too long clears it.
+__device__ inline bool resident_start(const ResArgs &P, uint32_t *go, ResShared &rs)
+{
+    if (threadIdx.x == 0) {
+        rs.go = 1;
+        st<true>(&P.w->arrive[blockIdx.x * 4], tagged(0u, P.tag));
     }
+    __syncthreads();
     if (blockIdx.x == 0) {
-        // the state for the host (workgroup 0 wrote the last fold itself)
+        bool here = threadIdx.x >= gridDim.x;
+        for (uint32_t n = 0; n < kGoSpin && !here; n++)
+            here = (uint32_t)ld<true>(&P.w->arrive[threadIdx.x * 4]) == P.tag;
+        if (!here) rs.go = 0;
         __syncthreads();
-        constexpr int words = (int)(sizeof(Ctl) / 4);
-        const volatile uint32_t *src = reinterpret_cast<const volatile uint32_t *>(ctl);
-        uint32_t *dst = reinterpret_cast<uint32_t *>(a.mirror);
-        for (int w = threadIdx.x; w < words; w += kBlock) dst[w] = src[w];
+        if (threadIdx.x == 0) {
+            const uint32_t was = atomicCAS(go, 0u, rs.go ? 1u : 2u);
+            if (was) rs.go = was == 1u;
+        }
+    } else if (threadIdx.x == 0) {
+        uint32_t x = 0;
+        for (uint32_t n = 0; n < 2 * kGoSpin && !x; n++) x = ld<true>(go);
+        if (!x) {
+            x = atomicCAS(go, 0u, 2u);
+            if (!x) x = 2u;
+        }
+        rs.go = x == 1u;
     }
+    __syncthreads();
+    return rs.go != 0;
+}
+
+template <bool DF, bool F32>
+__global__ __launch_bounds__(kResThreads) void k_resident(IterArgs a, ResArgs P)
+{
+    __shared__ IterSharedT<kResWaves> sh;
+    __shared__ ResShared rs;
+    __shared__ double hub_lds[kResHub];
+    if (!resident_start(P, &a.ctl->loop_go[P.go], rs)) return;
+    const uint32_t G = gridDim.x, blk = blockIdx.x;
+    const int wave = threadIdx.x / kWave, lane = lane_id();
+    // the state at the launch's start: the kernels before it left it
+    bool dense = !DF || a.ctl->dense, stop = a.ctl->done || (F32 && a.ctl->phase_end);
+    if (threadIdx.x < 8)
+        rs.state[threadIdx.x] =
+            threadIdx.x ? a.ctl->snap[P.it_start & 1][threadIdx.x - 1] : 0u;
+    if (threadIdx.x == 0) {
+        rs.fail = 0;
+        // a negative frontier tolerance asks for the call's adaptive choice
+        sh.plan.ftol = a.ftol >= 0.0 ? a.ftol : a.ctl->ftol_used;
+        sh.plan.plain = a.ctl->plain_marks;
+        rs.stage.item = reinterpret_cast<uint2 *>(hub_lds);
+        rs.stage.cap = kResHub;
+    }
+    a.stage = &rs.stage;
+    if (blk == 0) {
+        constexpr int words = (int)(sizeof(Ctl) / 4);
+        for (int i = threadIdx.x; i < words; i += kResThreads)
+            reinterpret_cast<uint32_t *>(&rs.ctl)[i] = reinterpret_cast<const uint32_t *>(a.ctl)[i];
+    }
+    __syncthreads();
+    unsigned long long tot[kCounters] = {0, 0, 0, 0};
+    uint32_t tag = P.tag;
+    bool planned = false;       // the full schedule's plan does not change
+    for (int k = 0; k < kResSteps; k++) {
+        const int it = P.it_start + k;
+        uint32_t rows = 0;
+#pragma unroll
+        for (int b = 0; b < kBins; b++) rows += rs.state[1 + b];
+        if (stop || (dense ? !P.full : rows > P.limit)) break;     // uniform over the launch
+        const int src = P.base ^ ((it - P.it0) & 1);
+        a.it = it;
+        a.Rc = src ? P.R[1] : P.R[0];
+        a.Cc = src ? P.C[1] : P.C[0];
+        a.Rn = src ? P.R[0] : P.R[1];
+        a.Cn = src ? P.C[0] : P.C[1];
+        a.C32c = src ? P.C32[1] : P.C32[0];
+        a.C32n = src ? P.C32[0] : P.C32[1];
+        const bool sparse = DF && !dense;
+        if (wave == 0 && !(dense && planned))
+            make_plan_wave(a, a.ctl, sparse, DF, rs.state + 1, G, G * kResWaves, sh.plan);
+        planned = dense;
+        if (sparse && threadIdx.x <= kBins) (threadIdx.x ? rs.stage.cnt[threadIdx.x - 1] : rs.stage.n) = 0;
+        Hub hub{hub_lds, reinterpret_cast<const float *>(hub_lds), 0u};
+        if (!sparse && a.hub) {
+            hub.n = a.hub;
+            if (F32) {
+                float *f = reinterpret_cast<float *>(hub_lds);
+                for (uint32_t v = threadIdx.x; v < hub.n; v += kResThreads) f[v] = ld<true>(a.C32c + v);
+            } else {
+                for (uint32_t v = threadIdx.x; v < hub.n; v += kResThreads)
+                    hub_lds[v] = ld<true>(a.Cc + v);
+            }
+        }
+        __syncthreads();
+        Acc acc;
+        acc.ftol = sh.plan.ftol;
+        acc.plain = sh.plan.plain != 0;
+        iter_rows<DF, F32, kResWaves, true>(a, hub, blk, G, sh, DF && dense, sparse, acc);
+#pragma unroll
+        for (int j = 0; j < kCounters; j++) tot[j] += acc.c[j];
+        if (sparse) {
+            // the new list entries of the workgroup
+            __syncthreads();
+            const uint32_t n = min(rs.stage.n, rs.stage.cap);
+            if (n) {
+                if (threadIdx.x < kBins && rs.stage.cnt[threadIdx.x])
+                    rs.stage.base[threadIdx.x] =
+                        atomicAdd(&a.ctl->live[threadIdx.x], rs.stage.cnt[threadIdx.x]);
+                __syncthreads();
+                for (uint32_t i = threadIdx.x; i < n; i += kResThreads) {
+                    const uint2 e = rs.stage.item[i];
+                    const uint32_t c = e.y >> 28;
+                    st<true>(&a.bins[(size_t)c * a.n_stride + rs.stage.base[c] + (e.y & 0xFFFFFFFu)],
+                             (int32_t)e.x);
+                }
+            }
+        }
+        // arrive: Delta R and the largest rank of the workgroup
+        double dr = acc.dr_max, rm = acc.r_max;
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) {
+            dr = fmax(dr, __shfl_xor(dr, off, kWave));
+            rm = fmax(rm, __shfl_xor(rm, off, kWave));
+        }
+        if (lane == 0) {
+            rs.wdr[wave] = dr;
+            rs.wrm[wave] = rm;
+        }
+        drain_stores();
+        __syncthreads();
+        tag++;
+        if (threadIdx.x < kWave) {
+            dr = lane < kResWaves ? rs.wdr[lane] : 0.0;
+            rm = lane < kResWaves ? rs.wrm[lane] : 0.0;
+#pragma unroll
+            for (int off = kResWaves / 2; off > 0; off >>= 1) {
+                dr = fmax(dr, __shfl_xor(dr, off, kWave));
+                rm = fmax(rm, __shfl_xor(rm, off, kWave));
+            }
+            const unsigned long long bits =
+                (unsigned long long)__double_as_longlong(lane & 2 ? rm : dr);
+            if (lane < 4)
+                st<true>(&P.w->arrive[blk * 4 + lane],
+                         tagged((uint32_t)(lane & 1 ? bits >> 32 : bits), tag));
+        }
+        if (blk == 0) {
+            // fold: thread t polls word t; non-negative doubles order like
+            // their bit patterns
+            uint32_t v = 0;
+            if (threadIdx.x < G * 4 && !await_word(&P.w->arrive[threadIdx.x], tag, v)) rs.fail = 1;
+            unsigned long long x = ((unsigned long long)(uint32_t)__shfl_xor((int)v, 1) << 32) | v;
+#pragma unroll
+            for (int off = 4; off < kWave; off <<= 1) {
+                const unsigned long long y = __shfl_xor(x, off, kWave);
+                x = y > x ? y : x;
+            }
+            if (lane == 0 || lane == 2) rs.wmax[wave][lane / 2] = x;
+            __syncthreads();
+            if (wave == 0) {
+                // lanes 0-15 and 16-31: the waves' Delta R and largest ranks
+                if (sparse && lane <= kBins)
+                    rs.lists[lane] = lane < kBins ? ld<true>(&a.ctl->live[lane])
+                                                  : ld<true>(&a.ctl->force_dense);
+                x = lane < 2 * kResWaves ? rs.wmax[lane % kResWaves][lane / kResWaves] : 0ull;
+#pragma unroll
+                for (int off = kResWaves / 2; off > 0; off >>= 1) {
+                    const unsigned long long y = __shfl_xor(x, off, kWave);
+                    x = y > x ? y : x;
+                }
+                const unsigned long long r = __shfl(x, kResWaves);
+                if (lane == 0) {
+                    final_step(a, &rs.ctl, rs.lists, sparse, F32, __longlong_as_double((long long)x),
+                               __longlong_as_double((long long)r));
+                    const bool end = rs.fail || rs.ctl.done || (F32 && rs.ctl.phase_end);
+                    rs.state[0] = (end ? 1u : 0u) | (rs.ctl.dense ? 2u : 0u);
+                }
+                if (lane < kBins) rs.state[1 + lane] = rs.ctl.snap[(it & 1) ^ 1][lane];
+            }
+            __syncthreads();
+            if (threadIdx.x < kResCopies * 8)
+                st<true>(&P.w->state[threadIdx.x], tagged(rs.state[threadIdx.x & 7], tag));
+        } else {
+            if (threadIdx.x < 8) {
+                uint32_t v = 1u;
+                if (!await_word(&P.w->state[(blk & (kResCopies - 1)) * 8 + threadIdx.x], tag, v))
+                    rs.fail = 1;
+                rs.state[threadIdx.x] = v;
+            }
+            __syncthreads();
+        }
+        stop = rs.fail || (rs.state[0] & 1u);
+        dense = !DF || (rs.state[0] & 2u);
+    }
+    // counters of the launch, and the control block back to memory and host
+    double d0 = 0.0, d1 = 0.0;
+    block_fold<kResWaves>(d0, d1, tot, rs.wdr, rs.wrm, rs.wc);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int j = 0; j < kCounters; j++) st<true>(&P.w->count[blk * kCounters + j], tot[j]);
+        drain_stores();
+        st<true>(&P.w->arrive[blk * 4], tagged(0u, P.tag + kResSteps + 1));
+    }
+    if (blk) return;
+    uint32_t v = 0;
+    if (threadIdx.x < G && !await_word(&P.w->arrive[threadIdx.x * 4], P.tag + kResSteps + 1, v)) rs.fail = 1;
+#pragma unroll
+    for (int j = 0; j < kCounters; j++)
+        tot[j] = threadIdx.x < G ? ld<true>(&P.w->count[threadIdx.x * kCounters + j]) : 0ull;
+    block_fold<kResWaves>(d0, d1, tot, rs.wdr, rs.wrm, rs.wc);
+    if (threadIdx.x == 0) {
+        Ctl *c = a.ctl;
+        const Ctl &s = rs.ctl;
+        c->verts = s.verts + tot[0];
+        c->edges = s.edges + tot[1];
+        c->xverts = s.xverts + tot[2];
+        c->xedges = s.xedges + tot[3];
+        c->marked = s.marked;
+        c->iterations = s.iterations;
+        c->final_linf = s.final_linf;
+        c->final_rmax = s.final_rmax;
+        c->prev_linf = s.prev_linf;
+        c->phase_iters = s.phase_iters;
+        c->phase_end = s.phase_end;
+        c->converged = s.converged;
+        c->dense = s.dense;
+        c->done = rs.fail ? 1u : s.done;
+        c->loop_fail = (uint32_t)rs.fail;
+        c->loop_ran = P.tag;
+        for (int b = 0; b < kBins; b++) {
+            c->snap[0][b] = s.snap[0][b];
+            c->snap[1][b] = s.snap[1][b];
+        }
+        drain_stores();
+    }
+    __syncthreads();
+    if (threadIdx.x < kWave) ctl_to_mirror(a.ctl, a.mirror);
 }
 
 // ---------------------------------------------------------------------------
@@ -264,7 +503,7 @@ __global__ void k_reset(Ctl *ctl)
         ctl->mk_light = ctl->mk_heavy = 0;
         ctl->reach = 0;
         for (int k = 0; k < 3; k++) ctl->qn[k] = ctl->qhn[k] = 0;
-        ctl->bar[0] = ctl->bar[1] = 0;
+        for (int k = 0; k < kLoopLaunches; k++) ctl->loop_go[k] = 0;
         ctl->loop_fail = 0;
         ctl->reach0 = 0;
         ctl->ftol_used = 0.0;
@@ -921,33 +1160,92 @@ static uint32_t sparse_grid(const dfpr_graph *g, const Ctl &c)
     return (uint32_t)std::min<uint64_t>(g->grid, std::max<uint64_t>(lo, need * 4 + 64));
 }
 
-// One launch of the small-frontier loop from iteration it0 on buffer
-// `base`, on the graph's stream; the host reads its final state from
-// g->ctl_host after the stream has passed evc[0].
-static int launch_small_loop(dfpr_graph *g, IterArgs a, bool f32, int it0, int base, int slot)
+// Workgroups of a resident launch whose iterations walk the full schedule:
+// enough waves for its wave units and enough sub-blocks for its long rows,
+// one workgroup per compute unit at most.
+static uint32_t resident_grid(const dfpr_graph *g)
 {
-    LoopArgs L{};
-    for (int b = 0; b < 2; b++) {
-        L.R[b] = g->R[b];
-        L.C[b] = g->C[b];
-        L.C32[b] = g->C32[b];
+    const uint32_t *c = g->cls;
+    uint64_t nwu = ((uint64_t)(c[kBins + 1] - c[kBins]) + kWave - 1) / kWave;
+    for (int b = 0; b < kBins - 1; b++) {
+        const uint64_t rows = kWave / group_of(b);
+        nwu += ((uint64_t)(c[kBins - b] - c[kBins - 1 - b]) + rows - 1) / rows;
     }
-    L.base = base;
-    L.it0 = it0;
-    L.it_start = it0;
-    L.limit = kLoopRows;
-    L.bar = slot;
+    const uint64_t need = std::max<uint64_t>((nwu + kResWaves - 1) / kResWaves, (c[1] - c[0] + 3) / 4);
+    return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(need, g->cus));
+}
+
+// Contributions a workgroup of a resident launch copies into LDS: the number
+// that saves most.  A gather from L2 takes a compute unit about 1.1 ns beyond
+// the 2 us that an iteration's chain of accesses takes anyway, a copied entry
+// 0.21 ns (half that in FP32) and the copy itself 0.6 us; the share of the
+// gathers that the first entries take is known from the load.  On R-MAT scale
+// 18 that is all kResHub entries (4.1 us for 60% of 18 us of gathers), on a
+// uniform graph or one of 10,000 vertices none.
+static uint32_t resident_hub(const dfpr_graph *g, bool f32, uint32_t G)
+{
+    const double gathers = 1.1e-3 * (double)g->m / G - 2.0;     // us per workgroup
+    double best = 0.0;
+    uint32_t hub = 0;
+    for (int k = 0; k < kHubSteps; k++) {
+        const uint32_t h = std::min<uint32_t>(1024u << k, (uint32_t)g->n);
+        if (h > (f32 ? 2 * kResHub : kResHub)) break;
+        const double gain = g->hub_share[k] * gathers - (f32 ? 1.05e-4 : 2.1e-4) * h - 0.6;
+        if (gain > best) {
+            best = gain;
+            hub = h;
+        }
+    }
+    return hub;
+}
+
+// One launch of the resident loop from iteration `it` of the phase that
+// started at it0 on buffer `base`.  *ran: the workgroups were all running
+// and the control block's host copy is the state it left; otherwise nothing
+// was changed.
+static int launch_resident(dfpr_graph *g, IterArgs a, bool df, bool f32, int it0, int it, int base,
+                           bool full, uint32_t limit, bool *ran)
+{
+    *ran = false;
+    if (!g->it.res || g->res_used >= kLoopLaunches) return DFPR_OK;
+    if (g->res_tag > 0xFFFFFFFFu - 2 * kResTags) {
+        // the tags start over: the words of earlier launches must not match
+        DFPR_CHECK_RC(launch_fill_u32(g, reinterpret_cast<uint32_t *>(g->it.res),
+                                      sizeof(ResWords) / 4, 0));
+        g->res_tag = 0;
+    }
+    ResArgs P{};
+    for (int b = 0; b < 2; b++) {
+        P.R[b] = g->R[b];
+        P.C[b] = g->C[b];
+        P.C32[b] = g->C32[b];
+    }
+    P.w = reinterpret_cast<ResWords *>(g->it.res);
+    P.base = base;
+    P.it0 = it0;
+    P.it_start = it;
+    P.full = full ? 1 : 0;
+    P.limit = limit;
+    P.go = g->res_used++;
+    P.tag = g->res_tag + 1;
+    g->res_tag += kResTags;
     a.mirror = g->ctl_host;
-    void *args[] = {&a, &L};
-    const void *fn = f32 ? reinterpret_cast<const void *>(&k_loop<true>)
-                         : reinterpret_cast<const void *>(&k_loop<false>);
-    DFPR_HIP(hipLaunchCooperativeKernel(fn, dim3(kLoopGrid), dim3(kBlock), args, 0, g->stream));
+    const uint32_t G = full ? resident_grid(g) : (uint32_t)g->cus;
+    a.hub = full && a.hub ? resident_hub(g, f32, G) : 0u;
+    a.sparse_limit = std::max<uint32_t>(a.sparse_limit, g->n / kResSparse);
+    if (!df) k_resident<false, false><<<G, kResThreads, 0, g->stream>>>(a, P);
+    else if (f32) k_resident<true, true><<<G, kResThreads, 0, g->stream>>>(a, P);
+    else k_resident<true, false><<<G, kResThreads, 0, g->stream>>>(a, P);
+    DFPR_HIP(hipGetLastError());
     DFPR_HIP(hipEventRecord(g->evc[0], g->stream));
+    DFPR_HIP(hipEventSynchronize(g->evc[0]));
+    if (g->ctl_host->loop_fail) return set_error(DFPR_E_DEVICE, "resident loop: a barrier timed out");
+    *ran = g->ctl_host->loop_ran == P.tag;
     return DFPR_OK;
 }
 
 static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint32_t sbase,
-                    int it0, int base, int *res_buf, int small_slot = -1)
+                    int it0, int base, int *res_buf)
 {
     IterArgs a = iter_args(g, p, sbase);
     const bool async = p.mode == DFPR_ASYNC && !f32;
@@ -972,25 +1270,28 @@ static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint
     double prev_dr = -1.0;
     int prev_it = it0;
     *res_buf = base;
-    // Dynamic Frontier on the class lists, if asked for: the first
-    // iterations, while the frontier is small, run inside one launch of the
-    // small-frontier loop
-    if (df && !async && small_slot >= 0 && g->coop && p.loop == DFPR_LOOP_DEVICE &&
-        p.max_iters > it0) {
-        DFPR_CHECK_RC(launch_small_loop(g, a, f32, it0, base, small_slot));
-        DFPR_HIP(hipEventSynchronize(g->evc[0]));
-        const Ctl &st = *g->ctl_host;
-        if (st.loop_fail) return set_error(DFPR_E_DEVICE, "small-frontier loop: grid barrier timed out");
-        next_it = std::max(it0, (int)st.iterations);
-        g->loop_iters += next_it - it0;
-        // its work is not part of the iteration kernel's profile
-        g->prof_base[0] = (int64_t)st.verts;
-        g->prof_base[1] = (int64_t)st.edges;
-        g->prof_base[2] = (int64_t)st.xverts;
-        g->prof_base[3] = (int64_t)st.xedges;
-        g->prof_base[4] = (int64_t)st.marked;
-        if (st.done || (f32 && st.phase_end)) stop = true;
-        else if (!st.dense) gsz = sparse_grid(g, st);
+    // Iterations inside one launch (see kResEdges).  The asynchronous form
+    // and profiled calls keep a launch per iteration.
+    const bool device_loop = p.loop == DFPR_LOOP_DEVICE;
+    const bool full = !device_loop && g->m <= kResEdges;
+    if (!async && !g->prof.enabled && (full || df)) {
+        const uint32_t limit = device_loop ? kLoopRows : 0xFFFFFFFFu;
+        while (next_it < p.max_iters) {
+            bool ran = false;
+            DFPR_CHECK_RC(launch_resident(g, a, df, f32, it0, next_it, base, full, limit, &ran));
+            if (!ran) break;
+            const Ctl &c = *g->ctl_host;
+            const int steps = c.iterations - next_it;
+            next_it = c.iterations;
+            if (device_loop) g->loop_iters += steps;
+            if (c.done || (f32 && c.phase_end)) {
+                stop = true;
+                break;
+            }
+            gsz = df && !c.dense ? sparse_grid(g, c) : (uint32_t)g->grid;
+            wide = DFPR_WIDE && (!df || c.dense);
+            if (steps < kResSteps) break;     // handed over
+        }
     }
     auto launch = [&](int k) -> int {
         const int slot = nchunks & 1;
@@ -1185,6 +1486,7 @@ static int full_sweeps(dfpr_graph *g, const dfpr_params *pp, const double *prev,
     int res = cur;
     g->refine_sweeps = 0;
     g->loop_iters = 0;
+    g->res_used = 0;
     std::memset(g->prof_base, 0, sizeof(g->prof_base));
     DFPR_HIP(hipEventRecord(g->ev_mid, s));
     rc = run_loop(g, p, false, false, 0, 0, cur, &res);
@@ -1240,6 +1542,7 @@ int df_begin(dfpr_graph *g, const dfpr_params &p, int64_t nd, const int32_t *bds
     DFPR_HIP(hipGetLastError());
     g->refine_sweeps = 0;
     g->loop_iters = 0;
+    g->res_used = 0;
     std::memset(g->prof_base, 0, sizeof(g->prof_base));
     *sbase_out = sbase;
     return DFPR_OK;
@@ -1318,7 +1621,7 @@ static int df_impl(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32
     int res = cur;
     if (p.precision == DFPR_FP32_KAHAN) {
         // FP32 phase on FP32 copies of the contributions
-        rc = run_loop(g, p, true, true, sbase, 0, cur, &res, 0);
+        rc = run_loop(g, p, true, true, sbase, 0, cur, &res);
         if (rc) return rc;
         if (g->ctl_host->err)
             return set_error(DFPR_E_RANGE, "vertex id outside [0, n) in the batch");
@@ -1327,12 +1630,12 @@ static int df_impl(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32
         if (rc) return rc;
         if (!done) {
             const int it0 = g->ctl_host->iterations;
-            rc = run_loop(g, p, true, false, sbase, it0, res, &res, 1);
+            rc = run_loop(g, p, true, false, sbase, it0, res, &res);
             if (rc) return rc;
             g->refine_sweeps = g->ctl_host->iterations - it0;
         }
     } else {
-        rc = run_loop(g, p, true, false, sbase, 0, cur, &res, 0);
+        rc = run_loop(g, p, true, false, sbase, 0, cur, &res);
         if (rc) return rc;
     }
     const int32_t iters = g->ctl_host->iterations;
@@ -1470,6 +1773,7 @@ static int dt_impl(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32
     DFPR_HIP(hipGetLastError());
     g->refine_sweeps = 0;
     g->loop_iters = 0;
+    g->res_used = 0;
     std::memset(g->prof_base, 0, sizeof(g->prof_base));
     DFPR_HIP(hipEventRecord(g->ev_mid, s));
     int res = cur;

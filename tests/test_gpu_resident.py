@@ -1,0 +1,115 @@
+"""The resident loop (many iterations in one launch) against a launch per
+iteration, bitwise, and against the oracle.  Profiled calls always take a
+launch per iteration, so switching the profile on selects the comparison."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2401_03256_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dfpr():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2401_03256_amd import dfpr as mod
+    mod.lib()
+    return mod
+
+
+def _star(leaves):
+    v = np.arange(1, leaves + 1, dtype=np.int32)
+    z = np.zeros(leaves, np.int32)
+    return leaves + 1, np.concatenate([v, z]), np.concatenate([z, v])
+
+
+GRAPHS = {
+    "one": lambda: (1, np.zeros(0, np.int32), np.zeros(0, np.int32)),
+    "gnm63": lambda: (63, *synth.gnm(63, 300, seed=1)),
+    "gnm10000": lambda: (10_000, *synth.gnm(10_000, 80_000, seed=2)),
+    # one workgroup-wide row among rows of one in-edge
+    "star5000": lambda: _star(5000),
+    # long rows in every class; n no multiple of a wave
+    "rmat12": lambda: synth.rmat(12, 16, seed=3),
+    "rmat17": lambda: synth.rmat(17, 16, seed=4),
+    "grid301": lambda: synth.grid2d(301, seed=5),
+}
+
+
+def _same(tag, a, b):
+    (Ra, sa), (Rb, sb) = a, b
+    assert np.array_equal(Ra, Rb), f"{tag}: ranks differ by {np.abs(Ra - Rb).max()}"
+    for f in ("iterations", "converged", "refine_sweeps", "final_linf", "affected_initial",
+              "affected_final", "vertices_processed", "edges_processed"):
+        assert getattr(sa, f) == getattr(sb, f), f"{tag}: {f}"
+
+
+@pytest.mark.parametrize("name", list(GRAPHS))
+def test_resident_loop_bitwise_equal_to_launches(dfpr, name):
+    sys.stdout.write(f"\n[case] resident loop {name}\n")
+    sys.stdout.flush()
+    n, src, dst = GRAPHS[name]()
+    g, h = dfpr.Graph(n, src, dst), dfpr.Graph(n, src, dst)
+    h.profile_reset(True)                       # a launch per iteration
+    o = oracle.OracleGraph(n, src, dst)
+    a, b = g.static(), h.static()
+    _same("static", a, b)
+    R, _ = o.static()
+    assert np.abs(a[0] - R).max() <= 1e-9
+    for cap in (0, 1, 2, 7):
+        p = dfpr.params(max_iters=cap)
+        _same(f"cap {cap}", g.naive_dynamic(R, p), h.naive_dynamic(R, p))
+    if n < 60:
+        return
+    for k, (nd, ni) in enumerate([(1, 4), (0, 1), (3, 0), (17, 40)]):
+        nd = min(nd, src.size // 8)
+        bt = synth.random_batch(src, dst, n, nd, ni, seed=30 + k)
+        assert g.apply_batch(bt) == h.apply_batch(bt)
+        for prec in (dfpr.FP64, dfpr.FP32_KAHAN):
+            for ftol in (1e-13, -1.0):
+                p = dfpr.params(frontier_tol=ftol, precision=prec)
+                _same(f"df {k} {prec} {ftol}", g.dynamic_frontier(bt, R, p),
+                      h.dynamic_frontier(bt, R, p))
+                assert np.array_equal(g.affected(), h.affected())
+        _same(f"traversal {k}", g.dynamic_traversal(bt, R), h.dynamic_traversal(bt, R))
+        for cap in (1, 3):
+            p = dfpr.params(max_iters=cap)
+            _same(f"df {k} cap {cap}", g.dynamic_frontier(bt, R, p), h.dynamic_frontier(bt, R, p))
+        inv = synth.Batch(bt.ins_src, bt.ins_dst, bt.del_src, bt.del_dst)
+        assert g.apply_batch(inv) == h.apply_batch(inv)
+    assert h.profile().launches > 0 and g.profile().launches == 0
+
+
+def test_resident_loop_calls_from_two_threads(dfpr):
+    """Two graphs updated at once: each call's workgroups may find the other's
+    running; results stay those of calls one at a time."""
+    import threading
+    n, src, dst = synth.rmat(14, 16, seed=7)
+    batches = [synth.random_batch(src, dst, n, 4, 16, seed=40 + k) for k in range(2)]
+    want = []
+    for b in batches:
+        g = dfpr.Graph(n, src, dst)
+        R0, _ = g.static()
+        g.apply_batch(b)
+        want.append((R0, g.dynamic_frontier(b, R0)[0]))
+    graphs = [dfpr.Graph(n, src, dst) for _ in batches]
+    bad = []
+
+    def work(k):
+        try:
+            g, b = graphs[k], batches[k]
+            g.apply_batch(b)
+            for _ in range(20):
+                if not np.array_equal(g.dynamic_frontier(b, want[k][0])[0], want[k][1]):
+                    bad.append(k)
+        except Exception as e:      # reported below, in the main thread
+            bad.append(e)
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    [t.start() for t in ts]
+    [t.join() for t in ts]
+    assert not bad
