@@ -3,12 +3,12 @@
 //
 // Steps, all on the device:
 //   1. keys: each batch entry becomes, per orientation, the 64-bit key
-//      row << 33 | col << 1 | type (type 0 = deletion, 1 = insertion);
-//      self-loop deletions become a sentinel that sorts last; an id outside
-//      [0, n) sets the error flag and every later step does nothing.
-//   2. sort: each workgroup sorts a tile of 2048 keys in LDS (bitonic), then
-//      merge passes double the sorted runs (each key finds its output slot by
-//      a binary search in the other run).
+//      row << 33 | col << 1 | type (type 0 = deletion, 1 = insertion) in
+//      internal ids; self-loop deletions become a sentinel that sorts last; an
+//      id outside [0, n) sets the error flag and every later step does nothing.
+//   2. sort: workgroups sort tiles of keys in LDS (by rank), then merge passes
+//      double the sorted runs (each key finds its output slot by a binary
+//      search in the other run).
 //   3. heads: the first key of each row opens a "touched row" entry; rows
 //      whose capacity fits in LDS go to one list, larger rows to another.
 //   4. merge: one workgroup per touched row.  It copies the row (LDS or a
@@ -23,11 +23,17 @@
 //      left for a re-layout: new capacities, a prefix sum, a copy of every
 //      row to its new place with fresh free space, and the merge is run
 //      again from the round that did not fit.
+// A batch of at most kSmallBatch entries takes two launches: steps 1-3 by one
+// workgroup per orientation (k_apply_sorted), step 4 with the counts and the
+// host's copy of the control block by one grid (k_apply_merged).  The ten
+// launches of the general path cost it 60-80 us, 4-10 us of dispatch each, for
+// a few us of work.
 #include <algorithm>
 #include <cstring>
 #include <vector>
 
 #include "common.h"
+#include "iter.h"
 
 namespace dfpr {
 
@@ -98,7 +104,8 @@ __device__ inline uint32_t gallop_dev(const T *a, uint32_t lo, uint32_t len, T x
 struct ApplyArgs {
     int32_t n;
     int64_t nd, ni;
-    const int32_t *ds, *dd, *is, *id;
+    const int32_t *ds, *dd, *is, *id;   // the caller's ids
+    const int32_t *ext2int;
     uint64_t *keys[2];          // unsorted / sorted keys per orientation
     uint32_t *tiny_list[2], *small_list[2], *big_list[2], *ovf_list[2];
     int32_t *ovf_need[2];
@@ -118,8 +125,8 @@ __device__ inline void put_applied(const ApplyArgs &a, uint32_t slot, unsigned l
                                    unsigned long long i)
 {
     if (a.part) {
-        a.part[2 * slot] = d;
-        a.part[2 * slot + 1] = i;
+        st<true>(&a.part[2 * slot], d);
+        st<true>(&a.part[2 * slot + 1], i);
     } else if (d | i) {
         atomicAdd(&a.ctl->applied[0], d);
         atomicAdd(&a.ctl->applied[1], i);
@@ -127,12 +134,12 @@ __device__ inline void put_applied(const ApplyArgs &a, uint32_t slot, unsigned l
 }
 
 // Sum the applied counts that the launched workgroups of the three row
-// kernels left in part into Ctl.
+// kernels left in part into Ctl, and copy Ctl to the host's mirror.
 constexpr int kFoldThreads = 1024;
 
 __global__ __launch_bounds__(kFoldThreads) void k_apply_fold(const unsigned long long *part,
                                                        uint32_t tiny_grid, uint32_t small_grid,
-                                                       Ctl *ctl)
+                                                       Ctl *ctl, Ctl *mirror)
 {
     __shared__ unsigned long long s[2][kFoldThreads];
     const uint32_t base[3] = {0, kTinyGrid, kTinyGrid + kSmallGrid};
@@ -156,7 +163,10 @@ __global__ __launch_bounds__(kFoldThreads) void k_apply_fold(const unsigned long
     if (threadIdx.x == 0) {
         ctl->applied[0] += s[0][0];
         ctl->applied[1] += s[1][0];
+        drain_stores();
     }
+    __syncthreads();
+    if (threadIdx.x < kWave) ctl_to_mirror(ctl, mirror);
 }
 
 __global__ void k_apply_reset(Ctl *ctl)
@@ -170,25 +180,30 @@ __global__ void k_apply_reset(Ctl *ctl)
     }
 }
 
+// Key of batch entry i in each orientation; false for an id outside [0, n).
+__device__ inline bool entry_keys(const ApplyArgs &a, int64_t i, uint64_t &kin, uint64_t &kout)
+{
+    kin = kout = kSentinel;
+    const bool del = i < a.nd;
+    const int32_t cs = del ? a.ds[i] : a.is[i - a.nd];
+    const int32_t cd = del ? a.dd[i] : a.id[i - a.nd];
+    if (cs < 0 || cs >= a.n || cd < 0 || cd >= a.n) return false;
+    if (del && cs == cd) return true;   // self-loops are never deleted
+    const int32_t s = a.ext2int[cs], d = a.ext2int[cd];
+    const uint64_t t = del ? 0 : 1;
+    kin = ((uint64_t)d << 33) | ((uint64_t)(uint32_t)s << 1) | t;   // in-CSR: row = dst
+    kout = ((uint64_t)s << 33) | ((uint64_t)(uint32_t)d << 1) | t;  // out-CSR: row = src
+    return true;
+}
+
 __global__ void k_apply_keys(ApplyArgs a)
 {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= a.nd + a.ni) return;
-    const bool del = i < a.nd;
-    const int32_t s = del ? a.ds[i] : a.is[i - a.nd];
-    const int32_t d = del ? a.dd[i] : a.id[i - a.nd];
-    if (s < 0 || s >= a.n || d < 0 || d >= a.n) {
-        atomicOr(&a.ctl->err, 1u);
-        a.keys[0][i] = a.keys[1][i] = kSentinel;
-        return;
-    }
-    if (del && s == d) {   // self-loops are never deleted
-        a.keys[0][i] = a.keys[1][i] = kSentinel;
-        return;
-    }
-    const uint64_t t = del ? 0 : 1;
-    a.keys[0][i] = ((uint64_t)d << 33) | ((uint64_t)(uint32_t)s << 1) | t;   // in-CSR: row = dst
-    a.keys[1][i] = ((uint64_t)s << 33) | ((uint64_t)(uint32_t)d << 1) | t;   // out-CSR: row = src
+    uint64_t kin, kout;
+    if (!entry_keys(a, i, kin, kout)) atomicOr(&a.ctl->err, 1u);
+    a.keys[0][i] = kin;
+    a.keys[1][i] = kout;
 }
 
 // Sort tiles of up to kTile keys, in -> out; grid.y = orientation.  Rank
@@ -248,6 +263,79 @@ __global__ void k_merge_pass(const uint64_t *in0, uint64_t *out0, const uint64_t
     out[start + pos] = key;
 }
 
+// List of a touched row: by the capacity it had before the batch and its
+// number of batch entries: 0 = at most kWave of each (one wave), 1 = copied to
+// LDS (one workgroup), 2 = larger (workgroup with a global slab).  A row can
+// grow by its number of entries over the rounds of the merge: only rows that
+// stay within kRowLds go to LDS.
+__device__ inline int row_list(uint32_t cap, uint32_t nops)
+{
+    if ((uint64_t)cap + nops > (uint64_t)kRowLds) return 2;
+    return cap <= (uint32_t)kWave && nops <= (uint32_t)kWave ? 0 : 1;
+}
+
+// Steps 1-3 for a batch of at most kSmallBatch entries: one workgroup per
+// orientation maps, checks and sorts the keys (bitonic, a key per thread;
+// partners within a wave by shuffles, the others through LDS) and lists the
+// touched rows.
+__global__ __launch_bounds__(kSmallBatch) void k_apply_sorted(ApplyArgs a)
+{
+    __shared__ uint64_t s[kSmallBatch];
+    __shared__ uint32_t s_n[3], s_err;
+    const int o = blockIdx.y;
+    const uint32_t i = threadIdx.x, len = (uint32_t)(a.nd + a.ni);
+    if (i < 3) s_n[i] = 0;
+    if (i == 0) s_err = 0;
+    __syncthreads();
+    uint64_t k = kSentinel;
+    if (i < len) {
+        uint64_t kin, kout;
+        if (!entry_keys(a, i, kin, kout)) s_err = 1;
+        k = o == 0 ? kin : kout;
+    }
+    uint32_t full = kWave;
+    while (full < len) full *= 2;
+    for (uint32_t run = 2; run <= full; run *= 2)
+        for (uint32_t j = run / 2; j > 0; j /= 2) {
+            uint64_t y;
+            if (j >= (uint32_t)kWave) {
+                __syncthreads();
+                s[i] = k;
+                __syncthreads();
+                y = s[i ^ j];
+            } else {
+                y = __shfl_xor(k, (int)j, kWave);
+            }
+            const bool lower = !(i & j), up = !(i & run);
+            if ((lower == up) == (y < k)) k = y;
+        }
+    __syncthreads();
+    s[i] = k;
+    __syncthreads();
+    Ctl *ctl = a.ctl;
+    if (i < len) a.keys[o][i] = k;
+    if (i < len && k != kSentinel && !s_err) {
+        const uint32_t r = key_row(k);
+        if (i == 0 || key_row(s[i - 1]) != r) {
+            const uint32_t cap = a.cap[o][r];
+            const int w = row_list(cap, gallop_dev(s, i, len, (uint64_t)(r + 1) << 33) - i);
+            uint32_t *list = w == 0 ? a.tiny_list[o] : w == 1 ? a.small_list[o] : a.big_list[o];
+            list[atomicAdd(&s_n[w], 1u)] = i;
+        }
+    }
+    __syncthreads();
+    if (i == 0) {
+        ctl->ntiny[o] = s_n[0];
+        ctl->nsmall[o] = s_n[1];
+        ctl->nbig[o] = s_n[2];
+        ctl->novf[o] = 0;
+        if (o == 0) {
+            ctl->err = s_err;
+            ctl->applied[0] = ctl->applied[1] = 0;
+        }
+    }
+}
+
 // Open one touched-row entry at the first key of every row.
 __global__ void k_heads(ApplyArgs a, uint32_t len)
 {
@@ -255,9 +343,6 @@ __global__ void k_heads(ApplyArgs a, uint32_t len)
     const int o = blockIdx.y;
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t *keys = a.keys[o];
-    // rows by the capacity they had before the batch and their number of
-    // batch entries: 0 = at most kWave of each (one wave), 1 = copied to
-    // LDS (one workgroup), 2 = larger (workgroup with a global slab)
     bool head = false;
     int which_row = 1;
     if (i < len) {
@@ -265,14 +350,9 @@ __global__ void k_heads(ApplyArgs a, uint32_t len)
         if (k != kSentinel) {
             const uint32_t r = key_row(k);
             head = i == 0 || key_row(keys[i - 1]) != r;
-            if (head) {
-                // a row can grow by its number of entries over the rounds
-                // of the merge: only rows that stay within kRowLds go to LDS
-                const uint64_t cap = a.cap[o][r];
-                const uint32_t nops = gallop_dev(keys, i, len, (uint64_t)(r + 1) << 33) - i;
-                if (cap + nops > (uint64_t)kRowLds) which_row = 2;
-                else if (cap <= (uint64_t)kWave && nops <= (uint32_t)kWave) which_row = 0;
-            }
+            if (head)
+                which_row = row_list(a.cap[o][r],
+                                     gallop_dev(keys, i, len, (uint64_t)(r + 1) << 33) - i);
         }
     }
     const int lane = __lane_id();
@@ -319,20 +399,20 @@ __device__ inline unsigned long long lanes_mask(uint32_t k)
 // batch; survivors shift left past effective deletions and right past
 // effective insertions; a row that outgrows its slots moves to free space at
 // the top, or is left for a re-layout).
-__global__ __launch_bounds__(kBlock) void k_apply_tiny(ApplyArgs a, uint32_t len)
+// Workgroup blk of `blocks`; thread 0 gets the applied counts (out-rows).
+__device__ __forceinline__ void apply_tiny(const ApplyArgs &a, uint32_t len, int o, uint32_t blk,
+                                           uint32_t blocks, unsigned long long &sum_del,
+                                           unsigned long long &sum_ins)
 {
-    const int o = blockIdx.y;
     Ctl *ctl = a.ctl;
-    if (ctl->err) return;
     const uint32_t count = ctl->ntiny[o];
     const uint64_t *keys = a.keys[o];
     uint32_t *beg_a = a.beg[o], *cnt_a = a.cnt[o], *cap_a = a.cap[o];
     int32_t *idx = a.idx[o];
     const int lane = __lane_id();
     const unsigned long long below = (1ull << lane) - 1ull;
-    const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-    const uint32_t waves = gridDim.x * kWavesPerBlock;
-    unsigned long long sum_del = 0, sum_ins = 0;
+    const uint32_t wave = blk * kWavesPerBlock + threadIdx.x / kWave;
+    const uint32_t waves = blocks * kWavesPerBlock;
     for (uint32_t t = wave; t < count; t += waves) {
         const uint32_t start = a.tiny_list[o][t];
         // operations (sorted by column, deletion before insertion)
@@ -413,9 +493,16 @@ __global__ __launch_bounds__(kBlock) void k_apply_tiny(ApplyArgs a, uint32_t len
                 sum_del += s_sum[0][k];
                 sum_ins += s_sum[1][k];
             }
-            put_applied(a, blockIdx.x, sum_del, sum_ins);
         }
     }
+}
+
+__global__ __launch_bounds__(kBlock) void k_apply_tiny(ApplyArgs a, uint32_t len)
+{
+    if (a.ctl->err) return;
+    unsigned long long sum_del = 0, sum_ins = 0;
+    apply_tiny(a, len, blockIdx.y, blockIdx.x, gridDim.x, sum_del, sum_ins);
+    if (blockIdx.y == 1 && threadIdx.x == 0) put_applied(a, blockIdx.x, sum_del, sum_ins);
 }
 
 // Exclusive prefix sum of in[0 .. len) (len <= 4 * kBlock) into out[0 .. len],
@@ -486,36 +573,39 @@ __device__ inline uint32_t sampled_lower_bound(const int32_t *row, uint32_t c, c
 // LDS samples; a row that moves to fresh slots is read in place, and a row
 // that stays copies only the part from its first operation on to a global
 // slab, since the entries before it keep their slots.
-template <bool BIG>
-__global__ __launch_bounds__(kBlock) void k_apply_rows(ApplyArgs a, uint32_t len, int only_o)
-{
-    __shared__ int32_t s_d[kOpsLds];
-    __shared__ int32_t s_i[kOpsLds];
-    __shared__ uint8_t s_fd[kOpsLds];
-    __shared__ uint8_t s_fi[kOpsLds];
-    __shared__ uint32_t s_pd[kOpsLds + 1];
-    __shared__ uint32_t s_pi[kOpsLds + 1];
-    __shared__ uint32_t s_ipos[kOpsLds];  // row position of each insertion
-    __shared__ uint32_t s_tmp[kBlock];
-    __shared__ int32_t s_row[kRowLds];    // the row, or (BIG) its samples
-    __shared__ uint32_t s_dest, s_ncap, s_first;
-    __shared__ int s_ok;
+struct RowsShared {
+    int32_t d[kOpsLds];
+    int32_t i[kOpsLds];
+    uint8_t fd[kOpsLds];
+    uint8_t fi[kOpsLds];
+    uint32_t pd[kOpsLds + 1];
+    uint32_t pi[kOpsLds + 1];
+    uint32_t ipos[kOpsLds];     // row position of each insertion
+    uint32_t tmp[kBlock];
+    int32_t row[kRowLds];       // the row, or (BIG) its samples
+    uint32_t dest, ncap, first;
+    int ok;
+};
 
-    const int o = only_o >= 0 ? only_o : blockIdx.y;
-    if (only_o >= 0 && blockIdx.y > 0) return;
+// Workgroup blk of `blocks`; `slab`: its row copy (BIG).  Thread 0 gets the
+// applied counts (out-rows).
+template <bool BIG>
+__device__ __forceinline__ void apply_rows(const ApplyArgs &a, uint32_t len, int o, uint32_t blk,
+                                           uint32_t blocks, int32_t *slab, RowsShared &sh,
+                                           unsigned long long &sum_del, unsigned long long &sum_ins)
+{
+    int32_t *const s_d = sh.d, *const s_i = sh.i, *const s_row = sh.row;
+    uint8_t *const s_fd = sh.fd, *const s_fi = sh.fi;
+    uint32_t *const s_pd = sh.pd, *const s_pi = sh.pi, *const s_ipos = sh.ipos, *const s_tmp = sh.tmp;
+    uint32_t &s_dest = sh.dest, &s_ncap = sh.ncap, &s_first = sh.first;
+    int &s_ok = sh.ok;
     Ctl *ctl = a.ctl;
-    if (ctl->err) return;
     const uint32_t count = BIG ? ctl->nbig[o] : ctl->nsmall[o];
     const uint32_t *list = BIG ? a.big_list[o] : a.small_list[o];
     const uint64_t *keys = a.keys[o];
     uint32_t *beg_a = a.beg[o], *cnt_a = a.cnt[o], *cap_a = a.cap[o];
     int32_t *idx = a.idx[o];
-    // one slab per (workgroup, orientation): both orientations run at once
-    int32_t *slab = BIG ? a.slab + ((uint64_t)blockIdx.y * kBigGrid + blockIdx.x) * a.slab_stride
-                        : nullptr;
-
-    unsigned long long sum_del = 0, sum_ins = 0;  // thread 0, out-rows
-    for (uint32_t t = blockIdx.x; t < count; t += gridDim.x) {
+    for (uint32_t t = blk; t < count; t += blocks) {
         // list entries point at the first batch key of the row, or, for a
         // re-run after a re-layout, at the first key of the round that did
         // not fit (earlier rounds were applied)
@@ -700,8 +790,53 @@ __global__ __launch_bounds__(kBlock) void k_apply_rows(ApplyArgs a, uint32_t len
             __syncthreads();
         }
     }
+}
+
+template <bool BIG>
+__global__ __launch_bounds__(kBlock) void k_apply_rows(ApplyArgs a, uint32_t len, int only_o)
+{
+    __shared__ RowsShared sh;
+    const int o = only_o >= 0 ? only_o : blockIdx.y;
+    if (only_o >= 0 && blockIdx.y > 0) return;
+    if (a.ctl->err) return;
+    // one slab per (workgroup, orientation): both orientations run at once
+    int32_t *slab = BIG ? a.slab + ((uint64_t)blockIdx.y * kBigGrid + blockIdx.x) * a.slab_stride
+                        : nullptr;
+    unsigned long long sum_del = 0, sum_ins = 0;
+    apply_rows<BIG>(a, len, o, blockIdx.x, gridDim.x, slab, sh, sum_del, sum_ins);
     if (o == 1 && threadIdx.x == 0)
         put_applied(a, (BIG ? kTinyGrid + kSmallGrid : kTinyGrid) + blockIdx.x, sum_del, sum_ins);
+}
+
+// Step 4 for a batch of at most kSmallBatch entries: every kind of touched
+// row in one grid, orientation blockIdx.x & 1; the last workgroup adds up the
+// applied counts and copies the control block to the host's mirror.
+__global__ __launch_bounds__(kBlock) void k_apply_merged(ApplyArgs a, uint32_t len, Ctl *mirror)
+{
+    __shared__ RowsShared sh;
+    __shared__ int s_last;
+    __shared__ unsigned long long s_applied[2];
+    const int o = blockIdx.x & 1;
+    const uint32_t blk = blockIdx.x / 2, blocks = gridDim.x / 2;
+    unsigned long long sum_del = 0, sum_ins = 0;
+    if (!a.ctl->err) {
+        apply_tiny(a, len, o, blk, blocks, sum_del, sum_ins);
+        apply_rows<false>(a, len, o, blk, blocks, nullptr, sh, sum_del, sum_ins);
+        apply_rows<true>(a, len, o, blk, blocks, a.slab + ((uint64_t)o * kBigGrid + blk) * a.slab_stride,
+                         sh, sum_del, sum_ins);
+    }
+    if (o == 1 && threadIdx.x == 0) put_applied(a, blk, sum_del, sum_ins);
+    if (threadIdx.x < 2) s_applied[threadIdx.x] = 0;
+    if (!last_block(a.ctl->tick, &s_last)) return;
+    for (uint32_t k = threadIdx.x; k < 2 * blocks; k += kBlock) {
+        const unsigned long long x = ld<true>(&a.part[k]);
+        if (x) atomicAdd(&s_applied[k & 1], x);
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) st<true>(&a.ctl->applied[threadIdx.x], s_applied[threadIdx.x]);
+    drain_stores();
+    __syncthreads();
+    if (threadIdx.x < kWave) ctl_to_mirror(a.ctl, mirror);
 }
 
 // ---- re-layout of one orientation after slack overflow --------------------
@@ -865,14 +1000,8 @@ static inline unsigned grid_for(uint64_t items, unsigned per = kBlock)
     return (unsigned)std::max<uint64_t>(1, (items + per - 1) / per);
 }
 
-// Copy a batch (host or device arrays) into the graph's staging buffer in
-// internal ids; ids outside [0, n) become -1 and are rejected later.  The
-// buffer keeps 2 (n_del + n_ins) more entries after the batch for the
-// initial marking.
-int stage_batch(dfpr_graph *g, int64_t n_del, const int32_t *ds, const int32_t *dd,
-                int64_t n_ins, const int32_t *is, const int32_t *id, int on_device,
-                const int32_t **dds, const int32_t **ddd, const int32_t **dis,
-                const int32_t **did)
+int stage_raw(dfpr_graph *g, int64_t n_del, const int32_t *ds, const int32_t *dd, int64_t n_ins,
+              const int32_t *is, const int32_t *id, int on_device, const int32_t *src[4])
 {
     ApplyBufs &ap = g->ap;
     hipStream_t s = g->stream;
@@ -890,36 +1019,53 @@ int stage_batch(dfpr_graph *g, int64_t n_del, const int32_t *ds, const int32_t *
         DFPR_HIP(hipMalloc(&ap.batch_dev, cap * 4));
         ap.batch_cap = cap;
     }
-    int32_t *p = ap.batch_dev;
-    int32_t *dst[4] = {p, p + n_del, p + 2 * n_del, p + 2 * n_del + n_ins};
-    const int32_t *src[4] = {ds, dd, is, id};
+    const int32_t *in[4] = {ds, dd, is, id};
+    const int64_t len[4] = {n_del, n_del, n_ins, n_ins};
+    for (int k = 0; k < 4; k++) src[k] = in[k];
+    if (on_device || tot <= 0) return DFPR_OK;
+    if ((uint64_t)tot > ap.batch_host_cap || !ap.batch_host) {
+        if (ap.batch_host) (void)hipHostFree(ap.batch_host);
+        ap.batch_host = nullptr;
+        ap.batch_host_cap = 0;
+        const uint64_t cap = std::max<uint64_t>(tot, 8192);
+        DFPR_HIP(hipHostMalloc((void **)&ap.batch_host, cap * 4, hipHostMallocDefault));
+        ap.batch_host_cap = cap;
+    }
+    int64_t at = 0;
+    for (int k = 0; k < 4; k++) {
+        src[k] = ap.batch_host + at;
+        if (len[k]) std::memcpy(ap.batch_host + at, in[k], (size_t)len[k] * 4);
+        at += len[k];
+    }
+    return DFPR_OK;
+}
+
+// Copy a batch (host or device arrays) into the graph's staging buffer in
+// internal ids; ids outside [0, n) become -1 and are rejected later.  The
+// buffer keeps 2 (n_del + n_ins) more entries after the batch for the
+// initial marking.
+int stage_batch(dfpr_graph *g, int64_t n_del, const int32_t *ds, const int32_t *dd,
+                int64_t n_ins, const int32_t *is, const int32_t *id, int on_device,
+                const int32_t **dds, const int32_t **ddd, const int32_t **dis,
+                const int32_t **did)
+{
+    const int32_t *src[4];
+    DFPR_CHECK_RC(stage_raw(g, n_del, ds, dd, n_ins, is, id, on_device, src));
+    const int64_t tot = 2 * (n_del + n_ins);
+    int32_t *p = g->ap.batch_dev;
     const int64_t len[4] = {n_del, n_del, n_ins, n_ins};
     if (!on_device && tot > 0) {
-        // one copy through a pinned buffer, then the ids mapped in place
-        if ((uint64_t)tot > ap.batch_host_cap || !ap.batch_host) {
-            if (ap.batch_host) (void)hipHostFree(ap.batch_host);
-            ap.batch_host = nullptr;
-            ap.batch_host_cap = 0;
-            const uint64_t cap = std::max<uint64_t>(tot, 8192);
-            DFPR_HIP(hipHostMalloc((void **)&ap.batch_host, cap * 4, hipHostMallocDefault));
-            ap.batch_host_cap = cap;
-        }
-        int64_t at = 0;
-        for (int k = 0; k < 4; k++) {
-            if (len[k]) std::memcpy(ap.batch_host + at, src[k], (size_t)len[k] * 4);
-            at += len[k];
-        }
-        DFPR_HIP(hipMemcpyAsync(p, ap.batch_host, (size_t)tot * 4, hipMemcpyHostToDevice, s));
-        const int rc = map_ids(g, p, p, tot);
-        if (rc) return rc;
+        // one copy of the pinned arrays, then the ids mapped in place
+        DFPR_HIP(hipMemcpyAsync(p, g->ap.batch_host, (size_t)tot * 4, hipMemcpyHostToDevice,
+                                g->stream));
+        DFPR_CHECK_RC(map_ids(g, p, p, tot));
     } else if (tot > 0) {
-        const int rc = map_ids4(g, src, len, p);
-        if (rc) return rc;
+        DFPR_CHECK_RC(map_ids4(g, src, len, p));
     }
-    *dds = dst[0];
-    *ddd = dst[1];
-    *dis = dst[2];
-    *did = dst[3];
+    *dds = p;
+    *ddd = p + n_del;
+    *dis = p + 2 * n_del;
+    *did = p + 2 * n_del + n_ins;
     return DFPR_OK;
 }
 
@@ -960,6 +1106,7 @@ static ApplyArgs apply_args(dfpr_graph *g)
     a.C1 = g->C[1];
     a.slab = g->ap.slab;
     a.slab_stride = g->ap.slab_stride;
+    a.ext2int = g->ext2int;
     a.ctl = g->ctl;
     return a;
 }
@@ -1012,38 +1159,19 @@ static int relayout(dfpr_graph *g, int o, uint32_t novf, const uint64_t *sorted_
     return DFPR_OK;
 }
 
-int apply_batch_impl(dfpr_graph *g, int64_t n_del, const int32_t *ds, const int32_t *dd,
-                     int64_t n_ins, const int32_t *is, const int32_t *id, int on_device,
-                     int64_t applied[2])
+// The kernels of a batch of B entries up to the host's copy of the control
+// block.  a.keys: the unsorted keys on entry, the sorted ones on return.
+static void apply_small(dfpr_graph *g, ApplyArgs &a, uint32_t B)
 {
-    if (n_del < 0 || n_ins < 0 || (n_del && (!ds || !dd)) || (n_ins && (!is || !id)))
-        return set_error(DFPR_E_ARG, "bad batch arrays");
-    if (n_del + n_ins >= (1ll << 31)) return set_error(DFPR_E_ARG, "batch too large");
-    if (!on_device) {
-        int rc = check_ids_host(g->n, n_del, ds, dd);
-        if (!rc) rc = check_ids_host(g->n, n_ins, is, id);
-        if (rc) return rc;
-    }
-    if (applied) applied[0] = applied[1] = 0;
-    g->last_apply_ms = 0.f;
-    const uint32_t B = (uint32_t)(n_del + n_ins);
-    if (B == 0) return DFPR_OK;
-    int rc = ensure_apply_bufs(g, B);
-    if (!rc) rc = ensure_slab(g);
-    if (rc) return rc;
+    a.part = g->ap.part;
+    k_apply_sorted<<<dim3(1, 2), kSmallBatch, 0, g->stream>>>(a);
+    const unsigned blocks = std::min<unsigned>(grid_for(B, kWavesPerBlock), kBigGrid);
+    k_apply_merged<<<2 * blocks, kBlock, 0, g->stream>>>(a, B, g->ctl_host);
+}
+
+static void apply_large(dfpr_graph *g, ApplyArgs &a, uint32_t B)
+{
     hipStream_t s = g->stream;
-    DFPR_HIP(hipEventRecord(g->ev_a0, s));
-    rc = stage_batch(g, n_del, ds, dd, n_ins, is, id, on_device, &ds, &dd, &is, &id);
-    if (rc) return rc;
-    ApplyArgs a = apply_args(g);
-    a.nd = n_del;
-    a.ni = n_ins;
-    a.ds = ds;
-    a.dd = dd;
-    a.is = is;
-    a.id = id;
-    a.keys[0] = g->ap.keys[0][0];
-    a.keys[1] = g->ap.keys[1][0];
     k_apply_reset<<<1, 1, 0, s>>>(g->ctl);
     k_apply_keys<<<grid_for(B), kBlock, 0, s>>>(a);
     const unsigned tiles = (B + kTile - 1) / kTile;
@@ -1067,10 +1195,46 @@ int apply_batch_impl(dfpr_graph *g, int64_t n_del, const int32_t *ds, const int3
     k_apply_tiny<<<dim3(tiny_grid, 2), kBlock, 0, s>>>(a, B);
     k_apply_rows<false><<<dim3(small_grid, 2), kBlock, 0, s>>>(a, B, -1);
     k_apply_rows<true><<<dim3(kBigGrid, 2), kBlock, 0, s>>>(a, B, -1);
-    k_apply_fold<<<1, kFoldThreads, 0, s>>>(a.part, tiny_grid, small_grid, a.ctl);
+    k_apply_fold<<<1, kFoldThreads, 0, s>>>(a.part, tiny_grid, small_grid, a.ctl, g->ctl_host);
+}
+
+int apply_batch_impl(dfpr_graph *g, int64_t n_del, const int32_t *ds, const int32_t *dd,
+                     int64_t n_ins, const int32_t *is, const int32_t *id, int on_device,
+                     int64_t applied[2])
+{
+    if (n_del < 0 || n_ins < 0 || (n_del && (!ds || !dd)) || (n_ins && (!is || !id)))
+        return set_error(DFPR_E_ARG, "bad batch arrays");
+    if (n_del + n_ins >= (1ll << 31)) return set_error(DFPR_E_ARG, "batch too large");
+    if (!on_device) {
+        int rc = check_ids_host(g->n, n_del, ds, dd);
+        if (!rc) rc = check_ids_host(g->n, n_ins, is, id);
+        if (rc) return rc;
+    }
+    if (applied) applied[0] = applied[1] = 0;
+    g->last_apply_ms = 0.f;
+    const uint32_t B = (uint32_t)(n_del + n_ins);
+    if (B == 0) return DFPR_OK;
+    int rc = ensure_apply_bufs(g, B);
+    if (!rc) rc = ensure_slab(g);
+    if (rc) return rc;
+    hipStream_t s = g->stream;
+    DFPR_HIP(hipEventRecord(g->ev_a0, s));
+    const int32_t *src[4];
+    rc = stage_raw(g, n_del, ds, dd, n_ins, is, id, on_device, src);
+    if (rc) return rc;
+    ApplyArgs a = apply_args(g);
+    a.nd = n_del;
+    a.ni = n_ins;
+    a.ds = src[0];
+    a.dd = src[1];
+    a.is = src[2];
+    a.id = src[3];
+    a.keys[0] = g->ap.keys[0][0];
+    a.keys[1] = g->ap.keys[1][0];
+    if (B <= (uint32_t)kSmallBatch) apply_small(g, a, B);
+    else apply_large(g, a, B);
     DFPR_HIP(hipGetLastError());
     DFPR_HIP(hipEventRecord(g->ev_a1, s));
-    DFPR_CHECK_RC(ctl_to_host(g));
     DFPR_HIP(hipStreamSynchronize(s));
     if (g->ctl_host->err) return set_error(DFPR_E_RANGE, "vertex id outside [0, n) in the batch");
     for (int o = 0; o < 2; o++)

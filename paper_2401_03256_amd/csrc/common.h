@@ -23,6 +23,10 @@ constexpr int kCounters = 4;
 // reads 256 slots instead of one partial per workgroup.
 constexpr int kFoldSlots = 256;           // rows, in-edges, expanded rows, their out-edges
 constexpr int kLoopChunk = 64;         // most iteration launches between two host looks
+// Batches of at most this many entries are staged, checked and sorted by one
+// workgroup in one launch; larger ones take several kernels of many.
+constexpr int kSmallBatch = 1024;
+constexpr int kTickets = 16;           // counters that order the end of a grid (last_block)
 constexpr int kLoopLaunches = 8;       // most launches of the resident loop in one call
 constexpr int kHubSteps = 6;           // sizes of its LDS copy of contributions
 constexpr int kResBytes = 32768;       // words its workgroups exchange (ResWords)
@@ -90,7 +94,9 @@ struct Ctl {
     uint32_t loop_go[kLoopLaunches];   // resident loop: per launch of the call, 1 once every
                                 // workgroup was running, 2 if one gave up waiting first
     uint32_t loop_ran;          //   tag of the last launch that ran
+    uint32_t loop_closed;       //   that launch ended the call (see Close in iter.h)
     uint32_t loop_fail;         //   a barrier timed out
+    uint32_t tick[kTickets + 1];    // arrivals of a grid's workgroups (zero between launches)
 };
 
 // One orientation of the graph: row r holds cnt[r] sorted ids in
@@ -239,6 +245,11 @@ int stage_batch_into(dfpr_graph *g, int64_t n_del, const int32_t *ds, const int3
                      int64_t n_ins, const int32_t *is, const int32_t *id, int32_t *buf,
                      const int32_t **dds, const int32_t **ddd, const int32_t **dis,
                      const int32_t **did);
+// The batch where a kernel can read it as the caller gave it: the caller's
+// device arrays, or a pinned copy of host arrays.  Also makes room for the
+// batch in internal ids and the marking's source lists (batch_dev).
+int stage_raw(dfpr_graph *g, int64_t n_del, const int32_t *ds, const int32_t *dd, int64_t n_ins,
+              const int32_t *is, const int32_t *id, int on_device, const int32_t *src[4]);
 int check_ids_host(int32_t n, int64_t len, const int32_t *a, const int32_t *b);
 
 // renumbering at the boundary (graph.hip); enqueued on g->stream

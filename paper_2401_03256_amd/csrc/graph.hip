@@ -414,6 +414,7 @@ int dfpr_load_graph(int32_t n, int64_t m, const int32_t *src, const int32_t *dst
         hipError_t e =
             hipHostMalloc((void **)&g->ctl_host, 2 * sizeof(Ctl), hipHostMallocCoherent);
         if (e != hipSuccess) rc = hip_fail(e, "hipHostMalloc");
+        else std::memset(g->ctl_host, 0, 2 * sizeof(Ctl));
     }
     if (!rc) {
         hipError_t e = hipStreamCreateWithFlags(&g->own_stream, hipStreamNonBlocking);

@@ -50,6 +50,36 @@ __device__ __forceinline__ void st(T *p, T v)
     else *p = v;
 }
 
+// This wave's stores and atomics so far have reached the point where
+// agent-scope loads find them.
+__device__ __forceinline__ void drain_stores()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Whether this is the last workgroup of the grid to get here; the others'
+// atomics and agent-scope stores before the call are then visible to its
+// agent-scope loads.  Every thread calls it.  A workgroup arrives at one of
+// kTickets counters and the last of each at one more, since arrivals at one
+// address take 13 ns each; the last of all clears them.
+__device__ __forceinline__ bool last_block(uint32_t *tick, int *s_last)
+{
+    drain_stores();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t n = gridDim.x, b = blockIdx.x, t = b % kTickets;
+        const uint32_t mine = (n - t + kTickets - 1) / kTickets, used = min(n, (uint32_t)kTickets);
+        int last = 0;
+        if (atomicAdd(&tick[t], 1u) == mine - 1 && atomicAdd(&tick[kTickets], 1u) == used - 1) {
+            last = 1;
+            for (int k = 0; k <= kTickets; k++) st<true>(&tick[k], 0u);
+        }
+        *s_last = last;
+    }
+    __syncthreads();
+    return *s_last != 0;
+}
+
 // Index loads.  In a launch per iteration they are streamed: marked
 // non-temporal so that they do not displace gathered contributions from L2.
 // The resident loop reads the same indices every iteration and keeps them.
@@ -1002,18 +1032,26 @@ __device__ __forceinline__ void final_body(const IterArgs &a, bool df, bool f32,
 
 namespace dfpr {
 
+// How a call ends, if its last iteration runs in the resident loop: that
+// launch brings the other buffer up to date, counts the marks and writes the
+// ranks in the caller's order.
+struct Close {
+    double *out = nullptr;      // device; NULL: not wanted
+    bool done = false;          // the launch did it
+};
+
 // Host helpers of rank.hip shared with the serving loop (serve.hip).
 IterArgs iter_args(dfpr_graph *g, const dfpr_params &p, uint32_t sbase);
 int check_params(const dfpr_params *p, dfpr_params &out);
-int df_begin(dfpr_graph *g, const dfpr_params &p, int64_t nd, const int32_t *bds,
-             const int32_t *bdd, int64_t ni, const int32_t *bis, const int32_t *bid,
-             const double *prev, int prev_dev, uint32_t *sbase_out, int32_t *lists = nullptr);
+int df_begin(dfpr_graph *g, const dfpr_params &p, int64_t nd, const int32_t *ds,
+             const int32_t *dd, int64_t ni, const int32_t *is, const int32_t *id, int on_device,
+             const double *prev, uint32_t *sbase_out, int32_t *staging = nullptr);
 // A Dynamic Frontier call on device arrays whose batch is staged in
 // `staging` (4 (nd + ni) ints) instead of the library's buffer.
 int df_device_staged(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32_t *ds,
                      const int32_t *dd, int64_t ni, const int32_t *is, const int32_t *id,
                      const double *prev, double *ranks_out, dfpr_stats *st, int32_t *staging);
 int df_phase_end(dfpr_graph *g, int res, bool call_done);
-int df_finish(dfpr_graph *g, uint32_t sbase, int res, int32_t iters);
+int df_finish(dfpr_graph *g, uint32_t sbase, int res, int32_t iters, bool closed = false);
 
 }  // namespace dfpr

@@ -174,11 +174,13 @@ constexpr uint32_t kGoSpin = 256;                // polls before a launch gives 
 constexpr uint32_t kSpinLimit = 1u << 24;        // polls of a barrier before it reports failure
 constexpr int kResCopies = 8;                    // copies of the published state
 
+constexpr int kResCounts = kCounters + 1;        // and the marks
+
 // What the workgroups of a resident loop exchange (dfpr_graph::it.res).
 struct ResWords {
     unsigned long long arrive[kResMax * 4];          // per workgroup: Delta R, largest rank
     unsigned long long state[kResCopies * 8];        // flags, class list lengths
-    unsigned long long count[kResMax * kCounters];   // counters of the launch, at its end
+    unsigned long long count[kResMax * kResCounts];  // counters of the launch, at its end
 };
 
 static_assert(sizeof(ResWords) <= kResBytes, "kResBytes holds the exchanged words");
@@ -194,6 +196,9 @@ struct ResArgs {
     int go;             // its entry of Ctl::loop_go
     uint32_t limit;     // class list rows of an iteration above which it hands over
     uint32_t tag;       // first of its tags
+    int close;          // end the call too, if it converges or reaches the cap
+    double *out;        //   the ranks in the caller's order (nullable)
+    const int32_t *ext2int;
 };
 
 struct ResShared {
@@ -223,13 +228,6 @@ __device__ __forceinline__ bool await_word(const unsigned long long *p, uint32_t
         }
     }
     return false;
-}
-
-// This wave's stores so far have reached the point where agent-scope loads
-// find them.
-__device__ __forceinline__ void drain_stores()
-{
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // Whether every workgroup of the launch runs.  One compare-and-swap on the
@@ -297,7 +295,9 @@ __global__ __launch_bounds__(kResThreads) void k_resident(IterArgs a, ResArgs P)
     unsigned long long tot[kCounters] = {0, 0, 0, 0};
     uint32_t tag = P.tag;
     bool planned = false;       // the full schedule's plan does not change
-    for (int k = 0; k < kResSteps; k++) {
+    bool over = false;          // the call has converged or reached the cap
+    int k = 0;
+    for (; k < kResSteps; k++) {
         const int it = P.it_start + k;
         uint32_t rows = 0;
 #pragma unroll
@@ -408,7 +408,8 @@ __global__ __launch_bounds__(kResThreads) void k_resident(IterArgs a, ResArgs P)
                     final_step(a, &rs.ctl, rs.lists, sparse, F32, __longlong_as_double((long long)x),
                                __longlong_as_double((long long)r));
                     const bool end = rs.fail || rs.ctl.done || (F32 && rs.ctl.phase_end);
-                    rs.state[0] = (end ? 1u : 0u) | (rs.ctl.dense ? 2u : 0u);
+                    rs.state[0] = (end ? 1u : 0u) | (rs.ctl.dense ? 2u : 0u) |
+                                  (end && !rs.fail && rs.ctl.done ? 4u : 0u);
                 }
                 if (lane < kBins) rs.state[1 + lane] = rs.ctl.snap[(it & 1) ^ 1][lane];
             }
@@ -426,13 +427,52 @@ __global__ __launch_bounds__(kResThreads) void k_resident(IterArgs a, ResArgs P)
         }
         stop = rs.fail || (rs.state[0] & 1u);
         dense = !DF || (rs.state[0] & 2u);
+        over = rs.state[0] & 4u;
+    }
+    unsigned long long marks = 0;
+    const bool close = !F32 && P.close && over && !rs.fail;
+    if (close) {
+        // the other buffer on the processed rows (k_finish, k_copy2), and
+        // the ranks in the caller's order
+        const int it = P.it_start + k, res = P.base ^ ((it - P.it0) & 1);
+        const double *Rr = res ? P.R[1] : P.R[0], *Cr = res ? P.C[1] : P.C[0];
+        double *Ro = res ? P.R[0] : P.R[1], *Co = res ? P.C[0] : P.C[1];
+        const uint32_t t0 = blk * kResThreads + threadIdx.x, step = G * kResThreads;
+        if (DF && !dense) {
+            uint32_t tot = 0;
+#pragma unroll
+            for (int b = 0; b < kBins; b++) tot += rs.state[1 + b];
+            for (uint32_t t = t0; t < tot; t += step) {
+                uint32_t b = 0, r = t;
+                while (r >= rs.state[1 + b]) r -= rs.state[1 + b++];
+                const int32_t v = ld<true>(&a.bins[(size_t)b * a.n_stride + r]);
+                marks++;
+                Ro[v] = ld<true>(Rr + v);
+                Co[v] = ld<true>(Cr + v);
+            }
+        } else {
+            for (uint32_t v = t0; v < (uint32_t)a.n; v += step) {
+                if (DF) {
+                    const uint32_t sx = ld<true>(a.stamp + v);
+                    if (sx < a.sbase || sx > a.sbase + (uint32_t)it) continue;
+                    marks++;
+                }
+                Ro[v] = ld<true>(Rr + v);
+                Co[v] = ld<true>(Cr + v);
+            }
+        }
+        if (P.out)
+            for (uint32_t v = t0; v < (uint32_t)a.n; v += step) P.out[v] = ld<true>(Rr + P.ext2int[v]);
     }
     // counters of the launch, and the control block back to memory and host
     double d0 = 0.0, d1 = 0.0;
     block_fold<kResWaves>(d0, d1, tot, rs.wdr, rs.wrm, rs.wc);
+    unsigned long long mk[kCounters] = {marks, 0, 0, 0};
+    if (DF) block_fold<kResWaves>(d0, d1, mk, rs.wdr, rs.wrm, rs.wc);
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int j = 0; j < kCounters; j++) st<true>(&P.w->count[blk * kCounters + j], tot[j]);
+        for (int j = 0; j < kCounters; j++) st<true>(&P.w->count[blk * kResCounts + j], tot[j]);
+        st<true>(&P.w->count[blk * kResCounts + kCounters], mk[0]);
         drain_stores();
         st<true>(&P.w->arrive[blk * 4], tagged(0u, P.tag + kResSteps + 1));
     }
@@ -441,8 +481,13 @@ __global__ __launch_bounds__(kResThreads) void k_resident(IterArgs a, ResArgs P)
     if (threadIdx.x < G && !await_word(&P.w->arrive[threadIdx.x * 4], P.tag + kResSteps + 1, v)) rs.fail = 1;
 #pragma unroll
     for (int j = 0; j < kCounters; j++)
-        tot[j] = threadIdx.x < G ? ld<true>(&P.w->count[threadIdx.x * kCounters + j]) : 0ull;
+        tot[j] = threadIdx.x < G ? ld<true>(&P.w->count[threadIdx.x * kResCounts + j]) : 0ull;
     block_fold<kResWaves>(d0, d1, tot, rs.wdr, rs.wrm, rs.wc);
+    if (DF) {
+        mk[0] = threadIdx.x < G ? ld<true>(&P.w->count[threadIdx.x * kResCounts + kCounters]) : 0ull;
+        mk[1] = mk[2] = mk[3] = 0;
+        block_fold<kResWaves>(d0, d1, mk, rs.wdr, rs.wrm, rs.wc);
+    }
     if (threadIdx.x == 0) {
         Ctl *c = a.ctl;
         const Ctl &s = rs.ctl;
@@ -451,6 +496,8 @@ __global__ __launch_bounds__(kResThreads) void k_resident(IterArgs a, ResArgs P)
         c->xverts = s.xverts + tot[2];
         c->xedges = s.xedges + tot[3];
         c->marked = s.marked;
+        c->affected = s.affected + mk[0];
+        c->loop_closed = close && !rs.fail;
         c->iterations = s.iterations;
         c->final_linf = s.final_linf;
         c->final_rmax = s.final_rmax;
@@ -476,10 +523,10 @@ __global__ __launch_bounds__(kResThreads) void k_resident(IterArgs a, ResArgs P)
 // set-up kernels
 // ---------------------------------------------------------------------------
 
-// Clear the per-call loop state (not the batch-applier fields).
-__global__ void k_reset(Ctl *ctl)
+// Clear the per-call loop state (not the batch-applier fields).  One thread.
+__device__ inline void reset_ctl(Ctl *ctl)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
+    {
         for (int b = 0; b < kBins; b++) {
             ctl->live[b] = 0;
             ctl->snap[0][b] = ctl->snap[1][b] = 0;
@@ -505,13 +552,17 @@ __global__ void k_reset(Ctl *ctl)
         for (int k = 0; k < 3; k++) ctl->qn[k] = ctl->qhn[k] = 0;
         for (int k = 0; k < kLoopLaunches; k++) ctl->loop_go[k] = 0;
         ctl->loop_fail = 0;
+        ctl->loop_closed = 0;
         ctl->reach0 = 0;
         ctl->ftol_used = 0.0;
     }
 }
 
-// Freeze the lists built by the marking as iteration 0's snapshot and pick
-// the walk of the first iteration.
+__global__ void k_reset(Ctl *ctl)
+{
+    if (threadIdx.x == 0 && blockIdx.x == 0) reset_ctl(ctl);
+}
+
 // Adaptive frontier tolerance (the paper leaves the choice of tau_f by the
 // nature of the batch to future work, Section 5.2.4 and the Conclusion).
 // The initial marking measures how fast the frontier can grow: the mean
@@ -529,29 +580,41 @@ __host__ __device__ inline int adaptive_ftol_exponent(unsigned long long marked,
          : out_edges <= 32 * marked ? 3 : out_edges <= 64 * marked ? 4 : 5;
 }
 
+// Freeze the lists built by the marking as iteration 0's snapshot and pick
+// the walk of the first iteration.  One thread, after the marking (in the
+// same launch with COH).
+template <bool COH>
+__device__ inline void snap_ctl(Ctl *ctl, int32_t max_iters, uint32_t sparse_limit, int dense,
+                                double tol, double ftol)
+{
+    const unsigned long long marked = ld<COH>(&ctl->affected0), reach0 = ld<COH>(&ctl->reach0);
+    if (ftol >= 0.0) {
+        ctl->ftol_used = ftol;
+    } else {
+        const double p10[6] = {1.0, 1e1, 1e2, 1e3, 1e4, 1e5};
+        ctl->ftol_used = tol / p10[adaptive_ftol_exponent(marked, reach0)];
+    }
+    unsigned long long tot = 0;
+    for (int b = 0; b < kBins; b++) {
+        const uint32_t l = ld<COH>(&ctl->live[b]);
+        ctl->snap[0][b] = l;
+        tot += l;
+    }
+    ctl->dense = (dense || ld<COH>(&ctl->dense) || tot > sparse_limit) ? 1 : 0;
+    // a first frontier with more out-edges than the class lists take
+    // would append most of them in its first expansions, one list
+    // atomic per wave and round on counters that share a cache line;
+    // its expansions mark with plain stores instead, and the call walks
+    // the full schedule from the next iteration on
+    ctl->plain_marks = reach0 > sparse_limit ? 1 : 0;
+    ctl->done = (ld<COH>(&ctl->err) || max_iters <= 0) ? 1 : 0;
+}
+
 __global__ void k_snap(Ctl *ctl, int32_t max_iters, uint32_t sparse_limit, int dense, Ctl *mirror,
                        double tol, double ftol)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
-        if (ftol >= 0.0) {
-            ctl->ftol_used = ftol;
-        } else {
-            const double p10[6] = {1.0, 1e1, 1e2, 1e3, 1e4, 1e5};
-            ctl->ftol_used = tol / p10[adaptive_ftol_exponent(ctl->affected0, ctl->reach0)];
-        }
-        unsigned long long tot = 0;
-        for (int b = 0; b < kBins; b++) {
-            ctl->snap[0][b] = ctl->live[b];
-            tot += ctl->live[b];
-        }
-        ctl->dense = (dense || ctl->dense || tot > sparse_limit) ? 1 : 0;
-        // a first frontier with more out-edges than the class lists take
-        // would append most of them in its first expansions, one list
-        // atomic per wave and round on counters that share a cache line;
-        // its expansions mark with plain stores instead, and the call walks
-        // the full schedule from the next iteration on
-        ctl->plain_marks = ctl->reach0 > sparse_limit ? 1 : 0;
-        ctl->done = (ctl->err || max_iters <= 0) ? 1 : 0;
+        snap_ctl<false>(ctl, max_iters, sparse_limit, dense, tol, ftol);
         if (mirror) __builtin_memcpy(mirror, ctl, sizeof(Ctl));
     }
 }
@@ -732,46 +795,138 @@ __device__ inline void mark_one(const IterArgs &a, int32_t x, bool append,
 // class lists are filled (sparse mode) unless `dense` is set or the claimed
 // sources reach more vertices than the sparse limit; the decision goes to
 // the control block for the iterations.  Every loop bound is uniform
-// within a wave.
+// within a wave.  With `snap` the last workgroup of the grid takes the
+// snapshot of iteration 0.
 __global__ __launch_bounds__(kBlock) void k_mark_initial(IterArgs a, int64_t nd, const int32_t *dd,
                                                          const int32_t *light,
-                                                         const int32_t *heavy, int dense)
+                                                         const int32_t *heavy, int dense, int snap)
 {
     __shared__ unsigned long long s_new, s_deg;
+    __shared__ HeavyShared hs;
+    __shared__ int s_last;
     Ctl *ctl = a.ctl;
-    if (ctl->err) return;
     const bool dn = dense || ctl->reach + (unsigned long long)nd > a.sparse_limit;
     const bool append = !dn;
-    if (blockIdx.x == 0 && threadIdx.x == 0 && dn) ctl->dense = 1;
-    if (threadIdx.x == 0) s_new = s_deg = 0;
-    __syncthreads();
-    const int lane = lane_id();
-    const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
-    const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
-    unsigned long long mine = 0, mdeg = 0;
-    for (int64_t b0 = wave * kWave; b0 < nd; b0 += waves * kWave) {
-        const int64_t i = b0 + lane;
-        mark_one(a, i < nd ? dd[i] : -1, append, mine, mdeg);
-    }
-    const uint32_t nl = ctl->mk_light, nh = ctl->mk_heavy;
-    for (int64_t w = wave; w < nl; w += waves) {
-        const int32_t u = light[w];
-        const uint32_t ob = a.out_beg[u], oc = a.out_cnt[u];
-        for (uint32_t kb = 0; kb < oc; kb += kWave) {
-            const uint32_t k = kb + lane;
-            mark_one(a, k < oc ? a.out_idx[ob + k] : -1, append, mine, mdeg);
+    if (!ctl->err) {
+        if (blockIdx.x == 0 && threadIdx.x == 0 && dn) st<true>(&ctl->dense, 1u);
+        if (threadIdx.x == 0) s_new = s_deg = 0;
+        __syncthreads();
+        const int lane = lane_id();
+        const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
+        const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
+        unsigned long long mine = 0, mdeg = 0;
+        for (int64_t b0 = wave * kWave; b0 < nd; b0 += waves * kWave) {
+            const int64_t i = b0 + lane;
+            mark_one(a, i < nd ? dd[i] : -1, append, mine, mdeg);
+        }
+        const uint32_t nl = ctl->mk_light, nh = ctl->mk_heavy;
+        for (int64_t w = wave; w < nl; w += waves) {
+            const int32_t u = light[w];
+            const uint32_t ob = a.out_beg[u], oc = a.out_cnt[u];
+            for (uint32_t kb = 0; kb < oc; kb += kWave) {
+                const uint32_t k = kb + lane;
+                mark_one(a, k < oc ? a.out_idx[ob + k] : -1, append, mine, mdeg);
+            }
+        }
+        walk_heavy(a, heavy, nh, hs, [&](int32_t x) { mark_one(a, x, append, mine, mdeg); });
+        if (lane == 0 && mine) {
+            atomicAdd(&s_new, mine);
+            atomicAdd(&s_deg, mdeg);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0 && s_new) {
+            atomicAdd(&ctl->affected0, s_new);
+            atomicAdd(&ctl->reach0, s_deg);
         }
     }
-    __shared__ HeavyShared hs;
-    walk_heavy(a, heavy, nh, hs, [&](int32_t x) { mark_one(a, x, append, mine, mdeg); });
-    if (lane == 0 && mine) {
-        atomicAdd(&s_new, mine);
-        atomicAdd(&s_deg, mdeg);
+    if (snap && last_block(ctl->tick, &s_last) && threadIdx.x == 0)
+        snap_ctl<true>(ctl, a.max_iters, a.sparse_limit, dense, a.tol, a.ftol);
+}
+
+// The start of a call in one launch: workgroup 0 clears the loop state and,
+// for a batch of at most kSmallBatch entries, stages, checks and claims it
+// (what k_map_ids4, k_validate and k_mark_claim do for larger ones); the other
+// workgroups load the starting ranks.  Each of these kernels alone does
+// nothing for most of its 2-5 us, and the dispatch between them costs as much
+// again.
+struct BeginArgs {
+    int64_t nd, ni;             // the batch, 0 entries: none, or staged elsewhere
+    const int32_t *src[4];      // its four arrays in the caller's ids
+    const int32_t *ext2int, *int2ext;
+    int32_t *staged;            // the four arrays in internal ids
+    int32_t *light, *heavy;     // claimed sources
+    int snap;                   // 1: no marking follows; take the snapshot here
+    int dense;                  //   with the full schedule
+    int ranks;                  // 1: from prev, 2: uniform, 0: as they are
+    const double *prev;         // caller's order
+    double *R0, *R1, *C0, *C1;
+    const double *Ccur;         // contributions of the resident ranks
+    float *A, *B;               // FP32 copies of the contributions (nullable)
+};
+
+constexpr int kBeginThreads = 1024;
+static_assert(kSmallBatch <= kBeginThreads, "one batch entry per thread");
+
+__global__ __launch_bounds__(kBeginThreads) void k_begin(IterArgs a, BeginArgs b)
+{
+    if (blockIdx.x > 0) {
+        const int64_t step = (int64_t)(gridDim.x - 1) * kBeginThreads;
+        for (int64_t v = (int64_t)(blockIdx.x - 1) * kBeginThreads + threadIdx.x; v < a.n; v += step) {
+            double c;
+            if (b.ranks) {
+                const double r = b.ranks == 1 ? b.prev[b.int2ext[v]] : 1.0 / (double)a.n;
+                c = r / (double)a.out_cnt[v];
+                b.R0[v] = r;
+                b.R1[v] = r;
+                b.C0[v] = c;
+                b.C1[v] = c;
+            } else {
+                c = b.Ccur[v];
+            }
+            if (b.A) {
+                b.A[v] = (float)c;
+                b.B[v] = (float)c;
+            }
+        }
+        return;
+    }
+    __shared__ uint32_t s_light, s_heavy, s_err;
+    __shared__ unsigned long long s_reach;
+    if (threadIdx.x == 0) {
+        reset_ctl(a.ctl);
+        s_light = s_heavy = s_err = 0;
+        s_reach = 0;
     }
     __syncthreads();
-    if (threadIdx.x == 0 && s_new) {
-        atomicAdd(&ctl->affected0, s_new);
-        atomicAdd(&ctl->reach0, s_deg);
+    const int64_t tot = b.nd + b.ni, i = threadIdx.x;
+    if (i < tot) {
+        const bool del = i < b.nd;
+        const int64_t k = del ? i : i - b.nd;
+        const int32_t s = (del ? b.src[0] : b.src[2])[k], d = (del ? b.src[1] : b.src[3])[k];
+        const int32_t u = s >= 0 && s < a.n ? b.ext2int[s] : -1;
+        const int32_t w = d >= 0 && d < a.n ? b.ext2int[d] : -1;
+        int32_t *to = b.staged + (del ? 0 : 2 * b.nd);
+        to[k] = u;
+        to[k + (del ? b.nd : b.ni)] = w;
+        if (u < 0 || w < 0) s_err = 1;
+        if (u >= 0 && atomicMax(&a.xstamp[u], a.sbase) < a.sbase) {
+            const uint32_t oc = a.out_cnt[u];
+            atomicAdd(&s_reach, (unsigned long long)oc);
+            if (oc > kHeavyRow) b.heavy[atomicAdd(&s_heavy, 1u)] = u;
+            else b.light[atomicAdd(&s_light, 1u)] = u;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        Ctl *ctl = a.ctl;
+        ctl->mk_light = s_light;
+        ctl->mk_heavy = s_heavy;
+        ctl->reach = s_reach;
+        if (s_err) {
+            ctl->err = 1;
+            ctl->done = 1;
+        }
+        if (b.snap) snap_ctl<false>(ctl, a.max_iters, a.sparse_limit, b.dense, a.tol, a.ftol);
     }
 }
 
@@ -944,16 +1099,6 @@ __global__ __launch_bounds__(kBlock) void k_finish(int32_t n, const uint32_t *st
     if (threadIdx.x == 0 && s_cnt) atomicAdd(&ctl->affected, s_cnt);
 }
 
-// Precision form: FP32 copies of the FP64 contributions, both buffers.
-__global__ void k_c32_init(int32_t n, const double *C, float *A, float *B)
-{
-    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-        const float c = (float)C[v];
-        A[v] = c;
-        B[v] = c;
-    }
-}
-
 // Sum of the ranks in FP64 with a fixed order: each workgroup folds a fixed
 // range with a fixed tree, then one workgroup folds the partials in order.
 constexpr int kSumBlocks = 1024;
@@ -1014,14 +1159,16 @@ static inline int blocks_for(int64_t items, int per_block = kBlock)
 // lists (2 (nd + ni) entries).
 static void launch_initial_marking(dfpr_graph *g, const IterArgs &a, int64_t nd,
                                    const int32_t *ds, const int32_t *dd, int64_t ni,
-                                   const int32_t *is, int dense, int32_t *lists)
+                                   const int32_t *is, int dense, int32_t *lists, int snap,
+                                   bool claimed = false)
 {
     int32_t *light = lists;
     int32_t *heavy = light + (nd + ni);
-    k_mark_claim<<<blocks_for(nd + ni), kBlock, 0, g->stream>>>(a, nd, ds, ni, is, light, heavy);
+    if (!claimed)
+        k_mark_claim<<<blocks_for(nd + ni), kBlock, 0, g->stream>>>(a, nd, ds, ni, is, light, heavy);
     const int64_t waves = std::max<int64_t>(nd + ni, 1024);
     k_mark_initial<<<(unsigned)std::min<int64_t>(blocks_for(waves * kWave), 2048), kBlock, 0,
-                     g->stream>>>(a, nd, dd, light, heavy, dense);
+                     g->stream>>>(a, nd, dd, light, heavy, dense, snap);
 }
 
 
@@ -1204,7 +1351,7 @@ static uint32_t resident_hub(const dfpr_graph *g, bool f32, uint32_t G)
 // and the control block's host copy is the state it left; otherwise nothing
 // was changed.
 static int launch_resident(dfpr_graph *g, IterArgs a, bool df, bool f32, int it0, int it, int base,
-                           bool full, uint32_t limit, bool *ran)
+                           bool full, uint32_t limit, Close *close, bool *ran)
 {
     *ran = false;
     if (!g->it.res || g->res_used >= kLoopLaunches) return DFPR_OK;
@@ -1228,6 +1375,9 @@ static int launch_resident(dfpr_graph *g, IterArgs a, bool df, bool f32, int it0
     P.limit = limit;
     P.go = g->res_used++;
     P.tag = g->res_tag + 1;
+    P.close = close ? 1 : 0;
+    P.out = close ? close->out : nullptr;
+    P.ext2int = g->ext2int;
     g->res_tag += kResTags;
     a.mirror = g->ctl_host;
     const uint32_t G = full ? resident_grid(g) : (uint32_t)g->cus;
@@ -1237,15 +1387,16 @@ static int launch_resident(dfpr_graph *g, IterArgs a, bool df, bool f32, int it0
     else if (f32) k_resident<true, true><<<G, kResThreads, 0, g->stream>>>(a, P);
     else k_resident<true, false><<<G, kResThreads, 0, g->stream>>>(a, P);
     DFPR_HIP(hipGetLastError());
-    DFPR_HIP(hipEventRecord(g->evc[0], g->stream));
-    DFPR_HIP(hipEventSynchronize(g->evc[0]));
-    if (g->ctl_host->loop_fail) return set_error(DFPR_E_DEVICE, "resident loop: a barrier timed out");
+    DFPR_HIP(hipEventRecord(g->ev1, g->stream));
+    DFPR_HIP(hipStreamSynchronize(g->stream));
+    if (g->ctl_host->loop_fail && g->ctl_host->loop_ran == P.tag) return set_error(DFPR_E_DEVICE, "resident loop: a barrier timed out");
     *ran = g->ctl_host->loop_ran == P.tag;
+    if (close) close->done = *ran && g->ctl_host->loop_closed;
     return DFPR_OK;
 }
 
 static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint32_t sbase,
-                    int it0, int base, int *res_buf)
+                    int it0, int base, int *res_buf, Close *close = nullptr)
 {
     IterArgs a = iter_args(g, p, sbase);
     const bool async = p.mode == DFPR_ASYNC && !f32;
@@ -1278,7 +1429,8 @@ static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint
         const uint32_t limit = device_loop ? kLoopRows : 0xFFFFFFFFu;
         while (next_it < p.max_iters) {
             bool ran = false;
-            DFPR_CHECK_RC(launch_resident(g, a, df, f32, it0, next_it, base, full, limit, &ran));
+            DFPR_CHECK_RC(launch_resident(g, a, df, f32, it0, next_it, base, full, limit,
+                                           f32 ? nullptr : close, &ran));
             if (!ran) break;
             const Ctl &c = *g->ctl_host;
             const int steps = c.iterations - next_it;
@@ -1456,6 +1608,40 @@ static void fill_stats(dfpr_graph *g, dfpr_stats *st, bool df)
     st->edges_processed = (int64_t)c.edges;
 }
 
+// k_begin of a call: the loop state and the starting ranks (prev, host or
+// device; uniform; or the resident ones), FP32 contributions with `f32`, and
+// whatever `b` already asks for.
+static int launch_begin(dfpr_graph *g, const IterArgs &a, BeginArgs b, const double *prev, int prev_dev,
+                        bool uniform, bool f32)
+{
+    const int32_t n = g->n;
+    if (prev && !prev_dev) {
+        DFPR_HIP(hipMemcpyAsync(g->Rx, prev, (size_t)n * 8, hipMemcpyHostToDevice, g->stream));
+        prev = g->Rx;
+    }
+    b.ext2int = g->ext2int;
+    b.int2ext = g->int2ext;
+    b.ranks = prev ? 1 : uniform ? 2 : 0;
+    b.prev = prev;
+    b.R0 = g->R[0];
+    b.R1 = g->R[1];
+    b.C0 = g->C[0];
+    b.C1 = g->C[1];
+    b.Ccur = g->C[g->cur];
+    if (f32) {
+        b.A = g->C32[0];
+        b.B = g->C32[1];
+    }
+    const int64_t work = b.ranks || f32 ? ((int64_t)n + kBeginThreads - 1) / kBeginThreads : 0;
+    k_begin<<<1 + (unsigned)std::min<int64_t>(work, 4096), kBeginThreads, 0, g->stream>>>(a, b);
+    DFPR_HIP(hipGetLastError());
+    g->refine_sweeps = 0;
+    g->loop_iters = 0;
+    g->res_used = 0;
+    std::memset(g->prof_base, 0, sizeof(g->prof_base));
+    return DFPR_OK;
+}
+
 // Static (prev == NULL and !use_resident: uniform start) or Naive-dynamic
 // (start from prev, or from the resident ranks).
 static int full_sweeps(dfpr_graph *g, const dfpr_params *pp, const double *prev, int prev_dev,
@@ -1470,34 +1656,24 @@ static int full_sweeps(dfpr_graph *g, const dfpr_params *pp, const double *prev,
     hipStream_t s = g->stream;
     DFPR_HIP(hipEventRecord(g->ev0, s));
     const int cur = g->cur;
-    if (prev) {
-        rc = ranks_from_caller(g, prev, prev_dev, g->R[cur]);
-        if (rc) return rc;
-        k_init_ranks<<<blocks_for(n), kBlock, 0, s>>>(n, g->R[cur], g->R[0], g->R[1], g->C[0],
-                                                      g->C[1], g->csr[1].cnt);
-    } else if (!use_resident) {
-        k_init_ranks<<<blocks_for(n), kBlock, 0, s>>>(n, nullptr, g->R[0], g->R[1], g->C[0],
-                                                      g->C[1], g->csr[1].cnt);
-    }
-    k_reset<<<1, 1, 0, s>>>(g->ctl);
-    k_snap<<<1, 1, 0, s>>>(g->ctl, p.max_iters, g->sparse_limit, 1, g->ctl_host, p.tol,
-                           p.frontier_tol);
-    DFPR_HIP(hipGetLastError());
+    BeginArgs b{};
+    b.snap = 1;
+    b.dense = 1;
+    DFPR_CHECK_RC(launch_begin(g, iter_args(g, p, 0), b, prev, prev_dev, !prev && !use_resident, false));
     int res = cur;
-    g->refine_sweeps = 0;
-    g->loop_iters = 0;
-    g->res_used = 0;
-    std::memset(g->prof_base, 0, sizeof(g->prof_base));
     DFPR_HIP(hipEventRecord(g->ev_mid, s));
-    rc = run_loop(g, p, false, false, 0, 0, cur, &res);
+    Close close;
+    if (ranks_out) close.out = out_dev ? ranks_out : g->Rx;
+    rc = run_loop(g, p, false, false, 0, 0, cur, &res, &close);
     if (rc) return rc;
-    k_copy2<<<blocks_for(n), kBlock, 0, s>>>(n, g->R[res], g->R[res ^ 1], g->C[res],
-                                             g->C[res ^ 1]);
     g->cur = res;
-    DFPR_HIP(hipEventRecord(g->ev1, s));
-    if (ranks_out) {
-        rc = ranks_to_caller(g, g->R[res], ranks_out, out_dev);
-        if (rc) return rc;
+    if (!close.done) {
+        k_copy2<<<blocks_for(n), kBlock, 0, s>>>(n, g->R[res], g->R[res ^ 1], g->C[res],
+                                                 g->C[res ^ 1]);
+        DFPR_HIP(hipEventRecord(g->ev1, s));
+        if (ranks_out) DFPR_CHECK_RC(ranks_to_caller(g, g->R[res], ranks_out, out_dev));
+    } else if (ranks_out && !out_dev) {
+        DFPR_HIP(hipMemcpyAsync(ranks_out, g->Rx, (size_t)n * 8, hipMemcpyDeviceToHost, s));
     }
     DFPR_HIP(hipStreamSynchronize(s));
     fill_stats(g, st, false);
@@ -1505,45 +1681,52 @@ static int full_sweeps(dfpr_graph *g, const dfpr_params *pp, const double *prev,
 }
 
 // Everything of a Dynamic Frontier call before its iterations, enqueued on
-// the graph's stream: optional previous ranks, a stamp base, the initial
-// marking of the batch (device arrays) and the snapshot of iteration 0.
-// Returns the stamp base.
-int df_begin(dfpr_graph *g, const dfpr_params &p, int64_t nd, const int32_t *bds,
-             const int32_t *bdd, int64_t ni, const int32_t *bis, const int32_t *bid,
-             const double *prev, int prev_dev, uint32_t *sbase_out, int32_t *lists)
+// the graph's stream: the batch (host or device arrays) staged in `staging`
+// (device arrays only) or in the graph's buffer, optional previous ranks (host
+// or device, as the batch), a stamp base, the initial marking and the
+// snapshot of iteration 0.  Returns the stamp base.
+int df_begin(dfpr_graph *g, const dfpr_params &p, int64_t nd, const int32_t *ds,
+             const int32_t *dd, int64_t ni, const int32_t *is, const int32_t *id, int on_device,
+             const double *prev, uint32_t *sbase_out, int32_t *staging)
 {
-    if (!lists) lists = g->ap.batch_dev + 2 * (nd + ni);
-    const int32_t n = g->n;
-    hipStream_t s = g->stream;
-    const int cur = g->cur;
-    int rc = DFPR_OK;
-    if (prev) {
-        rc = ranks_from_caller(g, prev, prev_dev, g->R[cur]);
-        if (rc) return rc;
-        k_init_ranks<<<blocks_for(n), kBlock, 0, s>>>(n, g->R[cur], g->R[0], g->R[1], g->C[0],
-                                                      g->C[1], g->csr[1].cnt);
+    const int64_t tot = nd + ni;
+    const bool small = tot <= kSmallBatch;
+    const int32_t *bds = nullptr, *bdd = nullptr, *bis = nullptr, *bid = nullptr;
+    BeginArgs b{};
+    if (small) {
+        const int32_t *const in[4] = {ds, dd, is, id};
+        for (int k = 0; k < 4; k++) b.src[k] = in[k];
+        if (!staging) DFPR_CHECK_RC(stage_raw(g, nd, ds, dd, ni, is, id, on_device, b.src));
+    } else if (staging) {
+        DFPR_CHECK_RC(stage_batch_into(g, nd, ds, dd, ni, is, id, staging, &bds, &bdd, &bis, &bid));
+    } else {
+        DFPR_CHECK_RC(stage_batch(g, nd, ds, dd, ni, is, id, on_device, &bds, &bdd, &bis, &bid));
     }
+    int32_t *const buf = staging ? staging : g->ap.batch_dev;
+    int32_t *const lists = buf + 2 * tot;
     uint32_t sbase = 0;
-    rc = take_base(g, p.max_iters, &sbase);
-    if (rc) return rc;
+    DFPR_CHECK_RC(take_base(g, p.max_iters, &sbase));
     // the initial marking decides on the device whether the batch's
     // sources reach enough vertices to start on the full schedule
     const int dense = 0;
-    IterArgs a = iter_args(g, p, sbase);
-    k_reset<<<1, 1, 0, s>>>(g->ctl);
-    if (nd + ni > 0) {
-        k_validate<<<blocks_for(nd + ni), kBlock, 0, s>>>(n, nd, bds, bdd, ni, bis, bid, g->ctl);
-        launch_initial_marking(g, a, nd, bds, bdd, ni, bis, dense, lists);
+    const IterArgs a = iter_args(g, p, sbase);
+    if (small) {
+        b.nd = nd;
+        b.ni = ni;
+        b.staged = buf;
+        b.light = lists;
+        b.heavy = lists + tot;
+        bdd = buf + nd;
     }
-    k_snap<<<1, 1, 0, s>>>(g->ctl, p.max_iters, g->sparse_limit, dense, g->ctl_host, p.tol,
-                           p.frontier_tol);
-    if (p.precision == DFPR_FP32_KAHAN)
-        k_c32_init<<<blocks_for(n), kBlock, 0, s>>>(n, g->C[cur], g->C32[0], g->C32[1]);
+    b.snap = tot == 0;
+    DFPR_CHECK_RC(launch_begin(g, a, b, prev, on_device, false, p.precision == DFPR_FP32_KAHAN));
+    if (tot > 0) {
+        if (!small)
+            k_validate<<<blocks_for(tot), kBlock, 0, g->stream>>>(g->n, nd, bds, bdd, ni, bis, bid,
+                                                                 g->ctl);
+        launch_initial_marking(g, a, nd, bds, bdd, ni, bis, dense, lists, 1, small);
+    }
     DFPR_HIP(hipGetLastError());
-    g->refine_sweeps = 0;
-    g->loop_iters = 0;
-    g->res_used = 0;
-    std::memset(g->prof_base, 0, sizeof(g->prof_base));
     *sbase_out = sbase;
     return DFPR_OK;
 }
@@ -1570,18 +1753,40 @@ int df_phase_end(dfpr_graph *g, int res, bool call_done)
 }
 
 // After the last iteration (result in buffer `res`): bring the other buffer
-// up to date on the processed rows, count the marks, and make the result
-// the resident ranks.
-int df_finish(dfpr_graph *g, uint32_t sbase, int res, int32_t iters)
+// up to date on the processed rows, count the marks (unless the resident loop
+// has `closed` the call), and make the result the resident ranks.
+int df_finish(dfpr_graph *g, uint32_t sbase, int res, int32_t iters, bool closed)
 {
     const int32_t n = g->n;
-    k_finish<<<std::min(blocks_for(n), 2048), kBlock, 0, g->stream>>>(
-        n, g->stamp, sbase, sbase + (uint32_t)iters, g->R[res], g->R[res ^ 1], g->C[res],
-        g->C[res ^ 1], g->ctl, g->bins, g->n);
-    DFPR_HIP(hipGetLastError());
+    if (!closed) {
+        k_finish<<<std::min(blocks_for(n), 2048), kBlock, 0, g->stream>>>(
+            n, g->stamp, sbase, sbase + (uint32_t)iters, g->R[res], g->R[res ^ 1], g->C[res],
+            g->C[res ^ 1], g->ctl, g->bins, g->n);
+        DFPR_HIP(hipGetLastError());
+    }
     g->cur = res;
     g->last_base = sbase;
     g->last_iters = iters;
+    return DFPR_OK;
+}
+
+// The end of a Dynamic Frontier or Traversal call, after its last iteration.
+static int df_end(dfpr_graph *g, uint32_t sbase, int res, const Close &close, double *ranks_out,
+                  int on_device, dfpr_stats *st)
+{
+    hipStream_t s = g->stream;
+    if (g->ctl_host->err) return set_error(DFPR_E_RANGE, "vertex id outside [0, n) in the batch");
+    DFPR_CHECK_RC(df_finish(g, sbase, res, g->ctl_host->iterations, close.done));
+    if (!close.done) {
+        DFPR_HIP(hipEventRecord(g->ev1, s));
+        if (ranks_out) DFPR_CHECK_RC(ranks_to_caller(g, g->R[res], ranks_out, on_device));
+        DFPR_CHECK_RC(ctl_to_host(g));
+        DFPR_HIP(hipStreamSynchronize(s));
+    } else if (ranks_out && !on_device) {
+        DFPR_HIP(hipMemcpyAsync(ranks_out, g->Rx, (size_t)g->n * 8, hipMemcpyDeviceToHost, s));
+        DFPR_HIP(hipStreamSynchronize(s));
+    }
+    fill_stats(g, st, true);
     return DFPR_OK;
 }
 
@@ -1608,15 +1813,12 @@ static int df_impl(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32
     if (!guard.ok) return set_error(DFPR_E_BUSY, "graph in use");
     hipStream_t s = g->stream;
     DFPR_HIP(hipEventRecord(g->ev0, s));
-    const int32_t *bds, *bdd, *bis, *bid;
-    if (staging) rc = stage_batch_into(g, nd, ds, dd, ni, is, id, staging, &bds, &bdd, &bis, &bid);
-    else rc = stage_batch(g, nd, ds, dd, ni, is, id, on_device, &bds, &bdd, &bis, &bid);
-    if (rc) return rc;
     const int cur = g->cur;
     uint32_t sbase = 0;
-    rc = df_begin(g, p, nd, bds, bdd, ni, bis, bid, prev, on_device, &sbase,
-                  staging ? staging + 2 * (nd + ni) : nullptr);
+    rc = df_begin(g, p, nd, ds, dd, ni, is, id, on_device, prev, &sbase, staging);
     if (rc) return rc;
+    Close close;
+    if (ranks_out) close.out = on_device ? ranks_out : g->Rx;
     DFPR_HIP(hipEventRecord(g->ev_mid, s));
     int res = cur;
     if (p.precision == DFPR_FP32_KAHAN) {
@@ -1630,27 +1832,15 @@ static int df_impl(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32
         if (rc) return rc;
         if (!done) {
             const int it0 = g->ctl_host->iterations;
-            rc = run_loop(g, p, true, false, sbase, it0, res, &res);
+            rc = run_loop(g, p, true, false, sbase, it0, res, &res, &close);
             if (rc) return rc;
             g->refine_sweeps = g->ctl_host->iterations - it0;
         }
     } else {
-        rc = run_loop(g, p, true, false, sbase, 0, cur, &res);
+        rc = run_loop(g, p, true, false, sbase, 0, cur, &res, &close);
         if (rc) return rc;
     }
-    const int32_t iters = g->ctl_host->iterations;
-    if (g->ctl_host->err) return set_error(DFPR_E_RANGE, "vertex id outside [0, n) in the batch");
-    rc = df_finish(g, sbase, res, iters);
-    if (rc) return rc;
-    DFPR_HIP(hipEventRecord(g->ev1, s));
-    if (ranks_out) {
-        rc = ranks_to_caller(g, g->R[res], ranks_out, on_device);
-        if (rc) return rc;
-    }
-    DFPR_CHECK_RC(ctl_to_host(g));
-    DFPR_HIP(hipStreamSynchronize(s));
-    fill_stats(g, st, true);
-    return DFPR_OK;
+    return df_end(g, sbase, res, close, ranks_out, on_device, st);
 }
 
 int df_device_staged(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32_t *ds,
@@ -1750,17 +1940,11 @@ static int dt_impl(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32
     rc = stage_batch(g, nd, ds, dd, ni, is, id, on_device, &bds, &bdd, &bis, &bid);
     if (rc) return rc;
     const int cur = g->cur;
-    if (prev) {
-        rc = ranks_from_caller(g, prev, on_device, g->R[cur]);
-        if (rc) return rc;
-        k_init_ranks<<<blocks_for(n), kBlock, 0, s>>>(n, g->R[cur], g->R[0], g->R[1], g->C[0],
-                                                      g->C[1], g->csr[1].cnt);
-    }
     uint32_t sbase = 0;
     rc = take_base(g, p.max_iters, &sbase);
     if (rc) return rc;
     IterArgs a = iter_args(g, p, sbase);
-    k_reset<<<1, 1, 0, s>>>(g->ctl);
+    DFPR_CHECK_RC(launch_begin(g, a, BeginArgs{}, prev, on_device, false, false));
     if (nd + ni > 0) {
         k_validate<<<blocks_for(nd + ni), kBlock, 0, s>>>(n, nd, bds, bdd, ni, bis, bid, g->ctl);
         rc = traverse(g, a, nd, bds, bdd, ni, bis, false);
@@ -1771,27 +1955,13 @@ static int dt_impl(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32
     k_snap<<<1, 1, 0, s>>>(g->ctl, p.max_iters, g->sparse_limit, 1, g->ctl_host, p.tol,
                            p.frontier_tol);
     DFPR_HIP(hipGetLastError());
-    g->refine_sweeps = 0;
-    g->loop_iters = 0;
-    g->res_used = 0;
-    std::memset(g->prof_base, 0, sizeof(g->prof_base));
     DFPR_HIP(hipEventRecord(g->ev_mid, s));
     int res = cur;
-    rc = run_loop(g, p, true, false, sbase, 0, cur, &res);
+    Close close;
+    if (ranks_out) close.out = on_device ? ranks_out : g->Rx;
+    rc = run_loop(g, p, true, false, sbase, 0, cur, &res, &close);
     if (rc) return rc;
-    const int32_t iters = g->ctl_host->iterations;
-    if (g->ctl_host->err) return set_error(DFPR_E_RANGE, "vertex id outside [0, n) in the batch");
-    rc = df_finish(g, sbase, res, iters);
-    if (rc) return rc;
-    DFPR_HIP(hipEventRecord(g->ev1, s));
-    if (ranks_out) {
-        rc = ranks_to_caller(g, g->R[res], ranks_out, on_device);
-        if (rc) return rc;
-    }
-    DFPR_CHECK_RC(ctl_to_host(g));
-    DFPR_HIP(hipStreamSynchronize(s));
-    fill_stats(g, st, true);
-    return DFPR_OK;
+    return df_end(g, sbase, res, close, ranks_out, on_device, st);
 }
 
 // Stamp arrays of the marking-only calls (dfpr_mark_affected,
@@ -1950,7 +2120,7 @@ int dfpr_mark_affected(dfpr_graph *g, int64_t n_del, const int32_t *del_src,
     k_reset<<<1, 1, 0, s>>>(g->ctl);
     if (n_del + n_ins > 0)
         launch_initial_marking(g, a, n_del, bds, bdd, n_ins, bis, 1,
-                               g->ap.batch_dev + 2 * (n_del + n_ins));
+                               g->ap.batch_dev + 2 * (n_del + n_ins), 0);
     DFPR_HIP(hipGetLastError());
     std::vector<uint32_t> st(n);
     DFPR_HIP(hipMemcpyAsync(st.data(), g->mstamp, (size_t)n * 4, hipMemcpyDeviceToHost, s));

@@ -224,12 +224,9 @@ static int admit(dfpr_server *srv, int64_t r, Slot &sl, double now_ms)
         if (rc) break;
         q.res.applied[0] = applied[0];
         q.res.applied[1] = applied[1];
-        const int32_t *bds, *bdd, *bis, *bid;
-        rc = stage_batch(g, nd, q.ds.data(), q.dd.data(), ni, q.is.data(), q.id.data(), 0, &bds,
-                         &bdd, &bis, &bid);
-        if (rc) break;
         uint32_t sbase = 0;
-        rc = df_begin(g, ge.p, nd, bds, bdd, ni, bis, bid, nullptr, 0, &sbase);
+        rc = df_begin(g, ge.p, nd, q.ds.data(), q.dd.data(), ni, q.is.data(), q.id.data(), 0, nullptr,
+                      &sbase);
         if (rc) break;
         if (hipStreamSynchronize(srv->astream) != hipSuccess) {
             rc = set_error(DFPR_E_DEVICE, "admission failed on the device");
