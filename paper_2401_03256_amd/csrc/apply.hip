@@ -930,6 +930,16 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(uint64_t *x, uint64_t len
     }
 }
 
+uint64_t scan_u64_sums(uint64_t len) { return (len + kScanTile - 1) / kScanTile; }
+
+void scan_u64(hipStream_t s, uint64_t *x, uint64_t len, uint64_t *sums)
+{
+    const uint32_t nb = (uint32_t)scan_u64_sums(len);
+    k_scan_sums<<<nb, kBlock, 0, s>>>(x, len, sums);
+    k_scan_top<<<1, kBlock, 0, s>>>(sums, nb);
+    k_scan_apply<<<nb, kBlock, 0, s>>>(x, len, sums);
+}
+
 // copy every row's live entries to its new place (one wave per row)
 __global__ __launch_bounds__(kBlock) void k_move_rows(int32_t n, uint32_t *beg,
                                                       const uint32_t *cnt, const int32_t *idx,
@@ -1124,9 +1134,8 @@ static int relayout(dfpr_graph *g, int o, uint32_t novf, const uint64_t *sorted_
         ~Tmp() { (void)hipFree(p); }
     } caps_buf, sums_buf;
     const uint64_t len = (uint64_t)n + 1;
-    const uint32_t nb = (uint32_t)((len + kScanTile - 1) / kScanTile);
     DFPR_HIP(hipMalloc(&caps_buf.p, len * 8));
-    DFPR_HIP(hipMalloc(&sums_buf.p, (uint64_t)nb * 8));
+    DFPR_HIP(hipMalloc(&sums_buf.p, scan_u64_sums(len) * 8));
     uint64_t *const caps = caps_buf.p, *const sums = sums_buf.p;
     k_caps<<<grid_for(len), kBlock, 0, s>>>(n, c.cap, caps);
     k_ovf_caps<<<grid_for(novf), kBlock, 0, s>>>(novf, g->ap.ovf_list[o], g->ap.ovf_need[o],
@@ -1134,9 +1143,7 @@ static int relayout(dfpr_graph *g, int o, uint32_t novf, const uint64_t *sorted_
     std::vector<int32_t> need(novf);
     DFPR_HIP(hipMemcpyAsync(need.data(), g->ap.ovf_need[o], (size_t)novf * 4,
                             hipMemcpyDeviceToHost, s));
-    k_scan_sums<<<nb, kBlock, 0, s>>>(caps, len, sums);
-    k_scan_top<<<1, kBlock, 0, s>>>(sums, nb);
-    k_scan_apply<<<nb, kBlock, 0, s>>>(caps, len, sums);
+    scan_u64(s, caps, len, sums);
     uint64_t packed = 0;
     DFPR_HIP(hipMemcpyAsync(&packed, caps + n, 8, hipMemcpyDeviceToHost, s));
     DFPR_HIP(hipStreamSynchronize(s));

@@ -159,10 +159,9 @@ struct ApplyBufs {
 struct dfpr_graph {
     int32_t n = 0;
     int64_t m = 0;                    // live edges, self-loops included
+    void *arena = nullptr;            // device: every array of fixed size below
     int32_t *ext2int = nullptr;       // device: caller id -> internal id
     int32_t *int2ext = nullptr;       // device: internal id -> caller id
-    std::vector<int32_t> ext2int_h;   // host copies of the two maps
-    std::vector<int32_t> int2ext_h;
     double *Rx = nullptr;             // n ranks in the caller's numbering (staging)
     dfpr::Csr csr[2];                 // [0] = in (rows = dst), [1] = out (rows = src)
     double *R[2] = {};                // rank double buffer
@@ -257,6 +256,13 @@ int map_ids(dfpr_graph *g, const int32_t *in, int32_t *out, int64_t len);
 int map_ids4(dfpr_graph *g, const int32_t *const in[4], const int64_t len[4], int32_t *out);
 int ranks_to_caller(const dfpr_graph *g, const double *Rint, double *out, int out_dev);
 int ranks_from_caller(const dfpr_graph *g, const double *in, int in_dev, double *Rint);
+
+// Flags (n bytes, host) of the vertices whose stamp lies in [lo, hi]; waits.
+int flags_to_caller(const dfpr_graph *g, const uint32_t *stamp, uint32_t lo, uint32_t hi, uint8_t *out);
+
+// Exclusive scan of x[0 .. len) in place; sums: scan_u64_sums(len) entries.
+uint64_t scan_u64_sums(uint64_t len);
+void scan_u64(hipStream_t s, uint64_t *x, uint64_t len, uint64_t *sums);
 
 // device helpers (rank.hip)
 int64_t apply_slab_bytes(const dfpr_graph *g);

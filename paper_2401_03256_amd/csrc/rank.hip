@@ -2063,7 +2063,6 @@ int dfpr_mark_reachable(dfpr_graph *g, int64_t n_del, const int32_t *del_src,
     if (rc) return rc;
     BusyGuard guard(g);
     if (!guard.ok) return set_error(DFPR_E_BUSY, "graph in use");
-    const int32_t n = g->n;
     hipStream_t s = g->stream;
     const int32_t *bds, *bdd, *bis, *bid;
     rc = stage_batch(g, n_del, del_src, del_dst, n_ins, ins_src, ins_dst, 0, &bds, &bdd, &bis,
@@ -2083,11 +2082,7 @@ int dfpr_mark_reachable(dfpr_graph *g, int64_t n_del, const int32_t *del_src,
         rc = traverse(g, a, n_del, bds, bdd, n_ins, bis, false);
         if (rc) return rc;
     }
-    std::vector<uint32_t> st(n);
-    DFPR_HIP(hipMemcpyAsync(st.data(), g->mstamp, (size_t)n * 4, hipMemcpyDeviceToHost, s));
-    DFPR_HIP(hipStreamSynchronize(s));
-    for (int32_t v = 0; v < n; v++) flags_out[v] = st[g->ext2int_h[v]] == sbase ? 1 : 0;
-    return DFPR_OK;
+    return flags_to_caller(g, g->mstamp, sbase, sbase, flags_out);
 }
 
 int dfpr_mark_affected(dfpr_graph *g, int64_t n_del, const int32_t *del_src,
@@ -2103,7 +2098,6 @@ int dfpr_mark_affected(dfpr_graph *g, int64_t n_del, const int32_t *del_src,
     if (rc) return rc;
     BusyGuard guard(g);
     if (!guard.ok) return set_error(DFPR_E_BUSY, "graph in use");
-    const int32_t n = g->n;
     hipStream_t s = g->stream;
     const int32_t *bds, *bdd, *bis, *bid;
     rc = stage_batch(g, n_del, del_src, del_dst, n_ins, ins_src, ins_dst, 0, &bds, &bdd, &bis,
@@ -2122,31 +2116,27 @@ int dfpr_mark_affected(dfpr_graph *g, int64_t n_del, const int32_t *del_src,
         launch_initial_marking(g, a, n_del, bds, bdd, n_ins, bis, 1,
                                g->ap.batch_dev + 2 * (n_del + n_ins), 0);
     DFPR_HIP(hipGetLastError());
-    std::vector<uint32_t> st(n);
-    DFPR_HIP(hipMemcpyAsync(st.data(), g->mstamp, (size_t)n * 4, hipMemcpyDeviceToHost, s));
-    DFPR_HIP(hipStreamSynchronize(s));
-    for (int32_t v = 0; v < n; v++) flags_out[v] = st[g->ext2int_h[v]] == sbase ? 1 : 0;
-    return DFPR_OK;
+    return flags_to_caller(g, g->mstamp, sbase, sbase, flags_out);
 }
 
 int dfpr_get_affected(const dfpr_graph *g, uint8_t *flags_out)
 {
     if (!g || !flags_out) return set_error(DFPR_E_ARG, "NULL argument");
-    const int32_t n = g->n;
-    std::vector<uint32_t> st(n);
-    DFPR_HIP(hipStreamSynchronize(g->stream));
-    DFPR_HIP(hipMemcpy(st.data(), g->stamp, (size_t)n * 4, hipMemcpyDeviceToHost));
-    const uint32_t lo = g->last_base, hi = g->last_base + (uint32_t)std::max(g->last_iters, 0);
-    for (int32_t v = 0; v < n; v++) {
-        const uint32_t x = st[g->ext2int_h[v]];
-        flags_out[v] = (g->last_iters >= 0 && x >= lo && x <= hi) ? 1 : 0;
+    if (g->last_iters < 0) {
+        std::memset(flags_out, 0, (size_t)g->n);
+        return DFPR_OK;
     }
-    return DFPR_OK;
+    return flags_to_caller(g, g->stamp, g->last_base, g->last_base + (uint32_t)g->last_iters, flags_out);
 }
 
 int dfpr_profile_reset(dfpr_graph *g, int enable)
 {
     if (!g) return set_error(DFPR_E_ARG, "graph is NULL");
+    // per-launch timing only, read after a stream synchronisation: no
+    // system-scope fence (with it, each record stalls the queue ~6 us)
+    if (enable)
+        for (hipEvent_t &ev : g->evk)
+            if (!ev) DFPR_HIP(hipEventCreateWithFlags(&ev, hipEventDisableSystemFence));
     g->prof = Profile{};
     g->prof.enabled = enable ? 1 : 0;
     return DFPR_OK;
