@@ -951,13 +951,16 @@ struct BfsQueues {
     uint32_t *clear, *hclear;         // the level after next
 };
 
-// Every lane of the wave calls it; x < 0 claims nothing.
+// Every lane of the wave calls it; x < 0 claims nothing.  `deg` sums this
+// lane's claims' out-edges.
 __device__ inline void bfs_claim(const IterArgs &a, int32_t x, const BfsQueues &q, bool append,
-                                 unsigned long long &mine)
+                                 unsigned long long &mine, unsigned long long &deg)
 {
     bool nw = false;
     if (x >= 0 && a.stamp[x] < a.sbase) nw = atomicMax(&a.stamp[x], a.sbase) < a.sbase;
-    const bool big = nw && a.out_cnt[x] > kHeavyRow;
+    const uint32_t oc = nw ? a.out_cnt[x] : 0u;
+    deg += oc;
+    const bool big = oc > kHeavyRow;
     const unsigned long long ml = __ballot(nw && !big), mh = __ballot(big);
     const int lane = lane_id();
     const unsigned long long below = (1ull << lane) - 1ull;
@@ -979,27 +982,42 @@ __device__ inline void bfs_claim(const IterArgs &a, int32_t x, const BfsQueues &
     }
 }
 
+// A workgroup's claims (lane 0 of each wave holds `mine`) and their out-edges
+// into the control block.  Every thread calls it.
+__device__ inline void bfs_totals(Ctl *ctl, unsigned long long mine, unsigned long long deg,
+                                  unsigned long long &s_new, unsigned long long &s_reach)
+{
+    for (int off = kWave / 2; off > 0; off >>= 1) deg += __shfl_xor(deg, off, kWave);
+    if (lane_id() == 0 && mine) {
+        atomicAdd(&s_new, mine);
+        atomicAdd(&s_reach, deg);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_new) {
+        atomicAdd(&ctl->affected0, s_new);
+        atomicAdd(&ctl->reach, s_reach);
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_bfs_seed(IterArgs a, int64_t nd, const int32_t *ds,
                                                      const int32_t *dd, int64_t ni,
                                                      const int32_t *is, BfsQueues q, int append)
 {
-    __shared__ unsigned long long s_new;
+    __shared__ unsigned long long s_new, s_reach;
     if (a.ctl->err) return;
-    if (threadIdx.x == 0) s_new = 0;
+    if (threadIdx.x == 0) s_new = s_reach = 0;
     __syncthreads();
     const int lane = lane_id();
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
     const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
-    unsigned long long mine = 0;
+    unsigned long long mine = 0, deg = 0;
     for (int64_t b0 = wave * kWave; b0 < nd + ni; b0 += waves * kWave) {
         const int64_t i = b0 + lane;
         const int32_t u = i < nd + ni ? (i < nd ? ds[i] : is[i - nd]) : -1;
-        bfs_claim(a, u, q, append != 0, mine);
-        bfs_claim(a, i < nd ? dd[i] : -1, q, append != 0, mine);
+        bfs_claim(a, u, q, append != 0, mine, deg);
+        bfs_claim(a, i < nd ? dd[i] : -1, q, append != 0, mine, deg);
     }
-    if (lane == 0 && mine) atomicAdd(&s_new, mine);
-    __syncthreads();
-    if (threadIdx.x == 0 && s_new) atomicAdd(&a.ctl->affected0, s_new);
+    bfs_totals(a.ctl, mine, deg, s_new, s_reach);
 }
 
 // One level.  Light vertices: each wave takes 64 and walks their out-edges
@@ -1007,19 +1025,19 @@ __global__ __launch_bounds__(kBlock) void k_bfs_seed(IterArgs a, int64_t nd, con
 // workgroup takes chunks of kBlock out-edges of each of them.
 __global__ __launch_bounds__(kBlock) void k_bfs_level(IterArgs a, BfsQueues q, int append)
 {
-    __shared__ unsigned long long s_new;
+    __shared__ unsigned long long s_new, s_reach;
     if (a.ctl->err) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *q.clear = 0;
         *q.hclear = 0;
     }
     const uint32_t nin = *q.nin, nh = *q.nhin;
-    if (threadIdx.x == 0) s_new = 0;
+    if (threadIdx.x == 0) s_new = s_reach = 0;
     __syncthreads();
     const int lane = lane_id();
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
     const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
-    unsigned long long mine = 0;
+    unsigned long long mine = 0, reach = 0;
     for (int64_t b0 = wave * kWave; b0 < nin; b0 += waves * kWave) {
         const int64_t i = b0 + lane;
         const int32_t x = i < nin ? q.in[i] : -1;
@@ -1042,14 +1060,125 @@ __global__ __launch_bounds__(kBlock) void k_bfs_level(IterArgs a, BfsQueues q, i
             const uint32_t first = __shfl(incl, j) - __shfl(deg, j);
             const uint32_t base = __shfl(ob, j);
             const int32_t y = t < total ? a.out_idx[base + (tt - first)] : -1;
-            bfs_claim(a, y, q, append != 0, mine);
+            bfs_claim(a, y, q, append != 0, mine, reach);
         }
     }
     __shared__ HeavyShared hs;
-    walk_heavy(a, q.hin, nh, hs, [&](int32_t x) { bfs_claim(a, x, q, append != 0, mine); });
-    if (lane == 0 && mine) atomicAdd(&s_new, mine);
+    walk_heavy(a, q.hin, nh, hs, [&](int32_t x) { bfs_claim(a, x, q, append != 0, mine, reach); });
+    bfs_totals(a.ctl, mine, reach, s_new, s_reach);
+}
+
+// A wide level.  Appending hundreds of thousands of vertices to the queues
+// costs an atomic on one address per wave and round (13 ns each: 330 us a level
+// on R-MAT scale 19, 2.3 ms a search), so wide levels keep no queue: a pass
+// looks at every vertex and expands those marked but not expanded yet
+// (expansion stamp), marking with plain stores; a mark made in the pass may be
+// expanded by it too, which changes no result.  k_bfs_scan does the vertices of
+// up to kHeavyRow out-edges and lists the others for k_bfs_heavy.  Waves take
+// vertices a stride apart, since neighbouring ids have similar degrees.
+// *nfresh and *nheavy count what the pass expanded; the search is over when
+// that is nothing.
+__global__ __launch_bounds__(kBlock) void k_bfs_scan(IterArgs a, int32_t *heavy, uint32_t *nfresh,
+                                                     uint32_t *nheavy, uint32_t *clear, uint32_t *hclear)
+{
+    if (a.ctl->err) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *clear = 0;
+        *hclear = 0;
+    }
+    __shared__ uint32_t s_fresh;
+    if (threadIdx.x == 0) s_fresh = 0;
     __syncthreads();
-    if (threadIdx.x == 0 && s_new) atomicAdd(&a.ctl->affected0, s_new);
+    const int lane = lane_id();
+    const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
+    const int64_t wave = blockIdx.x * (int64_t)kWavesPerBlock + threadIdx.x / kWave;
+    uint32_t fresh = 0;
+    for (int64_t v0 = 0; v0 < a.n; v0 += waves * kWave) {
+        const int64_t v = v0 + lane * waves + wave;
+        const bool take = v < a.n && a.stamp[v] == a.sbase && a.xstamp[v] != a.sbase;
+        if (!__ballot(take)) continue;
+        if (take) a.xstamp[v] = a.sbase;
+        const uint32_t oc = take ? a.out_cnt[v] : 0u;
+        const bool big = oc > kHeavyRow;
+        const unsigned long long mh = __ballot(big);
+        if (mh) {
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(nheavy, (uint32_t)__popcll(mh));
+            at = __shfl(at, 0);
+            if (big) heavy[at + __popcll(mh & ((1ull << lane) - 1ull))] = (int32_t)v;
+        }
+        fresh += (uint32_t)__popcll(__ballot(take && !big));
+        // rows shorter than a wave together, the others one at a time
+        const uint32_t deg = oc < (uint32_t)kWave ? oc : 0u;
+        const uint32_t ob = deg ? a.out_beg[v] : 0u;
+        uint32_t incl = deg;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const uint32_t y = __shfl_up(incl, d);
+            if (lane >= d) incl += y;
+        }
+        expand_rows<false, false>(a, incl, deg, ob, __shfl(incl, kWave - 1), a.sbase);
+        for (unsigned long long q = __ballot(oc >= (uint32_t)kWave && !big); q; q &= q - 1)
+            mark_out_row<false, false>(a, __shfl((int32_t)v, __ffsll((long long)q) - 1), lane, kWave,
+                                       a.sbase);
+    }
+    if (lane == 0 && fresh) atomicAdd(&s_fresh, fresh);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_fresh) atomicAdd(nfresh, s_fresh);
+}
+
+__global__ __launch_bounds__(kBlock) void k_bfs_heavy(IterArgs a, const int32_t *heavy,
+                                                      const uint32_t *nheavy)
+{
+    __shared__ HeavyShared hs;
+    if (a.ctl->err) return;
+    walk_heavy(a, heavy, *nheavy, hs, [&](int32_t x) {
+        if (x >= 0 && a.stamp[x] < a.sbase) a.stamp[x] = a.sbase;
+    });
+}
+
+// The vertices marked but not expanded into the queues of the next level.
+__global__ __launch_bounds__(kBlock) void k_bfs_collect(IterArgs a, BfsQueues q)
+{
+    if (a.ctl->err) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *q.clear = 0;
+        *q.hclear = 0;
+    }
+    const int lane = lane_id();
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const int64_t step = (int64_t)gridDim.x * kBlock;
+    for (int64_t v0 = blockIdx.x * (int64_t)kBlock + threadIdx.x - lane; v0 < a.n; v0 += step) {
+        const int64_t v = v0 + lane;
+        const bool take = v < a.n && a.stamp[v] == a.sbase && a.xstamp[v] != a.sbase;
+        const bool big = take && a.out_cnt[v] > kHeavyRow;
+        const unsigned long long ml = __ballot(take && !big), mh = __ballot(big);
+        if (!(ml | mh)) continue;
+        uint32_t bl = 0, bh = 0;
+        if (lane == 0) {
+            if (ml) bl = atomicAdd(q.nout, (uint32_t)__popcll(ml));
+            if (mh) bh = atomicAdd(q.nhout, (uint32_t)__popcll(mh));
+        }
+        bl = __shfl(bl, 0);
+        bh = __shfl(bh, 0);
+        if (take && !big) q.out[bl + __popcll(ml & below)] = (int32_t)v;
+        if (big) q.hout[bh + __popcll(mh & below)] = (int32_t)v;
+    }
+}
+
+// The marks of a search that had wide levels.
+__global__ __launch_bounds__(kBlock) void k_bfs_marked(IterArgs a)
+{
+    __shared__ unsigned long long s_cnt;
+    if (threadIdx.x == 0) s_cnt = 0;
+    __syncthreads();
+    unsigned long long mine = 0;
+    for (int64_t v = blockIdx.x * (int64_t)kBlock + threadIdx.x; v < a.n; v += (int64_t)gridDim.x * kBlock)
+        mine += a.stamp[v] == a.sbase;
+    for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_xor(mine, off, kWave);
+    if (lane_id() == 0 && mine) atomicAdd(&s_cnt, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_cnt) atomicAdd(&a.ctl->affected0, s_cnt);
 }
 
 // End of a Dynamic Frontier call: copy the rows processed in this call from
@@ -1897,17 +2026,51 @@ static int traverse(dfpr_graph *g, const IterArgs &a, int64_t nd, const int32_t 
     DFPR_HIP(hipGetLastError());
     uint32_t grid = (uint32_t)g->grid;
     int chunk = 1;
-    for (int64_t L = 0; L <= (int64_t)n;) {
-        for (int j = 0; j < chunk; j++, L++)
-            k_bfs_level<<<grid, kBlock, 0, s>>>(a, bfs_queues(g, L), append ? 1 : 0);
+    bool wide = false, was_wide = false;
+    unsigned long long reach = 0;       // out-edges of the claimed vertices, at the last look
+    // every level, narrow or wide, reaches a vertex or is the last
+    for (int64_t L = 0;;) {
+        if (wide) {
+            for (int j = 0; j < 2; j++, L++) {
+                const BfsQueues q = bfs_queues(g, L);
+                k_bfs_scan<<<std::min(blocks_for(n), 2048), kBlock, 0, s>>>(a, q.hout, q.nout, q.nhout,
+                                                                          q.clear, q.hclear);
+                k_bfs_heavy<<<1024, kBlock, 0, s>>>(a, q.hout, q.nhout);
+            }
+        } else {
+            for (int j = 0; j < chunk; j++, L++)
+                k_bfs_level<<<grid, kBlock, 0, s>>>(a, bfs_queues(g, L), append ? 1 : 0);
+        }
         DFPR_HIP(hipGetLastError());
         DFPR_CHECK_RC(ctl_to_host(g));
         DFPR_HIP(hipStreamSynchronize(s));
         const Ctl &c = *g->ctl_host;
         const uint32_t next = c.qn[L % 3], nexth = c.qhn[L % 3];
         if (c.err || (next == 0 && nexth == 0)) break;
+        if (wide) {
+            if ((int64_t)next + nexth > n / 1024) continue;
+            // few are left: a narrow level costs less than a look at every vertex
+            k_bfs_collect<<<std::min(blocks_for(n), 2048), kBlock, 0, s>>>(a, bfs_queues(g, L));
+            L++;
+            wide = false;
+            grid = (uint32_t)g->grid;
+            chunk = 1;
+            continue;
+        }
+        // the levels to come are wide once a level's claims have more
+        // out-edges than a quarter of the vertices (the claims of a chunk of
+        // several levels are below that taken together)
+        wide = !append && c.reach - reach > (unsigned long long)n / 4;
+        was_wide |= wide;
+        reach = c.reach;
         grid = bfs_grid(g, next, nexth);
         chunk = std::min(chunk * 2, 16);
+    }
+    if (was_wide) {
+        // wide levels do not count what they mark
+        DFPR_CHECK_RC(launch_fill_u32(g, reinterpret_cast<uint32_t *>(&g->ctl->affected0), 2, 0));
+        k_bfs_marked<<<std::min(blocks_for(n), 1024), kBlock, 0, s>>>(a);
+        DFPR_HIP(hipGetLastError());
     }
     return DFPR_OK;
 }
