@@ -50,6 +50,32 @@ __device__ __forceinline__ void st(T *p, T v)
     else *p = v;
 }
 
+// Largest of a non-negative value over the first `LANES` lanes of a wave (16 or
+// 64), in all of them: moves between lanes in the vector unit, where shuffles
+// go through LDS at some 100 cycles a step.
+template <int CTRL>
+__device__ __forceinline__ double max_step(double x)
+{
+    const int lo = __double2loint(x), hi = __double2hiint(x);
+    return fmax(x, __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false),
+                                    __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false)));
+}
+template <int LANES>
+__device__ __forceinline__ double wave_max(double x)
+{
+    static_assert(LANES == 16 || LANES == kWave, "one row of lanes, or all four");
+    x = max_step<0x111>(x);         // row_shr 1, 2, 4, 8: the last lane of each row
+    x = max_step<0x112>(x);
+    x = max_step<0x114>(x);
+    x = max_step<0x118>(x);
+    if constexpr (LANES == kWave) {
+        x = max_step<0x142>(x);     // row_bcast 15, 31: the last lane of the wave
+        x = max_step<0x143>(x);
+    }
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), LANES - 1),
+                            __builtin_amdgcn_readlane(__double2loint(x), LANES - 1));
+}
+
 // This wave's stores and atomics so far have reached the point where
 // agent-scope loads find them.
 __device__ __forceinline__ void drain_stores()
@@ -342,9 +368,14 @@ __device__ __forceinline__ void expand_rows(const IterArgs &a, uint32_t incl, ui
 }
 
 // Finish one row: Eq. 1, Delta r, writes; returns whether it must expand.
+// The resident loop hands over the row's expansion stamp (`xs`), loaded with
+// its other data: most rows of an iteration move by more than the frontier
+// tolerance, and one dependent access less per iteration is 1-4% of a call
+// (R-MAT scale 16 1.60 against 1.67 ms an update pair).  A launch per
+// iteration, bound by its loads, looks only when the row has moved.
 template <bool DF, bool F32, bool COH>
 __device__ __forceinline__ bool finish_row(const IterArgs &a, int32_t v, uint32_t cnt, double s, double rc,
-                                  uint32_t oc, Acc &acc)
+                                  uint32_t oc, uint32_t xs, Acc &acc)
 {
     const double r = a.base_rank + a.alpha * s;
     const double dr = fabs(r - rc);
@@ -355,7 +386,7 @@ __device__ __forceinline__ bool finish_row(const IterArgs &a, int32_t v, uint32_
     acc.r_max = fmax(acc.r_max, r);
     acc.c[0] += 1;
     acc.c[1] += cnt;
-    if (DF && dr > acc.ftol && ld<COH>(a.xstamp + v) != a.sbase) {
+    if (DF && dr > acc.ftol && (COH ? xs : a.xstamp[v]) != a.sbase) {
         st<COH>(a.xstamp + v, a.sbase);
         acc.c[2] += 1;
         acc.c[3] += oc;
@@ -368,7 +399,7 @@ __device__ __forceinline__ bool finish_row(const IterArgs &a, int32_t v, uint32_
 // of Eq. 1, and whether this lane finishes it (the row's first lane).
 struct UnitRow {
     int32_t v;
-    uint32_t cnt, oc;
+    uint32_t cnt, oc, xs;
     double rc, s;
     bool mine;
 };
@@ -389,7 +420,7 @@ __device__ __forceinline__ UnitRow wave_unit(const IterArgs &a, const Hub &hub, 
     const uint32_t pos = first + lane / G;
     bool active = false;
     int32_t v = 0;
-    uint32_t beg = 0, cnt = 0, oc = 1;
+    uint32_t beg = 0, cnt = 0, oc = 1, xs = 0;
     double rc = 0.0;
     if (pos < count) {
         v = list ? ld<COH>(list + pos) : (int32_t)(id0 + pos);
@@ -404,6 +435,7 @@ __device__ __forceinline__ UnitRow wave_unit(const IterArgs &a, const Hub &hub, 
                 beg = a.in_beg[v];
                 rc = ld<COH>(a.Rc + v);
                 oc = a.out_cnt[v];
+                if (DF && COH) xs = ld<COH>(a.xstamp + v);
             }
         } else {
             // the row's start, length, rank and out-degree are loaded with
@@ -416,6 +448,7 @@ __device__ __forceinline__ UnitRow wave_unit(const IterArgs &a, const Hub &hub, 
             if (sub == 0) {
                 rc = ld<COH>(a.Rc + v);
                 oc = a.out_cnt[v];
+                if (DF && COH) xs = ld<COH>(a.xstamp + v);
             }
             if (DF && check) {
                 const uint32_t sx = ld<COH>(a.stamp + v);
@@ -450,7 +483,7 @@ __device__ __forceinline__ UnitRow wave_unit(const IterArgs &a, const Hub &hub, 
     }
 #pragma unroll
     for (int off = G / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, G);
-    return {v, cnt, oc, rc, s, active && sub == 0};
+    return {v, cnt, oc, xs, rc, s, active && sub == 0};
 }
 
 // The rest of a wave unit, once its rows are summed: the same code for every
@@ -462,7 +495,7 @@ __device__ __forceinline__ void finish_unit(const IterArgs &a, const UnitRow &ro
     const int32_t v = row.v;
     const uint32_t oc = row.oc;
     bool expand = false;
-    if (row.mine) expand = finish_row<DF, F32, COH>(a, v, row.cnt, row.s, row.rc, oc, acc);
+    if (row.mine) expand = finish_row<DF, F32, COH>(a, v, row.cnt, row.s, row.rc, oc, row.xs, acc);
     // Rows with fewer out-edges than a wave has lanes expand together, one
     // out-edge per lane and round; longer rows one at a time with the whole
     // wave and kUnroll loads in flight per lane.
@@ -560,7 +593,8 @@ __device__ __forceinline__ void block_row(const IterArgs &a, const Hub &hub, int
             double r = ((red[0] + red[1]) + red[2]) + red[3];
             if (lng)
                 for (int w = kBlock / kWave; w < kLongFolds; w++) r += red[w];
-            *flag = finish_row<DF, F32, COH>(a, v, cnt, r, ld<COH>(a.Rc + v), a.out_cnt[v], acc)
+            *flag = finish_row<DF, F32, COH>(a, v, cnt, r, ld<COH>(a.Rc + v), a.out_cnt[v],
+                                             DF && COH ? ld<COH>(a.xstamp + v) : 0u, acc)
                         ? 1 : 0;
         }
     }
@@ -733,7 +767,7 @@ __device__ __forceinline__ void make_plan_wave(const IterArgs &a, const Ctl *ctl
         p.ustart[unit ? kBins - 2 - b : kBins - 1] = unit ? before : tot;
         if (!unit) {
             p.loop_cnt = loops;
-            p.loop_id0 = ctl->cls[kBins];
+            if (!sparse) p.loop_id0 = ctl->cls[kBins];
             p.nwu = tot + (loops + kWave - 1) / kWave;
             p.nbu = cnt;
         }
