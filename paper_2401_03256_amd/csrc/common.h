@@ -27,8 +27,7 @@ constexpr int kLoopChunk = 64;         // most iteration launches between two ho
 // workgroup in one launch; larger ones take several kernels of many.
 constexpr int kSmallBatch = 1024;
 constexpr int kTickets = 16;           // counters that order the end of a grid (last_block)
-constexpr int kLoopLaunches = 8;       // most launches of the resident loop in one call
-constexpr int kHubSteps = 6;           // sizes of its LDS copy of contributions
+constexpr int kHubSteps = 6;           // sizes of the resident loop's LDS copy of contributions
 constexpr int kResBytes = 32768;       // words its workgroups exchange (ResWords)
 
 // In-degree classes.  A row of class b < 6 is reduced by a group of
@@ -91,9 +90,7 @@ struct Ctl {
     unsigned long long reach0;  // out-edges of the vertices the initial marking marked
     double ftol_used;           // frontier tolerance of the call (the adaptive rule's
                                 // choice when the parameter asks for it)
-    uint32_t loop_go[kLoopLaunches];   // resident loop: per launch of the call, 1 once every
-                                // workgroup was running, 2 if one gave up waiting first
-    uint32_t loop_ran;          //   tag of the last launch that ran
+    uint32_t loop_ran;          // resident loop: tag of the last launch that ran
     uint32_t loop_closed;       //   that launch ended the call (see Close in iter.h)
     uint32_t loop_fail;         //   a barrier timed out
     uint32_t tick[kTickets + 1];    // arrivals of a grid's workgroups (zero between launches)
@@ -208,7 +205,6 @@ struct dfpr_graph {
                                       // below 1024 << k
     int cus = 0;                      // compute units: workgroups of a resident loop at most
     uint32_t res_tag = 0;             // last barrier tag handed to a resident loop
-    int res_used = 0;                 // resident launches of the current call
     uint32_t sparse_limit = 0;        // frontier size that switches to the full schedule
 };
 

@@ -58,6 +58,7 @@
 
 #include "common.h"
 #include "iter.h"
+#include "resident.h"
 
 namespace dfpr {
 
@@ -118,415 +119,11 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(IterArgs a, int df, int
     final_body(a, df != 0, f32 != 0, sh, last != 0);
 }
 
-// ---------------------------------------------------------------------------
-// resident loop
-// ---------------------------------------------------------------------------
-// Where an iteration's rows take less time than its two launches and the
-// dispatch between them (about 20 us from one k_iter to the next on a small
-// frontier), k_resident runs the iterations of Algorithm 1's loop inside one
-// launch: one workgroup of 16 waves per compute unit at most, rows spread and
-// summed exactly as in k_iter, and a barrier between iterations that carries
-// the fold.
-//
-// What bounds it is the barrier and one chain of dependent accesses per
-// iteration.  A barrier with agent-scope release and acquire fences took
-// 9 us for 64 workgroups and 31 us for 256, because the fences write back
-// and invalidate L2; so every access to data that another workgroup writes
-// during the launch is a relaxed agent-scope one (COH, iter.h), each wave
-// waits for its own stores to be acknowledged (s_waitcnt vmcnt(0)) before
-// its workgroup arrives, and the barrier has no fence: 1.4 us for 64
-// workgroups, 1.7 us for 256.
-//
-// Arrival: a workgroup stores its Delta R (and, in the FP32 phase, its largest
-// rank) as two tagged words each.  One wave of workgroup 0 polls all of them,
-// folds them, takes the decision of final_step on a copy of the control block
-// in LDS, and publishes the state of the next iteration as eight tagged words,
-// in eight copies so that an XCD's workgroups poll one of their own.  A word
-// is 32 bits of value and a 32-bit tag that no other barrier of the graph
-// uses, so a word is its own flag and nothing is cleared between launches.
-// One wave instead of a thread per word saves the workgroup barriers around
-// the fold, and lane moves instead of shuffles most of its latency: an
-// iteration of a 10,000-vertex graph takes 9.5 us against 10.4.
-//
-// No cooperative launch: before anything is written, the workgroups wait a
-// bounded time until all of them run, and one compare-and-swap decides for
-// all whether they go or leave.  Other work on the device can so at worst
-// send a call back to the launch pairs.
-// Where it is used.  Graphs of up to kResEdges in-edges run whole calls in
-// it, because their full sweep is short next to the launches or gains from
-// the larger LDS copy: against launches, an update pair took 1.56 / 2.15 ms on
-// a 10,000-vertex G(n, m), 9.5 / 12.9 ms on R-MAT scale 20 and 15.1 / 16.8 ms
-// on scale 21 (35M edges).  On scale 22 (69M) its 16 waves per compute unit
-// and gathers past the vector L1 lose to k_iter_wide (32.9 / 30.1 ms), so
-// larger graphs use it only while a Dynamic Frontier call is on the class
-// lists.
-constexpr int64_t kResEdges = 40000000;
-// In the resident loop a row goes to a class list by an LDS-staged append, so
-// the lists may hold an eighth of the vertices before walking every id range
-// with its stamp is quicker (a 64th with launches): 1.57 against 2.35 ms on
-// uniform grid batches, no change on R-MAT.
-constexpr int32_t kResSparse = 8;
-constexpr uint32_t kLoopRows = 16384;            // DFPR_LOOP_DEVICE: most rows of an iteration
-constexpr int kResWaves = 16;
-constexpr int kResThreads = kResWaves * kWave;
-constexpr int kResMax = 256;                     // workgroups
-constexpr uint32_t kResHub = 16384;              // contributions in LDS (twice as many FP32)
-constexpr int kResSteps = 1024;                  // most iterations of one launch
-constexpr uint32_t kResTags = kResSteps + 4;     // tags a launch takes
-constexpr uint32_t kGoSpin = 256;                // polls before a launch gives up starting
-constexpr uint32_t kSpinLimit = 1u << 24;        // polls of a barrier before it reports failure
-constexpr int kResCopies = 8;                    // copies of the published state
-
-constexpr int kResCounts = kCounters + 1;        // and the marks
-
-// What the workgroups of a resident loop exchange (dfpr_graph::it.res).
-struct ResWords {
-    unsigned long long arrive[4][kResMax];           // Delta R (low, high half), largest rank
-    unsigned long long state[kResCopies * 8];        // flags, class list lengths
-    unsigned long long count[kResMax * kResCounts];  // counters of the launch, at its end
-};
-
-static_assert(sizeof(ResWords) <= kResBytes, "kResBytes holds the exchanged words");
-
-struct ResArgs {
-    double *R[2], *C[2];
-    float *C32[2];
-    ResWords *w;
-    int base;           // buffer that iteration it0 reads
-    int it0;            // first iteration of the phase (buffer parity)
-    int it_start;       // first iteration of this launch
-    int full;           // the launch keeps going on the full schedule
-    int go;             // its entry of Ctl::loop_go
-    uint32_t limit;     // class list rows of an iteration above which it hands over
-    uint32_t tag;       // first of its tags
-    int close;          // end the call too, if it converges or reaches the cap
-    double *out;        //   the ranks in the caller's order (nullable)
-    const int32_t *ext2int;
-};
-
-struct ResShared {
-    Ctl ctl;                            // workgroup 0: the control block
-    double wdr[kResWaves], wrm[kResWaves];
-    unsigned long long wc[kResWaves][kCounters];
-    uint32_t state[8];
-    uint32_t lists[8];                  // class list lengths, and whether to leave the lists
-    Stage stage;
-    int go, fail;
-};
-
-__device__ __forceinline__ unsigned long long tagged(uint32_t value, uint32_t tag)
-{
-    return ((unsigned long long)value << 32) | tag;
-}
-
-// Poll a tagged word; false if its tag did not come within kSpinLimit polls.
-__device__ __forceinline__ bool await_word(const unsigned long long *p, uint32_t tag, uint32_t &value)
-{
-    for (uint32_t n = 0; n < kSpinLimit; n++) {
-        const unsigned long long x = ld<true>(p);
-        if ((uint32_t)x == tag) {
-            value = (uint32_t)(x >> 32);
-            return true;
-        }
-    }
-    return false;
-}
-
-// The value whose halves the G workgroups of a launch store in lo[] and hi[]
-// under `tag`: the largest of those a lane of the polling wave takes.  All
-// words of a round are loaded at once.
-__device__ __forceinline__ bool await_all(const unsigned long long *lo, const unsigned long long *hi,
-                                          uint32_t G, uint32_t tag, double &most)
-{
-    constexpr int K = kResMax / kWave;
-    unsigned long long x[K], y[K];
-    for (uint32_t n = 0; n < kSpinLimit; n++) {
-        bool all = true;
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            const uint32_t w = lane_id() + k * kWave;
-            x[k] = w < G ? ld<true>(lo + w) : (unsigned long long)tag;
-            y[k] = w < G ? ld<true>(hi + w) : (unsigned long long)tag;
-        }
-#pragma unroll
-        for (int k = 0; k < K; k++) all = all && (uint32_t)x[k] == tag && (uint32_t)y[k] == tag;
-        if (all) {
-#pragma unroll
-            for (int k = 0; k < K; k++)
-                most = fmax(most, __hiloint2double((int)(y[k] >> 32), (int)(x[k] >> 32)));
-            return true;
-        }
-    }
-    return false;
-}
-
-// Whether every workgroup of the launch runs.  One compare-and-swap on the
-// launch's entry of loop_go decides it for all of them: workgroup 0 sets it
-// once all have arrived, a workgroup that has waited too long clears it.
-__device__ inline bool resident_start(const ResArgs &P, uint32_t *go, ResShared &rs)
-{
-    if (threadIdx.x == 0) {
-        rs.go = 1;
-        st<true>(&P.w->arrive[0][blockIdx.x], tagged(0u, P.tag));
-    }
-    __syncthreads();
-    if (blockIdx.x == 0) {
-        bool here = threadIdx.x >= gridDim.x;
-        for (uint32_t n = 0; n < kGoSpin && !here; n++)
-            here = (uint32_t)ld<true>(&P.w->arrive[0][threadIdx.x]) == P.tag;
-        if (!here) rs.go = 0;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const uint32_t was = atomicCAS(go, 0u, rs.go ? 1u : 2u);
-            if (was) rs.go = was == 1u;
-        }
-    } else if (threadIdx.x == 0) {
-        uint32_t x = 0;
-        for (uint32_t n = 0; n < 2 * kGoSpin && !x; n++) x = ld<true>(go);
-        if (!x) {
-            x = atomicCAS(go, 0u, 2u);
-            if (!x) x = 2u;
-        }
-        rs.go = x == 1u;
-    }
-    __syncthreads();
-    return rs.go != 0;
-}
-
 template <bool DF, bool F32>
 __global__ __launch_bounds__(kResThreads) void k_resident(IterArgs a, ResArgs P)
 {
-    __shared__ IterSharedT<kResWaves> sh;
-    __shared__ ResShared rs;
-    __shared__ double hub_lds[kResHub];
-    if (!resident_start(P, &a.ctl->loop_go[P.go], rs)) return;
-    const uint32_t G = gridDim.x, blk = blockIdx.x;
-    const int wave = threadIdx.x / kWave, lane = lane_id();
-    // the state at the launch's start: the kernels before it left it
-    bool dense = !DF || a.ctl->dense, stop = a.ctl->done || (F32 && a.ctl->phase_end);
-    if (threadIdx.x < 8)
-        rs.state[threadIdx.x] =
-            threadIdx.x ? a.ctl->snap[P.it_start & 1][threadIdx.x - 1] : 0u;
-    if (threadIdx.x == 0) {
-        rs.fail = 0;
-        // a negative frontier tolerance asks for the call's adaptive choice
-        sh.plan.ftol = a.ftol >= 0.0 ? a.ftol : a.ctl->ftol_used;
-        sh.plan.plain = a.ctl->plain_marks;
-        rs.stage.item = reinterpret_cast<uint2 *>(hub_lds);
-        rs.stage.cap = kResHub;
-    }
-    a.stage = &rs.stage;
-    if (blk == 0) {
-        constexpr int words = (int)(sizeof(Ctl) / 4);
-        for (int i = threadIdx.x; i < words; i += kResThreads)
-            reinterpret_cast<uint32_t *>(&rs.ctl)[i] = reinterpret_cast<const uint32_t *>(a.ctl)[i];
-    }
-    __syncthreads();
-    unsigned long long tot[kCounters] = {0, 0, 0, 0};
-    uint32_t tag = P.tag;
-    bool planned = false;       // the full schedule's plan does not change
-    bool over = false;          // the call has converged or reached the cap
-    int k = 0;
-    for (; k < kResSteps; k++) {
-        const int it = P.it_start + k;
-        uint32_t rows = 0;
-#pragma unroll
-        for (int b = 0; b < kBins; b++) rows += rs.state[1 + b];
-        if (stop || (dense ? !P.full : rows > P.limit)) break;     // uniform over the launch
-        const int src = P.base ^ ((it - P.it0) & 1);
-        a.it = it;
-        a.Rc = src ? P.R[1] : P.R[0];
-        a.Cc = src ? P.C[1] : P.C[0];
-        a.Rn = src ? P.R[0] : P.R[1];
-        a.Cn = src ? P.C[0] : P.C[1];
-        a.C32c = src ? P.C32[1] : P.C32[0];
-        a.C32n = src ? P.C32[0] : P.C32[1];
-        const bool sparse = DF && !dense;
-        if (wave == 0 && !(dense && planned))
-            make_plan_wave(a, a.ctl, sparse, DF, rs.state + 1, G, G * kResWaves, sh.plan);
-        planned = dense;
-        if (sparse && threadIdx.x <= kBins) (threadIdx.x ? rs.stage.cnt[threadIdx.x - 1] : rs.stage.n) = 0;
-        Hub hub{hub_lds, reinterpret_cast<const float *>(hub_lds), 0u};
-        if (!sparse && a.hub) {
-            hub.n = a.hub;
-            if (F32) {
-                float *f = reinterpret_cast<float *>(hub_lds);
-                for (uint32_t v = threadIdx.x; v < hub.n; v += kResThreads) f[v] = ld<true>(a.C32c + v);
-            } else {
-                for (uint32_t v = threadIdx.x; v < hub.n; v += kResThreads)
-                    hub_lds[v] = ld<true>(a.Cc + v);
-            }
-        }
-        __syncthreads();
-        Acc acc;
-        acc.ftol = sh.plan.ftol;
-        acc.plain = sh.plan.plain != 0;
-        iter_rows<DF, F32, kResWaves, true>(a, hub, blk, G, sh, DF && dense, sparse, acc);
-#pragma unroll
-        for (int j = 0; j < kCounters; j++) tot[j] += acc.c[j];
-        if (sparse) {
-            // the new list entries of the workgroup
-            __syncthreads();
-            const uint32_t n = min(rs.stage.n, rs.stage.cap);
-            if (n) {
-                if (threadIdx.x < kBins && rs.stage.cnt[threadIdx.x])
-                    rs.stage.base[threadIdx.x] =
-                        atomicAdd(&a.ctl->live[threadIdx.x], rs.stage.cnt[threadIdx.x]);
-                __syncthreads();
-                for (uint32_t i = threadIdx.x; i < n; i += kResThreads) {
-                    const uint2 e = rs.stage.item[i];
-                    const uint32_t c = e.y >> 28;
-                    st<true>(&a.bins[(size_t)c * a.n_stride + rs.stage.base[c] + (e.y & 0xFFFFFFFu)],
-                             (int32_t)e.x);
-                }
-            }
-        }
-        // arrive: Delta R and the largest rank of the workgroup
-        const double wdr = wave_max<kWave>(acc.dr_max);
-        const double wrm = F32 ? wave_max<kWave>(acc.r_max) : 0.0;
-        if (lane == 0) {
-            rs.wdr[wave] = wdr;
-            if (F32) rs.wrm[wave] = wrm;
-        }
-        drain_stores();
-        __syncthreads();
-        tag++;
-        if (wave == 0) {
-            const double dr = wave_max<kResWaves>(rs.wdr[lane % kResWaves]);
-            const double rm = F32 ? wave_max<kResWaves>(rs.wrm[lane % kResWaves]) : 0.0;
-            const unsigned long long bits =
-                (unsigned long long)__double_as_longlong(lane & 2 ? rm : dr);
-            if (lane < (F32 ? 4 : 2))
-                st<true>(&P.w->arrive[lane][blk],
-                         tagged((uint32_t)(lane & 1 ? bits >> 32 : bits), tag));
-        }
-        if (blk == 0) {
-            if (wave == 0) {
-                double dr = 0.0, rm = 0.0;
-                bool ok = await_all(P.w->arrive[0], P.w->arrive[1], G, tag, dr);
-                if (F32) ok = await_all(P.w->arrive[2], P.w->arrive[3], G, tag, rm) && ok;
-                if (__ballot(!ok)) rs.fail = 1;
-                if (sparse && lane <= kBins)
-                    rs.lists[lane] = lane < kBins ? ld<true>(&a.ctl->live[lane])
-                                                  : ld<true>(&a.ctl->force_dense);
-                dr = wave_max<kWave>(dr);
-                if (F32) rm = wave_max<kWave>(rm);
-                __builtin_amdgcn_wave_barrier();
-                if (lane == 0) {
-                    final_step(a, &rs.ctl, rs.lists, sparse, F32, dr, rm);
-                    const bool end = rs.fail || rs.ctl.done || (F32 && rs.ctl.phase_end);
-                    rs.state[0] = (end ? 1u : 0u) | (rs.ctl.dense ? 2u : 0u) |
-                                  (end && !rs.fail && rs.ctl.done ? 4u : 0u);
-                }
-                __builtin_amdgcn_wave_barrier();
-                if (lane < kBins) rs.state[1 + lane] = rs.ctl.snap[(it & 1) ^ 1][lane];
-                static_assert(kResCopies * 8 == kWave, "a lane per published word");
-                __builtin_amdgcn_wave_barrier();
-                st<true>(&P.w->state[lane], tagged(rs.state[lane & 7], tag));
-            }
-            __syncthreads();
-        } else {
-            if (threadIdx.x < 8) {
-                uint32_t v = 1u;
-                if (!await_word(&P.w->state[(blk & (kResCopies - 1)) * 8 + threadIdx.x], tag, v))
-                    rs.fail = 1;
-                rs.state[threadIdx.x] = v;
-            }
-            __syncthreads();
-        }
-        stop = rs.fail || (rs.state[0] & 1u);
-        dense = !DF || (rs.state[0] & 2u);
-        over = rs.state[0] & 4u;
-    }
-    unsigned long long marks = 0;
-    const bool close = !F32 && P.close && over && !rs.fail;
-    if (close) {
-        // the other buffer on the processed rows (k_finish, k_copy2), and
-        // the ranks in the caller's order
-        const int it = P.it_start + k, res = P.base ^ ((it - P.it0) & 1);
-        const double *Rr = res ? P.R[1] : P.R[0], *Cr = res ? P.C[1] : P.C[0];
-        double *Ro = res ? P.R[0] : P.R[1], *Co = res ? P.C[0] : P.C[1];
-        const uint32_t t0 = blk * kResThreads + threadIdx.x, step = G * kResThreads;
-        if (DF && !dense) {
-            uint32_t tot = 0;
-#pragma unroll
-            for (int b = 0; b < kBins; b++) tot += rs.state[1 + b];
-            for (uint32_t t = t0; t < tot; t += step) {
-                uint32_t b = 0, r = t;
-                while (r >= rs.state[1 + b]) r -= rs.state[1 + b++];
-                const int32_t v = ld<true>(&a.bins[(size_t)b * a.n_stride + r]);
-                marks++;
-                Ro[v] = ld<true>(Rr + v);
-                Co[v] = ld<true>(Cr + v);
-            }
-        } else {
-            for (uint32_t v = t0; v < (uint32_t)a.n; v += step) {
-                if (DF) {
-                    const uint32_t sx = ld<true>(a.stamp + v);
-                    if (sx < a.sbase || sx > a.sbase + (uint32_t)it) continue;
-                    marks++;
-                }
-                Ro[v] = ld<true>(Rr + v);
-                Co[v] = ld<true>(Cr + v);
-            }
-        }
-        if (P.out)
-            for (uint32_t v = t0; v < (uint32_t)a.n; v += step) P.out[v] = ld<true>(Rr + P.ext2int[v]);
-    }
-    // counters of the launch, and the control block back to memory and host
-    double d0 = 0.0, d1 = 0.0;
-    block_fold<kResWaves>(d0, d1, tot, rs.wdr, rs.wrm, rs.wc);
-    unsigned long long mk[kCounters] = {marks, 0, 0, 0};
-    if (DF) block_fold<kResWaves>(d0, d1, mk, rs.wdr, rs.wrm, rs.wc);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int j = 0; j < kCounters; j++) st<true>(&P.w->count[blk * kResCounts + j], tot[j]);
-        st<true>(&P.w->count[blk * kResCounts + kCounters], mk[0]);
-        drain_stores();
-        st<true>(&P.w->arrive[0][blk], tagged(0u, P.tag + kResSteps + 1));
-    }
-    if (blk) return;
-    uint32_t v = 0;
-    if (threadIdx.x < G && !await_word(&P.w->arrive[0][threadIdx.x], P.tag + kResSteps + 1, v))
-        rs.fail = 1;
-#pragma unroll
-    for (int j = 0; j < kCounters; j++)
-        tot[j] = threadIdx.x < G ? ld<true>(&P.w->count[threadIdx.x * kResCounts + j]) : 0ull;
-    block_fold<kResWaves>(d0, d1, tot, rs.wdr, rs.wrm, rs.wc);
-    if (DF) {
-        mk[0] = threadIdx.x < G ? ld<true>(&P.w->count[threadIdx.x * kResCounts + kCounters]) : 0ull;
-        mk[1] = mk[2] = mk[3] = 0;
-        block_fold<kResWaves>(d0, d1, mk, rs.wdr, rs.wrm, rs.wc);
-    }
-    if (threadIdx.x == 0) {
-        Ctl *c = a.ctl;
-        const Ctl &s = rs.ctl;
-        c->verts = s.verts + tot[0];
-        c->edges = s.edges + tot[1];
-        c->xverts = s.xverts + tot[2];
-        c->xedges = s.xedges + tot[3];
-        c->marked = s.marked;
-        c->affected = s.affected + mk[0];
-        c->loop_closed = close && !rs.fail;
-        c->iterations = s.iterations;
-        c->final_linf = s.final_linf;
-        c->final_rmax = s.final_rmax;
-        c->prev_linf = s.prev_linf;
-        c->phase_iters = s.phase_iters;
-        c->phase_end = s.phase_end;
-        c->converged = s.converged;
-        c->dense = s.dense;
-        c->done = rs.fail ? 1u : s.done;
-        c->loop_fail = (uint32_t)rs.fail;
-        c->loop_ran = P.tag;
-        for (int b = 0; b < kBins; b++) {
-            c->snap[0][b] = s.snap[0][b];
-            c->snap[1][b] = s.snap[1][b];
-        }
-        drain_stores();
-    }
-    __syncthreads();
-    if (threadIdx.x < kWave) ctl_to_mirror(a.ctl, a.mirror);
+    __shared__ ResLds lds;
+    resident_body<DF, F32>(a, P, blockIdx.x, gridDim.x, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -560,7 +157,6 @@ __device__ inline void reset_ctl(Ctl *ctl)
         ctl->mk_light = ctl->mk_heavy = 0;
         ctl->reach = 0;
         for (int k = 0; k < 3; k++) ctl->qn[k] = ctl->qhn[k] = 0;
-        for (int k = 0; k < kLoopLaunches; k++) ctl->loop_go[k] = 0;
         ctl->loop_fail = 0;
         ctl->loop_closed = 0;
         ctl->reach0 = 0;
@@ -1449,7 +1045,7 @@ static uint32_t sparse_grid(const dfpr_graph *g, const Ctl &c)
 // Workgroups of a resident launch whose iterations walk the full schedule:
 // enough waves for its wave units and enough sub-blocks for its long rows,
 // one workgroup per compute unit at most.
-static uint32_t resident_grid(const dfpr_graph *g)
+uint32_t resident_grid(const dfpr_graph *g)
 {
     const uint32_t *c = g->cls;
     uint64_t nwu = ((uint64_t)(c[kBins + 1] - c[kBins]) + kWave - 1) / kWave;
@@ -1468,7 +1064,7 @@ static uint32_t resident_grid(const dfpr_graph *g)
 // gathers that the first entries take is known from the load.  On R-MAT scale
 // 18 that is all kResHub entries (4.1 us for 60% of 18 us of gathers), on a
 // uniform graph or one of 10,000 vertices none.
-static uint32_t resident_hub(const dfpr_graph *g, bool f32, uint32_t G)
+uint32_t resident_hub(const dfpr_graph *g, bool f32, uint32_t G)
 {
     const double gathers = 1.1e-3 * (double)g->m / G - 2.0;     // us per workgroup
     double best = 0.0;
@@ -1485,22 +1081,23 @@ static uint32_t resident_hub(const dfpr_graph *g, bool f32, uint32_t G)
     return hub;
 }
 
-// One launch of the resident loop from iteration `it` of the phase that
-// started at it0 on buffer `base`.  *ran: the workgroups were all running
-// and the control block's host copy is the state it left; otherwise nothing
-// was changed.
-static int launch_resident(dfpr_graph *g, IterArgs a, bool df, bool f32, int it0, int it, int base,
-                           bool full, uint32_t limit, Close *close, bool *ran)
+// Entries the class lists may hold in the resident loop.
+uint32_t resident_lists(const dfpr_graph *g)
 {
-    *ran = false;
-    if (!g->it.res || g->res_used >= kLoopLaunches) return DFPR_OK;
+    return std::max<uint32_t>(g->sparse_limit, (uint32_t)(g->n / kResSparse));
+}
+
+// Arguments of a resident launch from iteration `it` of the phase that started
+// at it0 on buffer `base`, with tags of its own.
+int resident_args(dfpr_graph *g, int it0, int it, int base, bool full, uint32_t limit, ResArgs &P)
+{
     if (g->res_tag > 0xFFFFFFFFu - 2 * kResTags) {
         // the tags start over: the words of earlier launches must not match
         DFPR_CHECK_RC(launch_fill_u32(g, reinterpret_cast<uint32_t *>(g->it.res),
                                       sizeof(ResWords) / 4, 0));
         g->res_tag = 0;
     }
-    ResArgs P{};
+    P = ResArgs{};
     for (int b = 0; b < 2; b++) {
         P.R[b] = g->R[b];
         P.C[b] = g->C[b];
@@ -1512,16 +1109,28 @@ static int launch_resident(dfpr_graph *g, IterArgs a, bool df, bool f32, int it0
     P.it_start = it;
     P.full = full ? 1 : 0;
     P.limit = limit;
-    P.go = g->res_used++;
     P.tag = g->res_tag + 1;
-    P.close = close ? 1 : 0;
-    P.out = close ? close->out : nullptr;
     P.ext2int = g->ext2int;
     g->res_tag += kResTags;
+    return DFPR_OK;
+}
+
+// One launch of the resident loop from iteration `it` of the phase that
+// started at it0 on buffer `base`.  *ran: the workgroups were all running
+// and the control block's host copy is the state it left; otherwise nothing
+// was changed.
+static int launch_resident(dfpr_graph *g, IterArgs a, bool df, bool f32, int it0, int it, int base,
+                           bool full, uint32_t limit, Close *close, bool *ran)
+{
+    *ran = false;
+    ResArgs P;
+    DFPR_CHECK_RC(resident_args(g, it0, it, base, full, limit, P));
+    P.close = close ? 1 : 0;
+    P.out = close ? close->out : nullptr;
     a.mirror = g->ctl_host;
     const uint32_t G = full ? resident_grid(g) : (uint32_t)g->cus;
     a.hub = full && a.hub ? resident_hub(g, f32, G) : 0u;
-    a.sparse_limit = std::max<uint32_t>(a.sparse_limit, g->n / kResSparse);
+    a.sparse_limit = resident_lists(g);
     if (!df) k_resident<false, false><<<G, kResThreads, 0, g->stream>>>(a, P);
     else if (f32) k_resident<true, true><<<G, kResThreads, 0, g->stream>>>(a, P);
     else k_resident<true, false><<<G, kResThreads, 0, g->stream>>>(a, P);
@@ -1776,7 +1385,6 @@ static int launch_begin(dfpr_graph *g, const IterArgs &a, BeginArgs b, const dou
     DFPR_HIP(hipGetLastError());
     g->refine_sweeps = 0;
     g->loop_iters = 0;
-    g->res_used = 0;
     std::memset(g->prof_base, 0, sizeof(g->prof_base));
     return DFPR_OK;
 }

@@ -21,7 +21,11 @@
 // workgroups sized for its graph, so small updates progress beside a large
 // one instead of waiting for it.  While a large request runs, a small-lane
 // step takes at most kSmallLaneBlocks workgroups.  FP64 slots and slots in
-// the FP32 phase of the precision form share a launch.  Chunk lengths
+// the FP32 phase of the precision form share a launch.  While no large
+// request runs, a small-lane chunk is one launch of the resident loop instead
+// (k_resident_multi): each slot has compute units of its own, in proportion to
+// its graph, and iterates at its own pace until its request is over, another's
+// is, or a time limit passes.  Chunk lengths
 // follow the observed geometric decay of Delta R of the slots (so a slot is
 // retired soon after it converges); small-lane chunks are kept short while
 // requests wait for a slot, because requests join and leave at chunk
@@ -38,6 +42,7 @@
 
 #include "common.h"
 #include "iter.h"
+#include "resident.h"
 #include "serve_policy.h"
 
 namespace dfpr {
@@ -54,6 +59,12 @@ constexpr int kDepth = 2;                      // chunks a lane may have in flig
 #define DFPR_SMALL_LANE_BLOCKS 512
 #endif
 constexpr uint32_t kSmallLaneBlocks = DFPR_SMALL_LANE_BLOCKS;
+// Compute units a resident chunk leaves to admissions (32 were no better, 64
+// 10% slower), and its time limits in
+// us: while a request could be admitted beside it (an admission takes about
+// 150 us of mostly host time), while requests are still to arrive, otherwise.
+constexpr uint32_t kFreeUnits = 16;
+constexpr uint32_t kBudgetAdmit = 250, kBudgetArrivals = 1000, kBudgetMost = 5000;
 
 struct MultiArgs {
     int32_t nslots;
@@ -94,6 +105,31 @@ __global__ __launch_bounds__(kFinalThreads) void k_final_multi(MultiArgs m)
     const IterArgs &a = m.s[s];
     const bool f32 = (m.f32_mask >> s) & 1u;
     final_body(a, true, f32, sh, false);
+}
+
+// Several graphs' resident loops side by side.  Bound: the slowest slot, so
+// compute units follow the graphs' edges; a step of all slots in k_iter_multi
+// took as long as the largest graph's iteration on the whole device (73 us for
+// two R-MAT graphs of 262144 vertices and four smaller ones) and every slot
+// waited for it.  24 requests on those graphs: 15.5 against 26.3 ms.
+struct ResMultiArgs {
+    int32_t nslots;
+    uint32_t f32_mask;
+    uint32_t off[kMaxSlots + 1];
+    IterArgs s[kMaxSlots];
+    ResArgs r[kMaxSlots];
+};
+static_assert(sizeof(ResMultiArgs) <= 4096, "kernel arguments must fit in 4 KiB");
+
+__global__ __launch_bounds__(kResThreads) void k_resident_multi(ResMultiArgs m)
+{
+    __shared__ ResLds lds;
+    const uint32_t b = blockIdx.x;
+    int s = 0;
+    while (s + 1 < m.nslots && b >= m.off[s + 1]) s++;
+    const uint32_t G = m.off[s + 1] - m.off[s];
+    if ((m.f32_mask >> s) & 1u) resident_body<true, true>(m.s[s], m.r[s], b - m.off[s], G, lds);
+    else resident_body<true, false>(m.s[s], m.r[s], b - m.off[s], G, lds);
 }
 
 // Copy the control blocks of the slots into one array for one host copy.
@@ -148,6 +184,7 @@ struct Slot {
     double prev_dr = -1.0;    // Delta R and iteration count at the last look
     int prev_it = 0;
     int pred = 4;             // predicted iterations left in the phase
+    uint32_t tag = 0;         // of its resident launch
 };
 
 struct GraphEntry {
@@ -194,6 +231,8 @@ struct dfpr_server {
     hipEvent_t done[dfpr::kLanes][dfpr::kDepth] = {};
     dfpr::Ctl *ctl_dev[dfpr::kLanes][dfpr::kDepth] = {};
     dfpr::Ctl *ctl_pin[dfpr::kLanes][dfpr::kDepth] = {};
+    uint32_t *stop = nullptr;                // resident chunks: the last one that a slot ended
+    uint32_t stop_tag = 0;
 };
 
 using namespace dfpr;
@@ -300,6 +339,58 @@ static int launch_chunk(dfpr_server *srv, int lane, int buf, std::vector<Slot *>
     return DFPR_OK;
 }
 
+// One resident chunk of the slots: compute units in proportion to the graphs'
+// edges, the control blocks straight to the lane's pinned buffer.
+static int launch_resident_chunk(dfpr_server *srv, int lane, int buf, std::vector<Slot *> &cs,
+                                 uint32_t budget_us)
+{
+    hipStream_t stream = srv->stream[lane];
+    ResMultiArgs m{};
+    m.nslots = (int32_t)cs.size();
+    if (++srv->stop_tag == 0) srv->stop_tag = 1;
+    double weight = 0.0;
+    uint32_t units = 256;
+    auto weight_of = [&](const Slot *sl) {
+        return (double)srv->graphs[srv->reqs[sl->req].gid].g->m + 2e5;
+    };
+    for (const Slot *sl : cs) {
+        weight += weight_of(sl);
+        units = std::min(units, (uint32_t)srv->graphs[srv->reqs[sl->req].gid].g->cus);
+    }
+    units = std::max(units, kFreeUnits + (uint32_t)kMaxSlots) - kFreeUnits;
+    const uint32_t spread = units - (uint32_t)cs.size();     // one each first
+    uint32_t at = 0;
+    for (int i = 0; i < m.nslots; i++) {
+        Slot &sl = *cs[i];
+        GraphEntry &ge = srv->graphs[srv->reqs[sl.req].gid];
+        dfpr_graph *g = ge.g;
+        const uint32_t share = 1 + (uint32_t)(spread * (weight_of(&sl) / weight));
+        const uint32_t G = std::min(resident_grid(g), share);
+        m.off[i] = at;
+        at += G;
+        IterArgs a = iter_args(g, ge.p, sl.sbase);
+        a.mirror = srv->ctl_pin[lane][buf] + i;
+        a.hub = resident_hub(g, sl.phase32 != 0, G);
+        a.sparse_limit = resident_lists(g);
+        ResArgs P;
+        DFPR_CHECK_RC(resident_args(g, sl.it0, sl.itq, sl.base, true, 0xFFFFFFFFu, P));
+        P.close = sl.phase32 ? 0 : 1;
+        P.budget = budget_us * 100;
+        P.stop = srv->stop;
+        P.stop_tag = srv->stop_tag;
+        m.s[i] = a;
+        m.r[i] = P;
+        if (sl.phase32) m.f32_mask |= 1u << i;
+        sl.tag = P.tag;
+        srv->ctl_pin[lane][buf][i].loop_ran = 0;
+    }
+    m.off[m.nslots] = at;
+    k_resident_multi<<<at, kResThreads, 0, stream>>>(m);
+    DFPR_HIP(hipGetLastError());
+    DFPR_HIP(hipEventRecord(srv->done[lane][buf], stream));
+    return DFPR_OK;
+}
+
 // Predicted iterations left in a slot's phase, from the geometric decay of
 // Delta R between two looks.
 static void predict(Slot &sl, const Ctl &c, double tol)
@@ -322,7 +413,7 @@ static void predict(Slot &sl, const Ctl &c, double tol)
 struct Chunk {
     std::vector<Slot *> cs;
     std::vector<uint32_t> epoch;
-    int K = 0;
+    int K = 0;                    // 0: a resident chunk
     int buf = 0;
     Clock::time_point t;
 };
@@ -376,12 +467,15 @@ static int run(dfpr_server *srv, dfpr_server_stats *st)
         for (int i = 0; i < srv->max_slots; i++) k += slots[i].req >= 0 && slot_lane[i] == lane;
         return k;
     };
+    bool resident_ok = true;      // the last resident chunk's workgroups all ran
+    uint32_t budget_us = kBudgetMost;
     auto launch = [&](int lane, std::vector<Slot *> &cs, int K) -> int {
         LaneState &L = lanes[lane];
         const int buf = L.free_buf();
         // small steps leave most of the GPU to a large request
         const uint32_t cap = lane == 1 && active_in(0) > 0 ? kSmallLaneBlocks : 0u;
-        const int lrc = launch_chunk(srv, lane, buf, cs, K, cap);
+        const int lrc = K ? launch_chunk(srv, lane, buf, cs, K, cap)
+                          : launch_resident_chunk(srv, lane, buf, cs, budget_us);
         if (lrc) return lrc;
         Chunk &c = L.q[buf];
         c.cs = cs;
@@ -393,6 +487,19 @@ static int run(dfpr_server *srv, dfpr_server_stats *st)
         L.n++;
         steps += K;
         return DFPR_OK;
+    };
+    auto view = [&](int64_t r) {
+        const Request &q = srv->reqs[r];
+        return PendingView{q.arrival_ms, q.state, q.gid, q.charge};
+    };
+    auto blocked = [&](int32_t gid) {
+        const GraphEntry &ge = srv->graphs[gid];
+        return ge.busy != 0 || (ge.lane == 0 && active_in(0) > 0);
+    };
+    // whether step 2 below would admit a request now
+    auto admissible = [&]() {
+        return next_admission(order, next, ms_since(t0), true, view, blocked,
+                              srv->resident + in_flight, srv->budget) >= 0;
     };
     while (done + failed < pending) {
         // 1. chunks for the lanes with admitted requests
@@ -407,7 +514,13 @@ static int run(dfpr_server *srv, dfpr_server_stats *st)
             for (int i = 0; i < srv->max_slots; i++)
                 if (slots[i].req >= 0 && slot_lane[i] == lane) cs.push_back(&slots[i]);
             if (cs.empty()) continue;
+            if (L.n == 0 && lane == 1 && active_in(0) == 0 && resident_ok) {
+                budget_us = !waiting ? kBudgetMost : admissible() ? kBudgetAdmit : kBudgetArrivals;
+                rc = launch(lane, cs, 0);
+                if (rc) goto out;
+            }
             if (L.n == 0) {
+                if (lane == 1) resident_ok = true;
                 int K = kMaxChunk;
                 for (Slot *s : cs) K = std::min(K, s->pred);
                 // requests join the small lane at chunk boundaries: keep its
@@ -432,14 +545,6 @@ static int run(dfpr_server *srv, dfpr_server_stats *st)
         {
             int admitted = 0;
             double now = ms_since(t0);
-            auto view = [&](int64_t r) {
-                const Request &q = srv->reqs[r];
-                return PendingView{q.arrival_ms, q.state, q.gid, q.charge};
-            };
-            auto blocked = [&](int32_t gid) {
-                const GraphEntry &ge = srv->graphs[gid];
-                return ge.busy != 0 || (ge.lane == 0 && active_in(0) > 0);
-            };
             for (size_t from = next;;) {
                 auto free_slot = std::find_if(slots.begin(), slots.end(),
                                               [](const Slot &s) { return s.req < 0; });
@@ -470,6 +575,8 @@ static int run(dfpr_server *srv, dfpr_server_stats *st)
                 } else {
                     free_slot->epoch = ++epochs;
                     admitted++;
+                    // an idle lane starts at once; later admissions overlap it
+                    if (lanes[slot_lane[si]].n == 0) break;
                 }
                 now = ms_since(t0);
             }
@@ -524,7 +631,7 @@ static int run(dfpr_server *srv, dfpr_server_stats *st)
             Chunk ch = L.oldest();
             L.head = (L.head + 1) % kDepth;
             L.n--;
-            if (lane == 1) {
+            if (lane == 1 && ch.K) {
                 const double chunk_ms =
                     std::chrono::duration<double, std::milli>(Clock::now() - ch.t).count();
                 const double per = chunk_ms / ch.K;
@@ -532,7 +639,8 @@ static int run(dfpr_server *srv, dfpr_server_stats *st)
             }
             const Ctl *pin = srv->ctl_pin[lane][ch.buf];
             std::vector<Slot *> fin;
-            std::vector<Ctl> fin_ctl;
+            int most = 0;             // iterations of a resident chunk's longest slot
+            bool open = false;        // a finished slot was not ended by its launch
             for (size_t i = 0; i < ch.cs.size(); i++) {
                 Slot &s = *ch.cs[i];
                 // a slot retired or moved to its next phase by an earlier
@@ -542,6 +650,20 @@ static int run(dfpr_server *srv, dfpr_server_stats *st)
                 GraphEntry &ge = srv->graphs[q.gid];
                 dfpr_graph *g = ge.g;
                 const Ctl c = pin[i];
+                if (!ch.K) {
+                    // a slot whose workgroups did not all run is as it was;
+                    // the next chunk takes a launch per iteration
+                    if (c.loop_ran != s.tag) {
+                        resident_ok = false;
+                        continue;
+                    }
+                    if (c.loop_fail) {
+                        rc = set_error(DFPR_E_DEVICE, "resident loop: a barrier timed out");
+                        goto out;
+                    }
+                    most = std::max(most, c.iterations - s.itq);
+                    s.itq = c.iterations;
+                }
                 *g->ctl_host = c;
                 s.it = c.iterations;
                 const int res = s.base ^ ((c.iterations - s.it0) & 1);
@@ -566,38 +688,45 @@ static int run(dfpr_server *srv, dfpr_server_stats *st)
                     }
                 }
                 if (c.done) {
-                    rc = df_finish(g, s.sbase, res, c.iterations);
+                    const bool closed = !ch.K && c.loop_closed;
+                    open |= !closed;
+                    rc = df_finish(g, s.sbase, res, c.iterations, closed);
                     if (rc) goto out;
                     fin.push_back(&s);
                     continue;
                 }
                 predict(s, c, ge.p.tol);
             }
+            steps += most;
             if (!fin.empty()) {
                 // the lane's later chunk, if any, only has steps of finished
                 // slots that return at once (the large lane holds one slot),
                 // so waiting for the stream is short
-                CtlGather cg{};
-                cg.n = (int32_t)fin.size();
-                for (size_t i = 0; i < fin.size(); i++)
-                    cg.src[i] = srv->graphs[srv->reqs[fin[i]->req].gid].g->ctl;
-                cg.dst = srv->ctl_dev[lane][ch.buf];
-                k_gather_ctl<<<1, kBlock, 0, srv->stream[lane]>>>(cg);
-                if (hipGetLastError() != hipSuccess ||
-                    hipMemcpyAsync(srv->ctl_pin[lane][ch.buf], srv->ctl_dev[lane][ch.buf],
-                                   fin.size() * sizeof(Ctl), hipMemcpyDeviceToHost,
-                                   srv->stream[lane]) != hipSuccess ||
-                    hipStreamSynchronize(srv->stream[lane]) != hipSuccess) {
-                    rc = set_error(DFPR_E_DEVICE, "finishing failed on the device");
-                    goto out;
+                if (open) {
+                    CtlGather cg{};
+                    cg.n = (int32_t)fin.size();
+                    for (size_t i = 0; i < fin.size(); i++)
+                        cg.src[i] = srv->graphs[srv->reqs[fin[i]->req].gid].g->ctl;
+                    cg.dst = srv->ctl_dev[lane][ch.buf];
+                    k_gather_ctl<<<1, kBlock, 0, srv->stream[lane]>>>(cg);
+                    if (hipGetLastError() != hipSuccess ||
+                        hipMemcpyAsync(srv->ctl_pin[lane][ch.buf], srv->ctl_dev[lane][ch.buf],
+                                       fin.size() * sizeof(Ctl), hipMemcpyDeviceToHost,
+                                       srv->stream[lane]) != hipSuccess ||
+                        hipStreamSynchronize(srv->stream[lane]) != hipSuccess) {
+                        rc = set_error(DFPR_E_DEVICE, "finishing failed on the device");
+                        goto out;
+                    }
                 }
                 const double t = ms_since(t0);
                 for (size_t i = 0; i < fin.size(); i++) {
                     Slot &s = *fin[i];
                     Request &q = srv->reqs[s.req];
                     GraphEntry &ge = srv->graphs[q.gid];
-                    const Ctl &c = srv->ctl_pin[lane][ch.buf][i];
-                    *ge.g->ctl_host = c;
+                    // the control block of a request ended by its launch came
+                    // with the chunk
+                    if (open) *ge.g->ctl_host = srv->ctl_pin[lane][ch.buf][i];
+                    const Ctl &c = *ge.g->ctl_host;
                     q.state = 2;
                     q.res.done_ms = t;
                     if (q.res.status == DFPR_OK) {
@@ -684,9 +813,12 @@ int dfpr_server_create(int32_t max_slots, int64_t hbm_budget_bytes, dfpr_server 
             if (e == hipSuccess)
                 e = hipEventCreateWithFlags(&s->done[l][b], hipEventDisableTiming);
             if (e == hipSuccess) e = hipMalloc(&s->ctl_dev[l][b], kMaxSlots * sizeof(Ctl));
-            if (e == hipSuccess) e = hipHostMalloc(&s->ctl_pin[l][b], kMaxSlots * sizeof(Ctl));
+            if (e == hipSuccess)
+                e = hipHostMalloc(&s->ctl_pin[l][b], kMaxSlots * sizeof(Ctl), hipHostMallocCoherent);
         }
     }
+    if (e == hipSuccess) e = hipMalloc(&s->stop, 256);
+    if (e == hipSuccess) e = hipMemset(s->stop, 0, 256);
     if (e != hipSuccess) {
         dfpr_server_free(s);
         return hip_fail(e, "server set-up");
@@ -709,6 +841,7 @@ void dfpr_server_free(dfpr_server *s)
             (void)hipFree(s->ctl_dev[l][b]);
             (void)hipHostFree(s->ctl_pin[l][b]);
         }
+    (void)hipFree(s->stop);
     delete s;
 }
 
