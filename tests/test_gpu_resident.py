@@ -84,6 +84,28 @@ def test_resident_loop_bitwise_equal_to_launches(dfpr, name):
     assert h.profile().launches > 0 and g.profile().launches == 0
 
 
+@pytest.mark.parametrize("changes", [60, 600, 6000])
+def test_first_frontiers_around_the_list_limits(dfpr, changes):
+    """Out-edges of the first frontier below 1/64 of the vertices, between 1/64
+    and 1/8 and above: appended, appended and marked in place."""
+    n, src, dst = synth.grid2d(500, seed=9)
+    g, h = dfpr.Graph(n, src, dst), dfpr.Graph(n, src, dst)
+    h.profile_reset(True)
+    R, _ = g.static()
+    bt = synth.random_batch(src, dst, n, changes // 4, changes, seed=50)
+    assert g.apply_batch(bt) == h.apply_batch(bt)
+    for prec in (dfpr.FP64, dfpr.FP32_KAHAN):
+        p = dfpr.params(frontier_tol=1e-9, precision=prec)
+        _same(f"{changes} {prec}", g.dynamic_frontier(bt, R, p), h.dynamic_frontier(bt, R, p))
+        assert np.array_equal(g.affected(), h.affected())
+    o = oracle.OracleGraph(n, src, dst)
+    o.apply_batch(bt)
+    Ro, _ = o.static()
+    Rd, _ = g.dynamic_frontier(bt, R)
+    # both within tol 1e-10 of the fixed point, damping 0.85: 2 tol / (1 - 0.85)
+    assert np.abs(Rd - Ro).max() <= 2e-9
+
+
 def test_resident_loop_calls_from_two_threads(dfpr):
     """Two graphs updated at once: each call's workgroups may find the other's
     running; results stay those of calls one at a time."""
