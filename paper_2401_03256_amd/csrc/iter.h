@@ -648,7 +648,7 @@ __device__ __forceinline__ void block_fold(double &dr, double &rm, unsigned long
 // of classes 5..0 and then of the self-loop-only rows (their own id
 // range; class lists hold them in class 0), in that order; block units are
 // the class-6 rows.
-constexpr uint32_t kSkips = 8;
+constexpr uint32_t kSkips = 16;
 struct Plan {
     double ftol;                // frontier tolerance in effect
     uint32_t plain;             // Ctl::plain_marks
@@ -719,10 +719,12 @@ __device__ __forceinline__ int lg_rows(int b)
 // b of G has long rows b, b + G, ..., and four of the others at a time, so the
 // first ones are busy longest.  A long row takes about as long as
 // 1 + in-edges / 16384 rounds of wave units (R-MAT scales 16 and 18), four of
-// the others one; a workgroup sits out as many rounds as its rows take beyond
-// those of the last workgroup.
+// the others one.  In FP32 every row takes 256 threads, four rows at a time of
+// which the first is the longest, and 1 + in-edges / 4096 rounds.  A workgroup
+// sits out as many rounds as its rows take beyond those of the last workgroup.
 __device__ __forceinline__ void make_plan_wave(const IterArgs &a, const Ctl *ctl, bool sparse, bool df,
-                                               const uint32_t *snap, uint32_t G, uint32_t waves, Plan &p)
+                                               bool f32, const uint32_t *snap, uint32_t G, uint32_t waves,
+                                               Plan &p)
 {
     const int lane = lane_id();
     const int b = lane < kBins ? lane : kBins - 1;
@@ -783,6 +785,10 @@ __device__ __forceinline__ void make_plan_wave(const IterArgs &a, const Ctl *ctl
         }
         auto rounds = [&](uint32_t w) {
             uint32_t c = 0;
+            if (f32) {
+                for (uint32_t u = w; u < nbu; u += 4 * G) c += 1 + (a.in_cnt[first + u] >> 12);
+                return c;
+            }
             for (uint32_t u = w; u < nlong; u += G) c += 1 + (a.in_cnt[first + u] >> 14);
             for (uint32_t u = nlong + (w + G - nlong % G) % G * 4; u < nbu; u += 4 * G) c++;
             return c;
@@ -872,13 +878,14 @@ __device__ __forceinline__ void iter_rows(const IterArgs &a, const Hub &hub, uin
         }
     };
     const int32_t *blist = sh.plan.list[kBins - 1];
-    // sub-blocks of T threads take rows from u0 on, one each, up to n
-    auto block_rows = [&](auto threads, uint32_t u0, uint32_t n) {
+    // sub-blocks of T threads take rows from u0 on, one each and `apart` ids
+    // from each other, up to n
+    auto block_rows = [&](auto threads, uint32_t u0, uint32_t n, uint32_t apart = 1) {
         constexpr int T = decltype(threads)::value;
         constexpr uint32_t S = NW * kWave / T;
         const uint32_t sub = threadIdx.x / T;
         for (; u0 < n; u0 += G * S) {
-            const uint32_t u = u0 + sub;
+            const uint32_t u = u0 + sub * apart;
             const bool valid = u < n;
             const int32_t v = !valid ? 0 : blist ? ld<COH>(blist + u)
                                                  : (int32_t)(sh.plan.id0[kBins - 1] + u);
@@ -893,6 +900,12 @@ __device__ __forceinline__ void iter_rows(const IterArgs &a, const Hub &hub, uin
         const uint32_t nlong = sh.plan.nlong;
         block_rows(std::integral_constant<int, kLongParts>(), blk, nlong);
         block_rows(quarter, nlong + (blk + G - nlong % G) % G * (NW * kWave / kBlock), nbu);
+    } else if constexpr (COH) {
+        // The longest rows in workgroups of their own, which then sit out
+        // units (make_plan_wave): with four rows in a row each, workgroup 0
+        // was busy 113 us of an iteration and the others 85 (R-MAT, 1.5e6
+        // vertices; the call 12.27 -> 10.63 ms).
+        block_rows(quarter, blk, nbu, G);
     } else {
         block_rows(quarter, blk * (NW * kWave / kBlock), nbu);
     }

@@ -244,7 +244,7 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
         a.C32n = src ? P.C32[0] : P.C32[1];
         const bool sparse = DF && !dense;
         if (wave == 0 && !(dense && planned))
-            make_plan_wave(a, a.ctl, sparse, DF, rs.state + 1, G, G * kResWaves, sh.plan);
+            make_plan_wave(a, a.ctl, sparse, DF, F32, rs.state + 1, G, G * kResWaves, sh.plan);
         planned = dense;
         if (sparse && threadIdx.x <= kBins) (threadIdx.x ? rs.stage.cnt[threadIdx.x - 1] : rs.stage.n) = 0;
         Hub hub{hub_lds, reinterpret_cast<const float *>(hub_lds), 0u};

@@ -106,6 +106,29 @@ def test_first_frontiers_around_the_list_limits(dfpr, changes):
     assert np.abs(Rd - Ro).max() <= 2e-9
 
 
+@pytest.mark.parametrize("rows", [255, 1023, 1500])
+def test_fp32_block_rows_over_the_workgroups(dfpr, rows):
+    """More rows of many in-edges than workgroups, and than one round of them."""
+    n = 20_000
+    rng = np.random.default_rng(rows)
+    deg = np.linspace(6000, 600, rows).astype(np.int64)
+    dst = np.repeat(np.arange(rows, dtype=np.int32), deg)
+    src = rng.integers(0, n, dst.size).astype(np.int32)
+    back = np.arange(n, dtype=np.int32)
+    src = np.concatenate([src, (back % rows).astype(np.int32)])
+    dst = np.concatenate([dst, back])
+    e = np.unique(src.astype(np.int64) * n + dst)
+    e = e[e // n != e % n]
+    src, dst = (e // n).astype(np.int32), (e % n).astype(np.int32)
+    g, h = dfpr.Graph(n, src, dst), dfpr.Graph(n, src, dst)
+    h.profile_reset(True)
+    R = np.full(n, 1.0 / n)
+    bt = synth.random_batch(src, dst, n, 10, 200, seed=60)
+    assert g.apply_batch(bt) == h.apply_batch(bt)
+    p = dfpr.params(precision=dfpr.FP32_KAHAN)
+    _same(f"{rows}", g.dynamic_frontier(bt, R, p), h.dynamic_frontier(bt, R, p))
+
+
 def test_resident_loop_calls_from_two_threads(dfpr):
     """Two graphs updated at once: each call's workgroups may find the other's
     running; results stay those of calls one at a time."""
