@@ -50,6 +50,17 @@ __device__ __forceinline__ void st(T *p, T v)
     else *p = v;
 }
 
+// x, as a value that nothing computed from it before can be reused for.  The
+// compiler otherwise computes the addresses of the resident loop once before
+// the iterations, keeps them in scratch memory (104 bytes a lane) and loads
+// them back in each: R-MAT scale 13 1093 against 1058 us a call, 300 x 300 grid
+// 834 against 806 us.
+__device__ __forceinline__ uint32_t fresh(uint32_t x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // Largest of a non-negative value over the first `LANES` lanes of a wave (16 or
 // 64), in all of them: moves between lanes in the vector unit, where shuffles
 // go through LDS at some 100 cycles a step.
@@ -186,6 +197,35 @@ struct Acc {
     bool plain = false;         // expansions mark with plain stores (Ctl::plain_marks)
 };
 
+// The contributions of the sources in i (-1: none), those below n_hub from the
+// LDS copy and the others from memory.  The resident loop reads LDS for all of
+// them first and then memory over it: with both kinds of load in one branch
+// the compiler waits for one before it issues the next into the same register
+// (a sweep of R-MAT scale 18 from host ranks: 3153 against 2974 us).  The
+// launch kernels, whose LDS copy takes a sixth of the gathers, have no
+// register left for that (R-MAT scale 22 29.8 against 31.6 ms).
+template <bool COH, class T>
+__device__ __forceinline__ void load_contribs(const T *hub, uint32_t n_hub, const T *C,
+                                              const int32_t (&i)[kUnroll], T (&c)[kUnroll])
+{
+    if constexpr (COH) {
+        if (n_hub) {
+#pragma unroll
+            for (int j = 0; j < kUnroll; j++) c[j] = hub[min((uint32_t)i[j], n_hub - 1)];
+        } else {
+#pragma unroll
+            for (int j = 0; j < kUnroll; j++) c[j] = (T)0;
+        }
+#pragma unroll
+        for (int j = 0; j < kUnroll; j++)
+            if (i[j] >= (int32_t)n_hub) c[j] = ld<COH>(C + i[j]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < kUnroll; j++)
+            c[j] = i[j] < 0 ? (T)0 : (uint32_t)i[j] < n_hub ? hub[i[j]] : ld<COH>(C + i[j]);
+    }
+}
+
 // Sum of the contributions of in-edges idx[k] for k = first, first + step,
 // ... < cnt, added in that order.  FP64, or (F32) FP32 contributions added
 // with Kahan's compensated summation and returned as sum - compensation in
@@ -204,9 +244,7 @@ __device__ __forceinline__ double gather_sum(const IterArgs &a, const Hub &hub, 
                 i[j] = k < cnt ? load_idx<COH>(idx + k) : -1;
             }
             double c[kUnroll];
-#pragma unroll
-            for (int j = 0; j < kUnroll; j++)
-                c[j] = i[j] < 0 ? 0.0 : (uint32_t)i[j] < hub.n ? hub.d[i[j]] : ld<COH>(a.Cc + i[j]);
+            load_contribs<COH>(hub.d, hub.n, a.Cc, i, c);
 #pragma unroll
             for (int j = 0; j < kUnroll; j++)
                 if (i[j] >= 0) s += c[j];
@@ -222,10 +260,7 @@ __device__ __forceinline__ double gather_sum(const IterArgs &a, const Hub &hub, 
                 i[j] = k < cnt ? load_idx<COH>(idx + k) : -1;
             }
             float c[kUnroll];
-#pragma unroll
-            for (int j = 0; j < kUnroll; j++)
-                c[j] = i[j] < 0 ? 0.0f : (uint32_t)i[j] < hub.n ? hub.f[i[j]]
-                                                              : ld<COH>(a.C32c + i[j]);
+            load_contribs<COH>(hub.f, hub.n, a.C32c, i, c);
 #pragma unroll
             for (int j = 0; j < kUnroll; j++) {
                 if (i[j] >= 0) {
@@ -726,7 +761,7 @@ __device__ __forceinline__ void make_plan_wave(const IterArgs &a, const Ctl *ctl
                                                bool f32, const uint32_t *snap, uint32_t G, uint32_t waves,
                                                Plan &p)
 {
-    const int lane = lane_id();
+    const int lane = (int)fresh((uint32_t)lane_id());
     const int b = lane < kBins ? lane : kBins - 1;
     uint32_t id0 = 0, cnt, loops = 0;
     if (sparse) {

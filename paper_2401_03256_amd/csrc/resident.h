@@ -202,7 +202,7 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
     double *const hub_lds = lds.hub;
     if (!resident_start(P, blk, G, rs)) return;
     const unsigned long long t0_clock = P.budget ? wall_clock64() : 0ull;
-    const int wave = threadIdx.x / kWave, lane = lane_id();
+    const int wave = threadIdx.x / kWave;
     // the state at the launch's start: the kernels before it left it
     bool dense = !DF || a.ctl->dense, stop = a.ctl->done || (F32 && a.ctl->phase_end);
     if (threadIdx.x < 8)
@@ -230,6 +230,8 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
     int k = 0;
     for (; k < kResSteps; k++) {
         const int it = P.it_start + k;
+        const uint32_t tid = fresh(threadIdx.x);
+        const int lane = tid % kWave;
         uint32_t rows = 0;
 #pragma unroll
         for (int b = 0; b < kBins; b++) rows += rs.state[1 + b];
@@ -246,15 +248,15 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
         if (wave == 0 && !(dense && planned))
             make_plan_wave(a, a.ctl, sparse, DF, F32, rs.state + 1, G, G * kResWaves, sh.plan);
         planned = dense;
-        if (sparse && threadIdx.x <= kBins) (threadIdx.x ? rs.stage.cnt[threadIdx.x - 1] : rs.stage.n) = 0;
+        if (sparse && tid <= kBins) (tid ? rs.stage.cnt[tid - 1] : rs.stage.n) = 0;
         Hub hub{hub_lds, reinterpret_cast<const float *>(hub_lds), 0u};
         if (!sparse && a.hub) {
             hub.n = a.hub;
             if (F32) {
                 float *f = reinterpret_cast<float *>(hub_lds);
-                for (uint32_t v = threadIdx.x; v < hub.n; v += kResThreads) f[v] = ld<true>(a.C32c + v);
+                for (uint32_t v = tid; v < hub.n; v += kResThreads) f[v] = ld<true>(a.C32c + v);
             } else {
-                for (uint32_t v = threadIdx.x; v < hub.n; v += kResThreads)
+                for (uint32_t v = tid; v < hub.n; v += kResThreads)
                     hub_lds[v] = ld<true>(a.Cc + v);
             }
         }
@@ -270,11 +272,11 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
             __syncthreads();
             const uint32_t n = min(rs.stage.n, rs.stage.cap);
             if (n) {
-                if (threadIdx.x < kBins && rs.stage.cnt[threadIdx.x])
-                    rs.stage.base[threadIdx.x] =
-                        atomicAdd(&a.ctl->live[threadIdx.x], rs.stage.cnt[threadIdx.x]);
+                if (tid < kBins && rs.stage.cnt[tid])
+                    rs.stage.base[tid] =
+                        atomicAdd(&a.ctl->live[tid], rs.stage.cnt[tid]);
                 __syncthreads();
-                for (uint32_t i = threadIdx.x; i < n; i += kResThreads) {
+                for (uint32_t i = tid; i < n; i += kResThreads) {
                     const uint2 e = rs.stage.item[i];
                     const uint32_t c = e.y >> 28;
                     st<true>(&a.bins[(size_t)c * a.n_stride + rs.stage.base[c] + (e.y & 0xFFFFFFFu)],
@@ -333,11 +335,11 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
             }
             __syncthreads();
         } else {
-            if (threadIdx.x < 8) {
+            if (tid < 8) {
                 uint32_t v = 1u;
-                if (!await_word(&P.w->state[(blk & (kResCopies - 1)) * 8 + threadIdx.x], tag, v))
+                if (!await_word(&P.w->state[(blk & (kResCopies - 1)) * 8 + tid], tag, v))
                     rs.fail = 1;
-                rs.state[threadIdx.x] = v;
+                rs.state[tid] = v;
             }
             __syncthreads();
         }
