@@ -521,6 +521,81 @@ __device__ __forceinline__ UnitRow wave_unit(const IterArgs &a, const Hub &hub, 
     return {v, cnt, oc, xs, rc, s, active && sub == 0};
 }
 
+// A wave unit of two rows a lane group, the one numbered as the group from
+// `first` on and that 64 / G later (resident loop, FP64, full schedule).  A
+// row's loads are a chain of three, and a wave whose units take one row a
+// group waits each of them out between few instructions: on R-MAT scale 20
+// the rows took 33 of their 65 us with the indices and the gathers left out.
+// Two rows share the chain, four in-edges of each in flight.  LOOP as in
+// wave_unit.  R-MAT with 1.5e6 vertices 11.05 -> 10.32 ms a call; see
+// kPairUnits for where it is used.
+template <int G, bool DF, bool LOOP = false>
+__device__ __forceinline__ void wave_pair(const IterArgs &a, const Hub &hub, uint32_t id0, uint32_t count,
+                                          uint32_t first, bool check, UnitRow (&row)[2])
+{
+    constexpr int U = kUnroll / 2;
+    const int lane = lane_id();
+    const int sub = lane & (G - 1);
+    uint32_t beg[2], n[2];
+    bool active[2];
+#pragma unroll
+    for (int p = 0; p < 2; p++) {
+        const uint32_t pos = first + p * (kWave / G) + lane / G;
+        UnitRow &r = row[p];
+        r = {0, 0, 1, 0, 0.0, 0.0, false};
+        beg[p] = n[p] = 0;
+        active[p] = pos < count;
+        r.v = (int32_t)(id0 + pos);
+        if (DF && LOOP && check && active[p]) {
+            const uint32_t sx = ld<true>(a.stamp + r.v);
+            active[p] = sx >= a.sbase && sx <= a.sbase + (uint32_t)a.it;
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < 2; p++) {
+        UnitRow &r = row[p];
+        if (!active[p]) continue;
+        beg[p] = a.in_beg[r.v];
+        r.cnt = a.in_cnt[r.v];
+        if (sub == 0) {
+            r.rc = ld<true>(a.Rc + r.v);
+            r.oc = a.out_cnt[r.v];
+            if (DF) r.xs = ld<true>(a.xstamp + r.v);
+        }
+        if (DF && !LOOP && check) {
+            const uint32_t sx = ld<true>(a.stamp + r.v);
+            active[p] = sx >= a.sbase && sx <= a.sbase + (uint32_t)a.it;
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < 2; p++) {
+        if (!active[p]) continue;
+        // a self-loop as the only in-edge needs no index
+        if (row[p].cnt == 1) row[p].s = sub == 0 ? ld<true>(a.Cc + row[p].v) : 0.0;
+        else n[p] = row[p].cnt;
+    }
+    const uint32_t most = max(n[0], n[1]);
+    for (uint32_t k0 = sub; k0 < most; k0 += G * U) {
+        int32_t i[kUnroll];
+#pragma unroll
+        for (int j = 0; j < kUnroll; j++) {
+            const uint32_t k = k0 + (j % U) * G;
+            i[j] = k < n[j / U] ? a.in_idx[beg[j / U] + k] : -1;
+        }
+        double c[kUnroll];
+        load_contribs<true>(hub.d, hub.n, a.Cc, i, c);
+#pragma unroll
+        for (int j = 0; j < kUnroll; j++)
+            if (i[j] >= 0) row[j / U].s += c[j];
+    }
+#pragma unroll
+    for (int p = 0; p < 2; p++) {
+#pragma unroll
+        for (int off = G / 2; off > 0; off >>= 1) row[p].s += __shfl_xor(row[p].s, off, G);
+        row[p].mine = active[p] && sub == 0;
+    }
+}
+
 // The rest of a wave unit, once its rows are summed: the same code for every
 // class.
 template <bool DF, bool F32, bool COH>
@@ -748,7 +823,8 @@ __device__ __forceinline__ int lg_rows(int b)
 // The same by one wave, for `waves` waves.  While the class lists hold fewer
 // rows than the waves could take, a wave unit takes fewer rows: a wave's
 // rows expand one round of out-edges after another, so a small frontier is
-// done soonest when it is spread over all waves.  p.ftol and p.plain are
+// done soonest when it is spread over all waves.  With `pairs` a unit of the
+// full schedule takes twice the rows (wave_pair).  p.ftol and p.plain are
 // left alone (they hold for the whole call).
 // On the full schedule block rows follow decreasing in-degree too: workgroup
 // b of G has long rows b, b + G, ..., and four of the others at a time, so the
@@ -758,8 +834,8 @@ __device__ __forceinline__ int lg_rows(int b)
 // which the first is the longest, and 1 + in-edges / 4096 rounds.  A workgroup
 // sits out as many rounds as its rows take beyond those of the last workgroup.
 __device__ __forceinline__ void make_plan_wave(const IterArgs &a, const Ctl *ctl, bool sparse, bool df,
-                                               bool f32, const uint32_t *snap, uint32_t G, uint32_t waves,
-                                               Plan &p)
+                                               bool f32, bool pairs, const uint32_t *snap, uint32_t G,
+                                               uint32_t waves, Plan &p)
 {
     const int lane = (int)fresh((uint32_t)lane_id());
     const int b = lane < kBins ? lane : kBins - 1;
@@ -774,7 +850,9 @@ __device__ __forceinline__ void make_plan_wave(const IterArgs &a, const Ctl *ctl
         if (!df) loops = 0;
     }
     const bool unit = lane < kBins - 1;
-    int lg = lg_rows(b);
+    // full schedule, wave_pair: twice the rows
+    const int two = pairs && !sparse ? 1 : 0;
+    int lg = unit ? lg_rows(b) + two : 0;
     uint32_t n = unit ? (cnt + (1u << lg) - 1) >> lg : 0u;
     if (sparse) {
         uint32_t tot = n;
@@ -805,7 +883,7 @@ __device__ __forceinline__ void make_plan_wave(const IterArgs &a, const Ctl *ctl
         if (!unit) {
             p.loop_cnt = loops;
             if (!sparse) p.loop_id0 = ctl->cls[kBins];
-            p.nwu = tot + (loops + kWave - 1) / kWave;
+            p.nwu = tot + ((loops + (kWave << two) - 1) >> (6 + two));
             p.nbu = cnt;
         }
     }
@@ -885,7 +963,7 @@ struct FinalShared {
 // time.  The resident loop (COH) deals the units out one workgroup after the
 // other, so that a few long units, or a frontier of few units, are spread
 // over all compute units.
-template <bool DF, bool F32, int NW, bool COH>
+template <bool DF, bool F32, int NW, bool COH, bool PAIRS = false>
 __device__ __forceinline__ void iter_rows(const IterArgs &a, const Hub &hub, uint32_t blk, uint32_t G,
                                           IterSharedT<NW> &sh, bool check, bool sparse, Acc &acc)
 {
@@ -944,9 +1022,37 @@ __device__ __forceinline__ void iter_rows(const IterArgs &a, const Hub &hub, uin
     } else {
         block_rows(quarter, blk * (NW * kWave / kBlock), nbu);
     }
+    auto unit_pair = [&](uint32_t u, int k, UnitRow (&row)[2]) {
+        if (k == kBins - 1) {
+            wave_pair<1, DF, true>(a, hub, sh.plan.loop_id0, sh.plan.loop_cnt,
+                                   (u - sh.plan.ustart[k]) * (2 * kWave), check, row);
+            return;
+        }
+        const int b = kBins - 2 - k;
+        const uint32_t first = (u - sh.plan.ustart[k]) * sh.plan.per[b];
+        const uint32_t id0 = sh.plan.id0[b], cnt = sh.plan.cnt[b];
+        switch (b) {
+        case 0: wave_pair<1, DF>(a, hub, id0, cnt, first, check, row); break;
+        case 1: wave_pair<2, DF>(a, hub, id0, cnt, first, check, row); break;
+        case 2: wave_pair<4, DF>(a, hub, id0, cnt, first, check, row); break;
+        case 3: wave_pair<8, DF>(a, hub, id0, cnt, first, check, row); break;
+        case 4: wave_pair<32, DF>(a, hub, id0, cnt, first, check, row); break;
+        default: wave_pair<64, DF>(a, hub, id0, cnt, first, check, row);
+        }
+    };
     auto run = [&](uint32_t u) {
         int k = 0;
         while (k + 1 < kBins && u >= sh.plan.ustart[k + 1]) k++;
+        if constexpr (PAIRS) {
+            if (!sparse) {
+                UnitRow rows[2];
+                unit_pair(u, k, rows);
+#pragma unroll 1
+                for (int p = 0; p < 2; p++)
+                    finish_unit<DF, F32, COH>(a, p ? rows[1] : rows[0], sparse, acc);
+                return;
+            }
+        }
         const UnitRow row = unit_rows(u, k);
         finish_unit<DF, F32, COH>(a, row, sparse, acc);
     };

@@ -119,11 +119,11 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(IterArgs a, int df, int
     final_body(a, df != 0, f32 != 0, sh, last != 0);
 }
 
-template <bool DF, bool F32>
+template <bool DF, bool F32, bool PAIRS>
 __global__ __launch_bounds__(kResThreads) void k_resident(IterArgs a, ResArgs P)
 {
     __shared__ ResLds lds;
-    resident_body<DF, F32>(a, P, blockIdx.x, gridDim.x, lds);
+    resident_body<DF, F32, PAIRS>(a, P, blockIdx.x, gridDim.x, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1046,10 +1046,8 @@ static uint32_t sparse_grid(const dfpr_graph *g, const Ctl &c)
     return (uint32_t)std::min<uint64_t>(g->grid, std::max<uint64_t>(lo, need * 4 + 64));
 }
 
-// Workgroups of a resident launch whose iterations walk the full schedule:
-// enough waves for its wave units and enough sub-blocks for its long rows,
-// one workgroup per compute unit at most.
-uint32_t resident_grid(const dfpr_graph *g)
+// Wave units of the full schedule (make_plan_wave).
+static uint64_t wave_units(const dfpr_graph *g)
 {
     const uint32_t *c = g->cls;
     uint64_t nwu = ((uint64_t)(c[kBins + 1] - c[kBins]) + kWave - 1) / kWave;
@@ -1057,6 +1055,16 @@ uint32_t resident_grid(const dfpr_graph *g)
         const uint64_t rows = kWave / group_of(b);
         nwu += ((uint64_t)(c[kBins - b] - c[kBins - 1 - b]) + rows - 1) / rows;
     }
+    return nwu;
+}
+
+// Workgroups of a resident launch whose iterations walk the full schedule:
+// enough waves for its wave units and enough sub-blocks for its long rows,
+// one workgroup per compute unit at most.
+uint32_t resident_grid(const dfpr_graph *g)
+{
+    const uint32_t *c = g->cls;
+    const uint64_t nwu = wave_units(g);
     const uint64_t need = std::max<uint64_t>((nwu + kResWaves - 1) / kResWaves, (c[1] - c[0] + 3) / 4);
     return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(need, g->cus));
 }
@@ -1135,9 +1143,11 @@ static int launch_resident(dfpr_graph *g, IterArgs a, bool df, bool f32, int it0
     const uint32_t G = full ? resident_grid(g) : (uint32_t)g->cus;
     a.hub = full && a.hub ? resident_hub(g, f32, G) : 0u;
     a.sparse_limit = resident_lists(g);
-    if (!df) k_resident<false, false><<<G, kResThreads, 0, g->stream>>>(a, P);
-    else if (f32) k_resident<true, true><<<G, kResThreads, 0, g->stream>>>(a, P);
-    else k_resident<true, false><<<G, kResThreads, 0, g->stream>>>(a, P);
+    const bool pairs = full && !f32 && wave_units(g) >= (uint64_t)kPairUnits * kResWaves * G;
+    auto *kernel = f32     ? k_resident<true, true, false>
+                   : !df   ? pairs ? k_resident<false, false, true> : k_resident<false, false, false>
+                   : pairs ? k_resident<true, false, true> : k_resident<true, false, false>;
+    kernel<<<G, kResThreads, 0, g->stream>>>(a, P);
     DFPR_HIP(hipGetLastError());
     DFPR_HIP(hipEventRecord(g->ev1, g->stream));
     DFPR_HIP(hipStreamSynchronize(g->stream));

@@ -51,6 +51,15 @@ constexpr int64_t kResEdges = 40000000;
 // with its stamp is quicker (a 64th with launches): 1.57 against 2.35 ms on
 // uniform grid batches, no change on R-MAT.
 constexpr int32_t kResSparse = 8;
+// Wave units per wave of the full schedule from which FP64 sweeps take two rows
+// a lane group (wave_pair).  Of a call on R-MAT scale 17 (2.2 units a wave) it
+// takes 2134 instead of 2076 us, since waves are left without a unit; scale 18
+// (4.4) 3009 instead of 3017, scale 20 (16) 8460 instead of 8742, a grid of
+// 2048 x 2048 vertices (32) 5759 instead of 6889.  The FP32 form's sums are a
+// longer chain of instructions and slower in pairs: 1.5e6 vertices 10.42
+// instead of 10.25 ms.  On the class lists a unit has one row a lane group:
+// pairs made a call on R-MAT scale 13 11% slower.
+constexpr uint32_t kPairUnits = 4;
 constexpr uint32_t kLoopRows = 16384;            // DFPR_LOOP_DEVICE: most rows of an iteration
 constexpr int kResWaves = 16;
 constexpr int kResThreads = kResWaves * kWave;
@@ -193,7 +202,7 @@ __device__ inline bool resident_start(const ResArgs &P, uint32_t blk, uint32_t G
 }
 
 // Workgroup blk of the G that iterate one graph.
-template <bool DF, bool F32>
+template <bool DF, bool F32, bool PAIRS>
 __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint32_t blk, uint32_t G,
                                               ResLds &lds)
 {
@@ -246,7 +255,7 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
         a.C32n = src ? P.C32[0] : P.C32[1];
         const bool sparse = DF && !dense;
         if (wave == 0 && !(dense && planned))
-            make_plan_wave(a, a.ctl, sparse, DF, F32, rs.state + 1, G, G * kResWaves, sh.plan);
+            make_plan_wave(a, a.ctl, sparse, DF, F32, PAIRS, rs.state + 1, G, G * kResWaves, sh.plan);
         planned = dense;
         if (sparse && tid <= kBins) (tid ? rs.stage.cnt[tid - 1] : rs.stage.n) = 0;
         Hub hub{hub_lds, reinterpret_cast<const float *>(hub_lds), 0u};
@@ -264,7 +273,7 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
         Acc acc;
         acc.ftol = sh.plan.ftol;
         acc.plain = sh.plan.plain != 0;
-        iter_rows<DF, F32, kResWaves, true>(a, hub, blk, G, sh, DF && dense, sparse, acc);
+        iter_rows<DF, F32, kResWaves, true, PAIRS>(a, hub, blk, G, sh, DF && dense, sparse, acc);
 #pragma unroll
         for (int j = 0; j < kCounters; j++) tot[j] += acc.c[j];
         if (sparse) {

@@ -128,8 +128,8 @@ __global__ __launch_bounds__(kResThreads) void k_resident_multi(ResMultiArgs m)
     int s = 0;
     while (s + 1 < m.nslots && b >= m.off[s + 1]) s++;
     const uint32_t G = m.off[s + 1] - m.off[s];
-    if ((m.f32_mask >> s) & 1u) resident_body<true, true>(m.s[s], m.r[s], b - m.off[s], G, lds);
-    else resident_body<true, false>(m.s[s], m.r[s], b - m.off[s], G, lds);
+    if ((m.f32_mask >> s) & 1u) resident_body<true, true, false>(m.s[s], m.r[s], b - m.off[s], G, lds);
+    else resident_body<true, false, true>(m.s[s], m.r[s], b - m.off[s], G, lds);
 }
 
 // Copy the control blocks of the slots into one array for one host copy.

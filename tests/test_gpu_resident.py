@@ -129,6 +129,26 @@ def test_fp32_block_rows_over_the_workgroups(dfpr, rows):
     _same(f"{rows}", g.dynamic_frontier(bt, R, p), h.dynamic_frontier(bt, R, p))
 
 
+@pytest.mark.parametrize("name", ["rmat18", "grid739"])
+def test_pairs_of_rows_bitwise_equal_to_launches(dfpr, name):
+    """Full schedules of more than four wave units a wave: two rows a lane
+    group, with odd rows left over and with self-loop rows."""
+    n, src, dst = {"rmat18": lambda: synth.rmat(18, 16, seed=11),
+                   "grid739": lambda: synth.grid2d(739, seed=12)}[name]()
+    n = int(n)
+    g, h = dfpr.Graph(n, src, dst), dfpr.Graph(n, src, dst)
+    h.profile_reset(True)
+    a, b = g.static(), h.static()
+    _same("static", a, b)
+    R = a[0]
+    bt = synth.random_batch(src, dst, n, 500, n // 40, seed=70)
+    assert g.apply_batch(bt) == h.apply_batch(bt)
+    _same("df", g.dynamic_frontier(bt, R), h.dynamic_frontier(bt, R))
+    assert np.array_equal(g.affected(), h.affected())
+    _same("traversal", g.dynamic_traversal(bt, R), h.dynamic_traversal(bt, R))
+    _same("naive", g.naive_dynamic(R), h.naive_dynamic(R))
+
+
 def test_resident_loop_calls_from_two_threads(dfpr):
     """Two graphs updated at once: each call's workgroups may find the other's
     running; results stay those of calls one at a time."""
