@@ -1695,10 +1695,11 @@ static int traverse(dfpr_graph *g, const IterArgs &a, int64_t nd, const int32_t 
             chunk = 1;
             continue;
         }
-        // the levels to come are wide once a level's claims have more
-        // out-edges than a quarter of the vertices (the claims of a chunk of
-        // several levels are below that taken together)
-        wide = !append && c.reach - reach > (unsigned long long)n / 4;
+        // the levels to come are wide once the claims of a level, on average
+        // over the chunk, have more out-edges than a quarter of the vertices
+        // (a grid of 2048 x 2048 vertices reaches that with the 16 levels of a
+        // chunk together: 24.5 ms a call, and 26.0 with wide levels)
+        wide = !append && c.reach - reach > (unsigned long long)n / 4 * (unsigned)chunk;
         was_wide |= wide;
         reach = c.reach;
         grid = bfs_grid(g, next, nexth);
