@@ -36,7 +36,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_iter_traffic.json")
 # sources whose text fixes the iteration kernel's code, launch shape and
 # the vertex numbering it runs on (all of which move its memory traffic)
 KERNEL_SRC = [os.path.join(ROOT, "paper_2401_03256_amd", "csrc", f)
-              for f in ("iter.h", "common.h", "rank.hip", "graph.hip")]
+              for f in ("iter.h", "resident.h", "common.h", "rank.hip", "graph.hip")]
 
 
 def log(*a):

@@ -36,11 +36,12 @@ namespace dfpr {
 // No cooperative launch: before anything is written, the workgroups wait a
 // bounded time until all of them run, and one compare-and-swap decides for
 // all whether they go or leave.  Other work on the device can so at worst
-// send a call back to the launch pairs.
+// send a call back to a launch per iteration.
+//
 // Where it is used.  Graphs of up to kResEdges in-edges run whole calls in
 // it, because their full sweep is short next to the launches or gains from
-// the larger LDS copy: against launches, an update pair took 1.56 / 2.15 ms on
-// a 10,000-vertex G(n, m), 9.5 / 12.9 ms on R-MAT scale 20 and 15.1 / 16.8 ms
+// the larger LDS copy: against launches, an update pair takes 1.21 / 2.15 ms on
+// a 10,000-vertex G(n, m), 8.5 / 12.9 ms on R-MAT scale 20 and 14.1 / 16.8 ms
 // on scale 21 (35M edges).  On scale 22 (69M) its 16 waves per compute unit
 // and gathers past the vector L1 lose to k_iter_wide (32.9 / 30.1 ms), so
 // larger graphs use it only while a Dynamic Frontier call is on the class
