@@ -404,7 +404,9 @@ __device__ inline void mark_one(const IterArgs &a, int32_t x, bool append,
 // sources reach more vertices than the sparse limit; the decision goes to
 // the control block for the iterations.  Every loop bound is uniform
 // within a wave.  With `snap` the last workgroup of the grid takes the
-// snapshot of iteration 0.
+// snapshot of iteration 0.  A call that is over with it (an id outside [0, n),
+// or no iteration allowed) has no iteration that would leave the control block
+// in the host's copy, so it goes there from here.
 __global__ __launch_bounds__(kBlock) void k_mark_initial(IterArgs a, int64_t nd, const int32_t *dd,
                                                          const int32_t *light,
                                                          const int32_t *heavy, int dense, int snap,
@@ -412,7 +414,7 @@ __global__ __launch_bounds__(kBlock) void k_mark_initial(IterArgs a, int64_t nd,
 {
     __shared__ unsigned long long s_new, s_deg;
     __shared__ HeavyShared hs;
-    __shared__ int s_last;
+    __shared__ int s_last, s_over;
     Ctl *ctl = a.ctl;
     const bool dn = dense || ctl->reach + (unsigned long long)nd > a.sparse_limit;
     const bool append = !dn;
@@ -448,8 +450,14 @@ __global__ __launch_bounds__(kBlock) void k_mark_initial(IterArgs a, int64_t nd,
             atomicAdd(&ctl->reach0, s_deg);
         }
     }
-    if (snap && last_block(ctl->tick, &s_last) && threadIdx.x == 0)
+    if (!snap || !last_block(ctl->tick, &s_last)) return;
+    if (threadIdx.x == 0) {
         snap_ctl<true>(ctl, a.max_iters, a.sparse_limit, plain_limit, dense, a.tol, a.ftol);
+        s_over = ctl->done != 0;
+        drain_stores();
+    }
+    __syncthreads();
+    if (s_over && threadIdx.x < kWave) ctl_to_mirror(ctl, a.mirror);
 }
 
 // The start of a call in one launch: workgroup 0 clears the loop state and,
