@@ -116,7 +116,7 @@ struct IterBufs {
     double *rmax_part = nullptr;              // largest rank (atomic max on the bits)
     unsigned long long *cnt_part = nullptr;   // counters (kCounters per slot)
     // resident loop: what its workgroups hand to workgroup 0 and back
-    // (ResWords in rank.hip); tags make clearing unnecessary
+    // (ResWords in resident.h); tags make clearing unnecessary
     unsigned long long *res = nullptr;
 };
 
@@ -196,6 +196,9 @@ struct dfpr_graph {
     int64_t prof_base[5] = {0, 0, 0, 0, 0};   // counters already added to prof
     int32_t refine_sweeps = 0;        // FP64 iterations after the FP32 phase
     int32_t loop_iters = 0;           // iterations the small-frontier loop ran
+    int64_t res_iters = 0;            // iterations run in resident launches since the load
+    int res_refuse = 0;               // resident launches do not wait for their workgroups,
+                                      // so that they end before they start (dfpr_test_resident)
     int busy = 0;
     int device = 0;                   // the HIP device the graph lives on
     int grid = 1024;                  // iteration-kernel workgroups

@@ -1129,6 +1129,7 @@ int resident_args(dfpr_graph *g, int it0, int it, int base, bool full, uint32_t 
     P.it_start = it;
     P.full = full ? 1 : 0;
     P.limit = limit;
+    P.spin = g->res_refuse ? 0u : kGoSpin;
     P.tag = g->res_tag + 1;
     P.ext2int = g->ext2int;
     g->res_tag += kResTags;
@@ -1205,6 +1206,7 @@ static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint
             const Ctl &c = *g->ctl_host;
             const int steps = c.iterations - next_it;
             next_it = c.iterations;
+            g->res_iters += steps;
             if (device_loop) g->loop_iters += steps;
             if (c.done || (f32 && c.phase_end)) {
                 stop = true;
@@ -1963,6 +1965,19 @@ int dfpr_profile_read(const dfpr_graph *g, dfpr_profile *out)
     out->expanded_rows = g->prof.exp_rows;
     out->expanded_edges = g->prof.exp_edges;
     out->marked = g->prof.marked;
+    return DFPR_OK;
+}
+
+// For this library's tests, and in no header: whether resident launches of the
+// graph are to end before they start, as they do when not all workgroups run;
+// the last barrier tag handed out (0: as it is); and the number of iterations
+// that ran in resident launches since the load, serving included.
+int dfpr_test_resident(dfpr_graph *g, int refuse, uint32_t tag, int64_t *iterations)
+{
+    if (!g) return set_error(DFPR_E_ARG, "graph is NULL");
+    g->res_refuse = refuse;
+    if (tag) g->res_tag = tag;
+    if (iterations) *iterations = g->res_iters;
     return DFPR_OK;
 }
 

@@ -93,6 +93,7 @@ struct ResArgs {
     int it_start;       // first iteration of this launch
     int full;           // the launch keeps going on the full schedule
     uint32_t limit;     // class list rows of an iteration above which it hands over
+    uint32_t spin;      // polls of workgroup 0 before the launch gives up starting
     uint32_t tag;       // first of its tags
     int close;          // end the call too, if it converges or reaches the cap
     double *out;        //   the ranks in the caller's order (nullable)
@@ -188,14 +189,14 @@ __device__ inline bool resident_start(const ResArgs &P, uint32_t blk, uint32_t G
     __syncthreads();
     if (blk == 0) {
         bool here = threadIdx.x >= G;
-        for (uint32_t n = 0; n < kGoSpin && !here; n++)
+        for (uint32_t n = 0; n < P.spin && !here; n++)
             here = (uint32_t)ld<true>(&P.w->arrive[0][threadIdx.x]) == P.tag;
         if (!here) rs.go = 0;
         __syncthreads();
         if (threadIdx.x == 0) rs.go = (int)decide(rs.go ? 1u : 0u);
     } else if (threadIdx.x == 0) {
         unsigned long long x = 0;
-        for (uint32_t n = 0; n < 2 * kGoSpin && (uint32_t)x != P.tag; n++) x = ld<true>(go);
+        for (uint32_t n = 0; n < 2 * P.spin && (uint32_t)x != P.tag; n++) x = ld<true>(go);
         rs.go = (int)decide(0u);
     }
     __syncthreads();

@@ -662,6 +662,7 @@ static int run(dfpr_server *srv, dfpr_server_stats *st)
                         goto out;
                     }
                     most = std::max(most, c.iterations - s.itq);
+                    g->res_iters += c.iterations - s.itq;
                     s.itq = c.iterations;
                 }
                 *g->ctl_host = c;
