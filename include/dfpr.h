@@ -72,6 +72,7 @@ extern "C" {
 /* iteration drivers (dfpr_params.loop) */
 #define DFPR_LOOP_LAUNCHES 0 /* the library's choice                            */
 #define DFPR_LOOP_DEVICE 1   /* only small frontiers iterate inside one launch  */
+#define DFPR_LOOP_ITERATION 2 /* a launch pair per iteration, always            */
 
 typedef struct dfpr_graph dfpr_graph;
 
@@ -104,11 +105,15 @@ typedef struct {
     int32_t loop;          /* DFPR_LOOP_LAUNCHES (default): the library picks
                               what is fastest, a launch pair per iteration
                               (pull, then fold) or many iterations inside one
-                              launch; DFPR_LOOP_DEVICE: a launch pair per
-                              iteration except while a Dynamic Frontier call's
-                              frontier is small (these iterations are counted
-                              in dfpr_stats.loop_iterations).  Results are
-                              bitwise the same either way.                     */
+                              launch, which then holds every compute unit for
+                              up to the length of the call; DFPR_LOOP_DEVICE:
+                              a launch pair per iteration except while a
+                              Dynamic Frontier call's frontier is small;
+                              DFPR_LOOP_ITERATION: a launch pair per iteration
+                              throughout, for callers whose other work should
+                              get the device between iterations (a served
+                              graph's requests too).  Results are bitwise the
+                              same in all of them.                             */
 } dfpr_params;
 
 typedef struct {
@@ -118,7 +123,8 @@ typedef struct {
                                    reaching max_iters is not an error         */
     int32_t refine_sweeps;      /* FP64 iterations after the FP32 phase       */
     int32_t loop_iterations;    /* DFPR_LOOP_DEVICE: iterations run inside one
-                                   launch while the frontier was small        */
+                                   launch while the frontier was small; 0 in
+                                   the other forms, whatever ran them         */
     double final_linf;          /* L-inf change of the last iteration          */
     double ms_device;           /* device time of the call (HIP events)        */
     int64_t affected_initial;   /* vertices marked by the initial marking      */
@@ -239,7 +245,8 @@ int dfpr_pagerank_dynamic_frontier_device(dfpr_graph *g, const dfpr_params *p,
  * ends) instead of a buffer it grows on demand, so the call makes no
  * allocation.  n_del + n_ins may be at most 1048576 (DFPR_E_LIMIT beyond,
  * nothing changed).  Every call on a GPU shares that array: calls that
- * overlap on one GPU race.  p->loop is taken as DFPR_LOOP_LAUNCHES. */
+ * overlap on one GPU race.  DFPR_LOOP_DEVICE is taken as
+ * DFPR_LOOP_LAUNCHES. */
 int dfpr_pagerank_dynamic_frontier_device_noalloc(dfpr_graph *g, const dfpr_params *p,
                                                   int64_t n_del, const int32_t *del_src,
                                                   const int32_t *del_dst, int64_t n_ins,

@@ -70,7 +70,7 @@ int dfpr_pagerank_dynamic_frontier_device_noalloc(dfpr_graph *g, const dfpr_para
     if (p) q = *p;
     else dfpr_params_default(&q);
     // DFPR_LOOP_DEVICE is not offered on this path
-    q.loop = DFPR_LOOP_LAUNCHES;
+    if (q.loop != DFPR_LOOP_ITERATION) q.loop = DFPR_LOOP_LAUNCHES;
     int32_t *buf = nullptr;
     const int rc = scratch_on(g->device, &buf);
     if (rc) return rc;

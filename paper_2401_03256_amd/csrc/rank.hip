@@ -971,7 +971,8 @@ int check_params(const dfpr_params *p, dfpr_params &out)
         std::isnan(out.frontier_tol) || out.max_iters < 0 || out.max_iters > 100000 ||
         (out.precision != DFPR_FP64 && out.precision != DFPR_FP32_KAHAN) ||
         (out.mode != DFPR_SYNC && out.mode != DFPR_ASYNC) ||
-        (out.loop != DFPR_LOOP_LAUNCHES && out.loop != DFPR_LOOP_DEVICE))
+        (out.loop != DFPR_LOOP_LAUNCHES && out.loop != DFPR_LOOP_DEVICE &&
+         out.loop != DFPR_LOOP_ITERATION))
         return set_error(DFPR_E_ARG, "invalid parameters");
     return DFPR_OK;
 }
@@ -1192,11 +1193,11 @@ static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint
     double prev_dr = -1.0;
     int prev_it = it0;
     *res_buf = base;
-    // Iterations inside one launch (see kResEdges).  The asynchronous form
-    // and profiled calls keep a launch per iteration.
+    // Iterations inside one launch (see kResEdges).  The asynchronous form,
+    // DFPR_LOOP_ITERATION and profiled calls keep a launch per iteration.
     const bool device_loop = p.loop == DFPR_LOOP_DEVICE;
     const bool full = !device_loop && g->m <= kResEdges;
-    if (!async && !g->prof.enabled && (full || df)) {
+    if (!async && p.loop != DFPR_LOOP_ITERATION && !g->prof.enabled && (full || df)) {
         const uint32_t limit = device_loop ? kLoopRows : 0xFFFFFFFFu;
         while (next_it < p.max_iters) {
             bool ran = false;
@@ -1485,7 +1486,8 @@ int df_begin(dfpr_graph *g, const dfpr_params &p, int64_t nd, const int32_t *ds,
     // keep can take it: where those are the resident loop's, from 1/64 to 1/8
     // of the vertices (2048 x 2048 grid, 256 scattered changes: a call
     // 3132 -> 2737 us; 10^6-vertex random graph: 4512 -> 4373 us).
-    const bool resident = p.mode != DFPR_ASYNC && !g->prof.enabled && g->m <= kResEdges;
+    const bool resident = p.mode != DFPR_ASYNC && p.loop != DFPR_LOOP_ITERATION &&
+                          !g->prof.enabled && g->m <= kResEdges;
     const uint32_t plain_limit = resident ? resident_lists(g) : a.sparse_limit;
     if (small) {
         b.nd = nd;

@@ -30,6 +30,7 @@ SYNC = 0
 ASYNC = 1
 LOOP_LAUNCHES = 0
 LOOP_DEVICE = 1
+LOOP_ITERATION = 2
 FTOL_ADAPTIVE = -1.0
 
 EXPORTED = [

@@ -193,3 +193,27 @@ def test_barrier_tags_start_over(dfpr):
             got = g.static()
             _same(f"{back}", got, want)
         assert _resident(dfpr, g) - at == 3 * want[1].iterations
+
+
+@pytest.mark.parametrize("name", ["gnm10000", "grid739"])
+def test_a_launch_per_iteration_on_request(dfpr, name):
+    _say(f"a launch per iteration, {name}")
+    n, src, dst = GRAPHS[name]()
+    bt = synth.random_batch(src, dst, n, 3, 9, seed=8)
+    g, h = dfpr.Graph(n, src, dst), dfpr.Graph(n, src, dst)
+    R, _ = g.static()
+    assert g.apply_batch(bt) == h.apply_batch(bt)
+    at = _resident(dfpr, g)
+    for kw in (dict(), dict(precision=dfpr.FP32_KAHAN)):
+        a = dfpr.params(frontier_tol=1e-13, loop=dfpr.LOOP_ITERATION, **kw)
+        b = dfpr.params(frontier_tol=1e-13, **kw)
+        for what, call in (("static", lambda x, p: x.static(p)),
+                           ("naive", lambda x, p: x.naive_dynamic(R, p)),
+                           ("df", lambda x, p: x.dynamic_frontier(bt, R, p)),
+                           ("traversal", lambda x, p: x.dynamic_traversal(bt, R, p))):
+            _same(what, call(g, a), call(h, b))
+    assert _resident(dfpr, g) == at and _resident(dfpr, h) > 0
+    srv = dfpr.Server(max_slots=2, hbm_budget_bytes=8 << 30)
+    rid = srv.submit(srv.add_graph(g, a), 0.0, bt)
+    srv.run()
+    assert srv.result(rid)["status"] == 0 and _resident(dfpr, g) == at
