@@ -308,7 +308,8 @@ int dfpr_export_csr(const dfpr_graph *g, int out_orientation, int64_t *offsets,
 
 /* Profile of the iteration kernel (the pull, Delta r, L-inf and expansion
  * of one iteration), summed over every call made while profiling is on.
- * Calls made then take a launch pair per iteration on every graph.
+ * Calls made then take a launch pair per iteration on every graph, but for the
+ * small frontiers of DFPR_LOOP_DEVICE, whose iterations are not counted here.
  * ms is measured with HIP events recorded on the graph's stream right
  * before and after each iteration-kernel launch (timing-only events, with
  * no system-scope fence).  bytes is the algorithmic traffic of those

@@ -1194,10 +1194,13 @@ static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint
     int prev_it = it0;
     *res_buf = base;
     // Iterations inside one launch (see kResEdges).  The asynchronous form,
-    // DFPR_LOOP_ITERATION and profiled calls keep a launch per iteration.
+    // DFPR_LOOP_ITERATION and, unless small frontiers are asked for, profiled
+    // calls keep a launch per iteration.
     const bool device_loop = p.loop == DFPR_LOOP_DEVICE;
     const bool full = !device_loop && g->m <= kResEdges;
-    if (!async && p.loop != DFPR_LOOP_ITERATION && !g->prof.enabled && (full || df)) {
+    const bool resident = device_loop ? df
+                          : p.loop != DFPR_LOOP_ITERATION && !g->prof.enabled && (full || df);
+    if (!async && resident) {
         const uint32_t limit = device_loop ? kLoopRows : 0xFFFFFFFFu;
         while (next_it < p.max_iters) {
             bool ran = false;
@@ -1216,6 +1219,12 @@ static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint
             gsz = df && !c.dense ? sparse_grid(g, c) : (uint32_t)g->grid;
             wide = DFPR_WIDE && (!df || c.dense);
             if (steps < kResSteps) break;     // handed over
+        }
+        if (g->prof.enabled && next_it > it0) {
+            // not the iteration kernel's work
+            const Ctl &c = *g->ctl_host;
+            const unsigned long long ran[5] = {c.verts, c.edges, c.xverts, c.xedges, c.marked};
+            for (int k = 0; k < 5; k++) g->prof_base[k] = (int64_t)ran[k];
         }
     }
     auto launch = [&](int k) -> int {

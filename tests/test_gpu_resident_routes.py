@@ -217,3 +217,24 @@ def test_a_launch_per_iteration_on_request(dfpr, name):
     rid = srv.submit(srv.add_graph(g, a), 0.0, bt)
     srv.run()
     assert srv.result(rid)["status"] == 0 and _resident(dfpr, g) == at
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_profiled_small_frontiers(dfpr, precision):
+    """DFPR_LOOP_DEVICE while profiled: small frontiers still iterate inside one
+    launch, and the profile holds the other iterations."""
+    _say(f"profiled small frontiers, {precision}")
+    n, src, dst = synth.rmat(16, 16, seed=7)
+    bt = synth.random_batch(src, dst, n, 0, 1, seed=8)
+    p = dfpr.params(loop=dfpr.LOOP_DEVICE,
+                    precision=dfpr.FP64 if precision == "fp64" else dfpr.FP32_KAHAN)
+    g, h = dfpr.Graph(n, src, dst), dfpr.Graph(n, src, dst)
+    R, _ = g.static()
+    assert g.apply_batch(bt) == h.apply_batch(bt)
+    h.profile_reset(True)
+    a, b = g.dynamic_frontier(bt, R, p), h.dynamic_frontier(bt, R, p)
+    _same("profiled", a, b)
+    assert 0 < a[1].loop_iterations == b[1].loop_iterations < a[1].iterations
+    pr = h.profile()
+    assert pr.launches >= b[1].iterations - b[1].loop_iterations
+    assert 0 < pr.rows < b[1].vertices_processed and 0 < pr.edges < b[1].edges_processed
