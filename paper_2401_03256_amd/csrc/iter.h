@@ -648,8 +648,10 @@ __device__ __forceinline__ void finish_unit(const IterArgs &a, const UnitRow &ro
 // Rows of more than 1024 in-edges (by their class).  The sum of such a row is
 // that of strided parts, part p adding entries p, p + parts, ... in order: the
 // parts of 64 neighbours fold with the butterfly of a wave, and the folds are
-// added in order.  A row has kBlock parts, or, in FP64 with more than kLongRow
-// in-edges, kLongParts.  The resident loop gives such a long row a workgroup
+// added in order, or, the 16 of a long row, in pairs (one after the other they
+// round 15 times at the size of the sum, where four folds round 3 times).  A
+// row has kBlock parts, or, in FP64 with more than kLongRow in-edges,
+// kLongParts.  The resident loop gives such a long row a workgroup
 // of kLongParts threads, because one of 10^4 in-edges in 256 parts was the
 // last thing every iteration waited for (13 us of 26 on R-MAT scale 18);
 // kBlock threads take its parts in four passes, which sums the same bits.
@@ -697,12 +699,16 @@ __device__ __forceinline__ void block_row(const IterArgs &a, const Hub &hub, int
         }
     }
     __syncthreads();
+    double r = 0.0;
+    if (active && lng && t < kWave) {
+        r = red[t % kLongFolds];
+#pragma unroll
+        for (int off = 1; off < kLongFolds; off *= 2) r += __shfl_xor(r, off, kWave);
+    }
     if (t == 0) {
         *flag = 0;
         if (active) {
-            double r = ((red[0] + red[1]) + red[2]) + red[3];
-            if (lng)
-                for (int w = kBlock / kWave; w < kLongFolds; w++) r += red[w];
+            if (!lng) r = ((red[0] + red[1]) + red[2]) + red[3];
             *flag = finish_row<DF, F32, COH>(a, v, cnt, r, ld<COH>(a.Rc + v), a.out_cnt[v],
                                              DF && COH ? ld<COH>(a.xstamp + v) : 0u, acc)
                         ? 1 : 0;
