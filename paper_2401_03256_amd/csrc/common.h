@@ -208,6 +208,8 @@ struct dfpr_graph {
                                       // below 1024 << k
     int cus = 0;                      // compute units: workgroups of a resident loop at most
     uint32_t res_tag = 0;             // last barrier tag handed to a resident loop
+    uint32_t long_row = 0;            // in-edges above which FP64 rows are summed in more
+                                      // parts (block_row in iter.h), set at load
     uint32_t sparse_limit = 0;        // frontier size that switches to the full schedule
 };
 

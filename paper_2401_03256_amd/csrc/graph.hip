@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "common.h"
+#include "resident.h"
 
 namespace dfpr {
 
@@ -703,6 +704,7 @@ int dfpr_load_graph(int32_t n, int64_t m, const int32_t *src, const int32_t *dst
         hipError_t e = hipMemcpyAsync(g->ctl, &c0, sizeof(Ctl), hipMemcpyHostToDevice, g->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
         if (e != hipSuccess) rc = hip_fail(e, "hipMemcpy");
+        g->long_row = g->m > kResEdges ? 0xFFFFFFFFu : kLongRow;
         g->sparse_limit = (uint32_t)std::max<int64_t>(4096, n / 64);
     }
     if (!rc) rc = launch_fill_u32(g, g->stamp, (uint64_t)n, 0);

@@ -171,6 +171,7 @@ struct IterArgs {
     uint32_t sparse_limit;
     int32_t it, max_iters;
     int32_t n_stride;
+    uint32_t long_row;          // FP64 rows of more in-edges take kLongParts parts
     uint32_t hub;               // contributions to copy into LDS (0: none)
     struct Stage *stage;        // resident loop: the workgroup's new list entries
 };
@@ -660,6 +661,11 @@ __device__ __forceinline__ void finish_unit(const IterArgs &a, const UnitRow &ro
 // (launches) 29.97 against 30.80 / 30.03.
 // The FP32 form keeps kBlock parts: with more, its Kahan sums would round
 // differently.
+// So does every row of a graph that is too large for the resident loop when it
+// is loaded (dfpr_graph::long_row): in launches four passes are only slower.
+// R-MAT with 2.5e6 vertices, 41.7M edges: a sweep 233.4 -> 231.3 us (228.8
+// before there were long rows), Static 15.89 -> 15.76 ms; scale 22 24.16 ->
+// 24.0 ms.
 constexpr uint32_t kLongRow = 2048;
 constexpr int kLongParts = 1024;
 constexpr int kLongFolds = kLongParts / kWave;
@@ -681,7 +687,7 @@ __device__ __forceinline__ void block_row(const IterArgs &a, const Hub &hub, int
     if (active) {
         cnt = a.in_cnt[v];
     }
-    const bool lng = !F32 && cnt > kLongRow;
+    const bool lng = !F32 && cnt > a.long_row;
     if (active) {
         const int32_t *idx = a.in_idx + a.in_beg[v];
         auto pass = [&](uint32_t q, auto step) {
@@ -899,7 +905,7 @@ __device__ __forceinline__ void make_plan_wave(const IterArgs &a, const Ctl *ctl
         nlong = 0;
         for (uint32_t u0 = 0; u0 < nbu; u0 += kWave) {
             const unsigned long long m =
-                __ballot(u0 + lane < nbu && a.in_cnt[first + u0 + lane] > kLongRow);
+                __ballot(u0 + lane < nbu && a.in_cnt[first + u0 + lane] > a.long_row);
             if (m) nlong = u0 + kWave - __clzll((long long)m);
         }
         auto rounds = [&](uint32_t w) {

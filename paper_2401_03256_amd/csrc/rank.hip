@@ -1001,6 +1001,7 @@ IterArgs iter_args(dfpr_graph *g, const dfpr_params &p, uint32_t sbase)
     a.ftol = p.frontier_tol;
     a.sbase = sbase;
     a.sparse_limit = g->sparse_limit;
+    a.long_row = g->long_row;
     a.max_iters = p.max_iters;
     a.n_stride = g->n;
     // In the asynchronous form too: a copy taken when a workgroup starts

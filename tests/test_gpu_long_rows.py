@@ -41,3 +41,29 @@ def test_folds_of_a_long_row(dfpr, leaves, first):
         R, _ = g.naive_dynamic(prev, dfpr.params(alpha=0.5, max_iters=1, loop=loop))
         err = abs(float(np.longdouble(R[0]) - exact)) * 2.0 ** 53
         assert err <= 2.5, (loop, err)
+
+
+def test_long_rows_above_the_resident_line(dfpr):
+    """A graph of more than 40M in-edges, whose calls iterate in the resident
+    loop while on the class lists and in launches after: the long row of a
+    vertex that both process has the same parts in them."""
+    from paper_2401_03256_amd import synth
+    sys.stdout.write("\n[case] 41M edges and a hub of 9000\n")
+    sys.stdout.flush()
+    n, hub = 2_500_000, 9000
+    rng = np.random.default_rng(1)
+    src = np.concatenate([rng.integers(0, n, 41_000_000, dtype=np.int32), np.arange(1, hub + 1, dtype=np.int32)])
+    dst = np.concatenate([rng.integers(0, n, 41_000_000, dtype=np.int32), np.zeros(hub, np.int32)])
+    g = dfpr.Graph(n, src, dst)
+    assert g.m > 40_000_000
+    R, st = g.static()
+    want, _ = g.static(dfpr.params(loop=dfpr.LOOP_ITERATION))
+    assert st.converged and np.array_equal(R, want)
+    z = np.zeros(0, np.int32)
+    b = synth.Batch(z, z, np.array([5, 77], np.int32), np.array([n - 1, 0], np.int32))
+    g.apply_batch(b)
+    a, sa = g.dynamic_frontier(b, R, dfpr.params(frontier_tol=1e-13))
+    marks = g.affected()
+    c, sc = g.dynamic_frontier(b, R, dfpr.params(frontier_tol=1e-13, loop=dfpr.LOOP_ITERATION))
+    assert marks[0] and sa.iterations == sc.iterations and np.array_equal(a, c)
+    assert np.array_equal(marks, g.affected())
