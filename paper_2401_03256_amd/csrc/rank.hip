@@ -554,8 +554,8 @@ __global__ __launch_bounds__(kBeginThreads) void k_begin(IterArgs a, BeginArgs b
 // those reachable along G^t's out-edges from the batch sources and the
 // deletion targets.  A level-synchronous breadth-first search claims each
 // vertex once through its stamp (the call's base, so that it is processed
-// from the first iteration) and appends it to the next level's queue and,
-// with `append`, to its class list.  Vertices with more than kHeavyRow
+// from the first iteration) and appends it to the next level's queue (no class
+// lists: the iterations walk the full schedule).  Vertices with more than kHeavyRow
 // out-edges go to a separate queue whose out-rows the whole grid walks in
 // workgroup-sized chunks; the others are walked by waves, 64 at a time.
 // Three queues (of each kind) rotate: level L reads queue L mod 3, fills
@@ -570,14 +570,15 @@ struct BfsQueues {
 };
 
 // Every lane of the wave calls it; x < 0 claims nothing.  `deg` sums this
-// lane's claims' out-edges.
-__device__ inline void bfs_claim(const IterArgs &a, int32_t x, const BfsQueues &q, bool append,
+// lane's claims' out-edges (REACH).
+template <bool REACH>
+__device__ inline void bfs_claim(const IterArgs &a, int32_t x, const BfsQueues &q,
                                  unsigned long long &mine, unsigned long long &deg)
 {
     bool nw = false;
     if (x >= 0 && a.stamp[x] < a.sbase) nw = atomicMax(&a.stamp[x], a.sbase) < a.sbase;
     const uint32_t oc = nw ? a.out_cnt[x] : 0u;
-    deg += oc;
+    if (REACH) deg += oc;
     const bool big = oc > kHeavyRow;
     const unsigned long long ml = __ballot(nw && !big), mh = __ballot(big);
     const int lane = lane_id();
@@ -594,32 +595,30 @@ __device__ inline void bfs_claim(const IterArgs &a, int32_t x, const BfsQueues &
         if (nw && !big) q.out[bl + __popcll(ml & below)] = x;
         if (big) q.hout[bh + __popcll(mh & below)] = x;
     }
-    if (append) {
-        const int cls = nw ? class_of_id(a, x) : 0;
-        append_to_bins(nw, x, cls, a.ctl, a.bins, a.n_stride);
-    }
 }
 
-// A workgroup's claims (lane 0 of each wave holds `mine`) and their out-edges
-// into the control block.  Every thread calls it.
+// A workgroup's claims (lane 0 of each wave holds `mine`) and, with REACH,
+// their out-edges into the control block.  Every thread calls it.
+template <bool REACH>
 __device__ inline void bfs_totals(Ctl *ctl, unsigned long long mine, unsigned long long deg,
                                   unsigned long long &s_new, unsigned long long &s_reach)
 {
-    for (int off = kWave / 2; off > 0; off >>= 1) deg += __shfl_xor(deg, off, kWave);
+    if (REACH)
+        for (int off = kWave / 2; off > 0; off >>= 1) deg += __shfl_xor(deg, off, kWave);
     if (lane_id() == 0 && mine) {
         atomicAdd(&s_new, mine);
-        atomicAdd(&s_reach, deg);
+        if (REACH) atomicAdd(&s_reach, deg);
     }
     __syncthreads();
     if (threadIdx.x == 0 && s_new) {
         atomicAdd(&ctl->affected0, s_new);
-        atomicAdd(&ctl->reach, s_reach);
+        if (REACH) atomicAdd(&ctl->reach, s_reach);
     }
 }
 
 __global__ __launch_bounds__(kBlock) void k_bfs_seed(IterArgs a, int64_t nd, const int32_t *ds,
                                                      const int32_t *dd, int64_t ni,
-                                                     const int32_t *is, BfsQueues q, int append)
+                                                     const int32_t *is, BfsQueues q)
 {
     __shared__ unsigned long long s_new, s_reach;
     if (a.ctl->err) return;
@@ -632,16 +631,19 @@ __global__ __launch_bounds__(kBlock) void k_bfs_seed(IterArgs a, int64_t nd, con
     for (int64_t b0 = wave * kWave; b0 < nd + ni; b0 += waves * kWave) {
         const int64_t i = b0 + lane;
         const int32_t u = i < nd + ni ? (i < nd ? ds[i] : is[i - nd]) : -1;
-        bfs_claim(a, u, q, append != 0, mine, deg);
-        bfs_claim(a, i < nd ? dd[i] : -1, q, append != 0, mine, deg);
+        bfs_claim<false>(a, u, q, mine, deg);
+        bfs_claim<false>(a, i < nd ? dd[i] : -1, q, mine, deg);
     }
-    bfs_totals(a.ctl, mine, deg, s_new, s_reach);
+    bfs_totals<false>(a.ctl, mine, deg, s_new, s_reach);
 }
 
 // One level.  Light vertices: each wave takes 64 and walks their out-edges
 // together, one out-edge per lane and round.  Heavy vertices: every
-// workgroup takes chunks of kBlock out-edges of each of them.
-__global__ __launch_bounds__(kBlock) void k_bfs_level(IterArgs a, BfsQueues q, int append)
+// workgroup takes chunks of kBlock out-edges of each of them.  REACH: the
+// out-edges of its claims are summed too (the level before a look by the host;
+// in each of the thousands of levels of a grid the sum cost 4% of a search).
+template <bool REACH>
+__global__ __launch_bounds__(kBlock) void k_bfs_level(IterArgs a, BfsQueues q)
 {
     __shared__ unsigned long long s_new, s_reach;
     if (a.ctl->err) return;
@@ -655,7 +657,7 @@ __global__ __launch_bounds__(kBlock) void k_bfs_level(IterArgs a, BfsQueues q, i
     const int lane = lane_id();
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
     const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
-    unsigned long long mine = 0, reach = 0;
+    unsigned long long mine = 0, claimed = 0;
     for (int64_t b0 = wave * kWave; b0 < nin; b0 += waves * kWave) {
         const int64_t i = b0 + lane;
         const int32_t x = i < nin ? q.in[i] : -1;
@@ -678,12 +680,12 @@ __global__ __launch_bounds__(kBlock) void k_bfs_level(IterArgs a, BfsQueues q, i
             const uint32_t first = __shfl(incl, j) - __shfl(deg, j);
             const uint32_t base = __shfl(ob, j);
             const int32_t y = t < total ? a.out_idx[base + (tt - first)] : -1;
-            bfs_claim(a, y, q, append != 0, mine, reach);
+            bfs_claim<REACH>(a, y, q, mine, claimed);
         }
     }
     __shared__ HeavyShared hs;
-    walk_heavy(a, q.hin, nh, hs, [&](int32_t x) { bfs_claim(a, x, q, append != 0, mine, reach); });
-    bfs_totals(a.ctl, mine, reach, s_new, s_reach);
+    walk_heavy(a, q.hin, nh, hs, [&](int32_t x) { bfs_claim<REACH>(a, x, q, mine, claimed); });
+    bfs_totals<REACH>(a.ctl, mine, claimed, s_new, s_reach);
 }
 
 // A wide level.  Appending hundreds of thousands of vertices to the queues
@@ -1168,8 +1170,10 @@ static int launch_resident(dfpr_graph *g, IterArgs a, bool df, bool f32, int it0
     return DFPR_OK;
 }
 
+// `lists`: a Dynamic Frontier call, which may be on the class lists (Dynamic
+// Traversal is on the full schedule throughout).
 static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint32_t sbase,
-                    int it0, int base, int *res_buf, Close *close = nullptr)
+                    int it0, int base, int *res_buf, Close *close, bool lists)
 {
     IterArgs a = iter_args(g, p, sbase);
     const bool async = p.mode == DFPR_ASYNC && !f32;
@@ -1199,8 +1203,8 @@ static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint
     // calls keep a launch per iteration.
     const bool device_loop = p.loop == DFPR_LOOP_DEVICE;
     const bool full = !device_loop && g->m <= kResEdges;
-    const bool resident = device_loop ? df
-                          : p.loop != DFPR_LOOP_ITERATION && !g->prof.enabled && (full || df);
+    const bool resident = device_loop ? lists
+                          : p.loop != DFPR_LOOP_ITERATION && !g->prof.enabled && (full || lists);
     if (!async && resident) {
         const uint32_t limit = device_loop ? kLoopRows : 0xFFFFFFFFu;
         while (next_it < p.max_iters) {
@@ -1446,7 +1450,7 @@ static int full_sweeps(dfpr_graph *g, const dfpr_params *pp, const double *prev,
     DFPR_HIP(hipEventRecord(g->ev_mid, s));
     Close close;
     if (ranks_out) close.out = out_dev ? ranks_out : g->Rx;
-    rc = run_loop(g, p, false, false, 0, 0, cur, &res, &close);
+    rc = run_loop(g, p, false, false, 0, 0, cur, &res, &close, false);
     if (rc) return rc;
     g->cur = res;
     if (!close.done) {
@@ -1612,7 +1616,7 @@ static int df_impl(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32
     int res = cur;
     if (p.precision == DFPR_FP32_KAHAN) {
         // FP32 phase on FP32 copies of the contributions
-        rc = run_loop(g, p, true, true, sbase, 0, cur, &res);
+        rc = run_loop(g, p, true, true, sbase, 0, cur, &res, nullptr, true);
         if (rc) return rc;
         if (g->ctl_host->err)
             return set_error(DFPR_E_RANGE, "vertex id outside [0, n) in the batch");
@@ -1621,12 +1625,12 @@ static int df_impl(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32
         if (rc) return rc;
         if (!done) {
             const int it0 = g->ctl_host->iterations;
-            rc = run_loop(g, p, true, false, sbase, it0, res, &res, &close);
+            rc = run_loop(g, p, true, false, sbase, it0, res, &res, &close, true);
             if (rc) return rc;
             g->refine_sweeps = g->ctl_host->iterations - it0;
         }
     } else {
-        rc = run_loop(g, p, true, false, sbase, 0, cur, &res, &close);
+        rc = run_loop(g, p, true, false, sbase, 0, cur, &res, &close, true);
         if (rc) return rc;
     }
     return df_end(g, sbase, res, close, ranks_out, on_device, st);
@@ -1673,7 +1677,7 @@ static BfsQueues bfs_queues(dfpr_graph *g, int64_t L)
 // deletion targets, then levels in chunks between host looks, until a
 // level queues nothing.  Reached vertices end with stamp a.sbase.
 static int traverse(dfpr_graph *g, const IterArgs &a, int64_t nd, const int32_t *bds,
-                    const int32_t *bdd, int64_t ni, const int32_t *bis, bool append)
+                    const int32_t *bdd, int64_t ni, const int32_t *bis)
 {
     const int32_t n = g->n;
     hipStream_t s = g->stream;
@@ -1682,12 +1686,12 @@ static int traverse(dfpr_graph *g, const IterArgs &a, int64_t nd, const int32_t 
     // (which reads and clears nothing)
     BfsQueues q0 = bfs_queues(g, 2);
     k_bfs_seed<<<std::min(blocks_for(nd + ni), 2048), kBlock, 0, s>>>(a, nd, bds, bdd, ni, bis,
-                                                                   q0, append ? 1 : 0);
+                                                                   q0);
     DFPR_HIP(hipGetLastError());
     uint32_t grid = (uint32_t)g->grid;
     int chunk = 1;
     bool wide = false, was_wide = false;
-    unsigned long long reach = 0;       // out-edges of the claimed vertices, at the last look
+    unsigned long long reach = 0;       // Ctl::reach at the last look
     // every level, narrow or wide, reaches a vertex or is the last
     for (int64_t L = 0;;) {
         if (wide) {
@@ -1698,8 +1702,10 @@ static int traverse(dfpr_graph *g, const IterArgs &a, int64_t nd, const int32_t 
                 k_bfs_heavy<<<1024, kBlock, 0, s>>>(a, q.hout, q.nhout);
             }
         } else {
-            for (int j = 0; j < chunk; j++, L++)
-                k_bfs_level<<<grid, kBlock, 0, s>>>(a, bfs_queues(g, L), append ? 1 : 0);
+            for (int j = 0; j < chunk; j++, L++) {
+                auto *level = j == chunk - 1 ? k_bfs_level<true> : k_bfs_level<false>;
+                level<<<grid, kBlock, 0, s>>>(a, bfs_queues(g, L));
+            }
         }
         DFPR_HIP(hipGetLastError());
         DFPR_CHECK_RC(ctl_to_host(g));
@@ -1717,11 +1723,11 @@ static int traverse(dfpr_graph *g, const IterArgs &a, int64_t nd, const int32_t 
             chunk = 1;
             continue;
         }
-        // the levels to come are wide once the claims of a level, on average
-        // over the chunk, have more out-edges than a quarter of the vertices
-        // (a grid of 2048 x 2048 vertices reaches that with the 16 levels of a
-        // chunk together: 24.5 ms a call, and 26.0 with wide levels)
-        wide = !append && c.reach - reach > (unsigned long long)n / 4 * (unsigned)chunk;
+        // the levels to come are wide once the claims of one, the last, have
+        // more out-edges than a quarter of the vertices (a grid of 2048 x 2048
+        // vertices reaches that with the 16 levels of a chunk together: 24.5 ms
+        // a call, and 26.0 with wide levels)
+        wide = c.reach - reach > (unsigned long long)n / 4;
         was_wide |= wide;
         reach = c.reach;
         grid = bfs_grid(g, next, nexth);
@@ -1771,7 +1777,7 @@ static int dt_impl(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32
     DFPR_CHECK_RC(launch_begin(g, a, BeginArgs{}, prev, on_device, false, false));
     if (nd + ni > 0) {
         k_validate<<<blocks_for(nd + ni), kBlock, 0, s>>>(n, nd, bds, bdd, ni, bis, bid, g->ctl);
-        rc = traverse(g, a, nd, bds, bdd, ni, bis, false);
+        rc = traverse(g, a, nd, bds, bdd, ni, bis);
         if (rc) return rc;
     }
     // the reachable set is usually most of the graph: the iterations walk
@@ -1783,7 +1789,7 @@ static int dt_impl(dfpr_graph *g, const dfpr_params *pp, int64_t nd, const int32
     int res = cur;
     Close close;
     if (ranks_out) close.out = on_device ? ranks_out : g->Rx;
-    rc = run_loop(g, p, true, false, sbase, 0, cur, &res, &close);
+    rc = run_loop(g, p, true, false, sbase, 0, cur, &res, &close, false);
     if (rc) return rc;
     return df_end(g, sbase, res, close, ranks_out, on_device, st);
 }
@@ -1903,7 +1909,7 @@ int dfpr_mark_reachable(dfpr_graph *g, int64_t n_del, const int32_t *del_src,
     k_reset<<<1, 1, 0, s>>>(g->ctl);
     DFPR_HIP(hipGetLastError());
     if (n_del + n_ins > 0) {
-        rc = traverse(g, a, n_del, bds, bdd, n_ins, bis, false);
+        rc = traverse(g, a, n_del, bds, bdd, n_ins, bis);
         if (rc) return rc;
     }
     return flags_to_caller(g, g->mstamp, sbase, sbase, flags_out);
