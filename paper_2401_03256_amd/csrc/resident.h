@@ -40,12 +40,15 @@ namespace dfpr {
 //
 // Where it is used.  Graphs of up to kResEdges in-edges run whole calls in
 // it, because their full sweep is short next to the launches or gains from
-// the larger LDS copy: against launches, an update pair takes 1.21 / 2.15 ms on
-// a 10,000-vertex G(n, m), 8.5 / 12.9 ms on R-MAT scale 20 and 14.1 / 16.8 ms
-// on scale 21 (35M edges).  On scale 22 (69M) its 16 waves per compute unit
-// and gathers past the vector L1 lose to k_iter_wide (32.9 / 30.1 ms), so
-// larger graphs use it only while a Dynamic Frontier call is on the class
-// lists.
+// the larger LDS copy.  Static and a Dynamic Frontier call of 1e-5 of the edges,
+// launches over resident loop: R-MAT with 16M / 25M / 33M / 39M edges 1.61 / 1.41
+// / 1.31 / 1.14 and 1.52 / 1.32 / 1.22 / 1.16; grids with 20M / 29M / 39M 1.36 /
+// 1.21 / 1.12 and 2.8; G(n, m) with 17M / 26M / 35M 1.05 / 1.00 / 1.00 and 1.12 /
+// 1.07 / 1.06 at 13 edges a vertex, 1.26 / 1.02 / 0.99 and 0.99 / 0.93 / 0.98 at
+// 24, where one iteration marks most vertices with stores that go past L2.  On
+// R-MAT scale 22 (69M) its 16 waves per compute unit and gathers past the vector
+// L1 lose to k_iter_wide (32.9 and 30.1 ms an update pair), so larger graphs use
+// it only while a Dynamic Frontier call is on the class lists.
 constexpr int64_t kResEdges = 40000000;
 // In the resident loop a row goes to a class list by an LDS-staged append, so
 // the lists may hold an eighth of the vertices before walking every id range
