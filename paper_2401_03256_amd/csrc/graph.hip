@@ -220,9 +220,9 @@ __global__ __launch_bounds__(kBlock) void k_sort_scatter(const uint64_t *key, ui
         // the wave runs in step: every lane reads the count before the first
         // lane of each digit adds to it
         const uint32_t c = ok ? (uint32_t)at[wave][d] : 0u;
-        __builtin_amdgcn_wave_barrier();
+        wave_fence();
         if (ok && rank == 0) at[wave][d] = c + (uint32_t)__popcll(m);
-        __builtin_amdgcn_wave_barrier();
+        wave_fence();
         before[r] = c + rank;
     }
     __syncthreads();

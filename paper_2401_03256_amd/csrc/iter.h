@@ -94,6 +94,15 @@ __device__ __forceinline__ void drain_stores()
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// What the lanes of a wave left in LDS before is there for all of them after: the
+// hardware runs a wave's accesses in order, the fence keeps the compiler from
+// moving them.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Whether this is the last workgroup of the grid to get here; the others'
 // atomics and agent-scope stores before the call are then visible to its
 // agent-scope loads.  Every thread calls it.  A workgroup arrives at one of

@@ -328,7 +328,7 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
                                                   : ld<true>(&a.ctl->force_dense);
                 dr = wave_max<kWave>(dr);
                 if (F32) rm = wave_max<kWave>(rm);
-                __builtin_amdgcn_wave_barrier();
+                wave_fence();
                 if (lane == 0) {
                     final_step(a, &rs.ctl, rs.lists, sparse, F32, dr, rm);
                     const bool end = rs.fail || rs.ctl.done || (F32 && rs.ctl.phase_end);
@@ -341,10 +341,10 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
                     if (P.budget && wall_clock64() - t0_clock > P.budget) out |= 1u;
                     rs.state[0] = out;
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_fence();
                 if (lane < kBins) rs.state[1 + lane] = rs.ctl.snap[(it & 1) ^ 1][lane];
                 static_assert(kResCopies * 8 == kWave, "a lane per published word");
-                __builtin_amdgcn_wave_barrier();
+                wave_fence();
                 st<true>(&P.w->state[lane], tagged(rs.state[lane & 7], tag));
             }
             __syncthreads();
