@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "common.h"
+#include "launch.h"
 #include "resident.h"
 
 namespace dfpr {
@@ -105,11 +106,12 @@ struct LoadInfo {
 __global__ void k_load_degrees(int32_t n, int64_t m, const int32_t *src, const int32_t *dst,
                                uint32_t *deg, LoadInfo *info)
 {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    const int32_t u = src[i], v = dst[i];
-    if (u < 0 || u >= n || v < 0 || v >= n) info->err = 1;
-    else atomicAdd(&deg[v], 1u);
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t u = src[i], v = dst[i];
+        if (u < 0 || u >= n || v < 0 || v >= n) info->err = 1;
+        else atomicAdd(&deg[v], 1u);
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_load_max(int32_t n, const uint32_t *deg, LoadInfo *info)
@@ -155,9 +157,10 @@ __global__ void k_load_maps(int32_t n, const uint64_t *key, uint32_t dmax, int32
 __global__ void k_load_edge_keys(int32_t n, int64_t m, const int32_t *src, const int32_t *dst,
                                  const int32_t *ext2int, int b, uint64_t *key)
 {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < m) key[i] = (uint64_t)ext2int[src[i]] << b | (uint64_t)ext2int[dst[i]];
-    else if (i < m + n) key[i] = (uint64_t)(i - m) << b | (uint64_t)(i - m);
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m + n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        key[i] = i < m ? (uint64_t)ext2int[src[i]] << b | (uint64_t)ext2int[dst[i]]
+                       : (uint64_t)(i - m) << b | (uint64_t)(i - m);
 }
 
 // One pass of a stable radix sort over digits of at most 8 bits.  A workgroup
@@ -270,18 +273,20 @@ __global__ __launch_bounds__(kBlock) void k_load_distinct(const uint64_t *key, u
 
 __global__ void k_load_swap(uint64_t len, int b, const uint64_t *key, uint64_t *out)
 {
-    const uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    if (i < len) out[i] = (key[i] & ((1ull << b) - 1)) << b | key[i] >> b;
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < len;
+         i += (uint64_t)gridDim.x * blockDim.x)
+        out[i] = (key[i] & ((1ull << b) - 1)) << b | key[i] >> b;
 }
 
 // First key of every row (each row holds at least its self-loop).
 __global__ void k_load_starts(uint64_t len, int b, int32_t n, const uint64_t *key, uint64_t *start)
 {
-    const uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    if (i >= len) return;
-    const uint64_t r = key[i] >> b;
-    if (i == 0 || (key[i - 1] >> b) != r) start[r] = i;
-    if (i == 0) start[n] = len;
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < len;
+         i += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t r = key[i] >> b;
+        if (i == 0 || (key[i - 1] >> b) != r) start[r] = i;
+        if (i == 0) start[n] = len;
+    }
 }
 
 __global__ void k_load_caps(int32_t n, const uint64_t *start, uint32_t *cnt, uint32_t *cap,
@@ -315,10 +320,11 @@ __global__ void k_load_begs(int32_t n, const uint64_t *at, uint32_t *beg, int o,
 __global__ void k_load_rows(uint64_t len, int b, const uint64_t *key, const uint64_t *start,
                             const uint32_t *beg, int32_t *idx)
 {
-    const uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    if (i >= len) return;
-    const uint64_t r = key[i] >> b;
-    idx[(uint64_t)beg[r] + (i - start[r])] = (int32_t)(key[i] & ((1ull << b) - 1));
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < len;
+         i += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t r = key[i] >> b;
+        idx[(uint64_t)beg[r] + (i - start[r])] = (int32_t)(key[i] & ((1ull << b) - 1));
+    }
 }
 
 // Device memory of a scope.
@@ -362,6 +368,9 @@ static int sort_keys(hipStream_t s, uint64_t *&key, uint64_t *&tmp, uint64_t len
     return DFPR_OK;
 }
 
+// Workgroups of a kernel that strides over the edges.
+static inline unsigned edge_grid(uint64_t items) { return stride_blocks(items, kBlock); }
+
 // Build the numbering and both CSRs of g from m input edges (host arrays), on
 // g->stream.  top[o] receives the first free slot of each index array.
 static int build_graph(dfpr_graph *g, int64_t m, const int32_t *src, const int32_t *dst, uint32_t top[2])
@@ -399,7 +408,7 @@ static int build_graph(dfpr_graph *g, int64_t m, const int32_t *src, const int32
         DFPR_HIP(hipMemcpyAsync(ed, dst, (size_t)m * 4, hipMemcpyHostToDevice, s));
     }
     DFPR_CHECK_RC(launch_fill_u32(g, deg, (uint64_t)n, 1));
-    if (m) k_load_degrees<<<grid_of(m), kBlock, 0, s>>>(n, m, es, ed, deg, info);
+    if (m) k_load_degrees<<<edge_grid((uint64_t)m), kBlock, 0, s>>>(n, m, es, ed, deg, info);
     k_load_max<<<std::min(grid_of(n), 1024u), kBlock, 0, s>>>(n, deg, info);
     LoadInfo got;
     DFPR_HIP(hipMemcpyAsync(&got, info, sizeof(got), hipMemcpyDeviceToHost, s));
@@ -411,11 +420,11 @@ static int build_graph(dfpr_graph *g, int64_t m, const int32_t *src, const int32
     // numbering
     k_load_vertex_keys<<<grid_of(n), kBlock, 0, s>>>(n, deg, got.dmax, key);
     int dbits = 1;
-    while (got.dmax >> dbits) dbits++;
+    while ((uint64_t)got.dmax >> dbits) dbits++;
     DFPR_CHECK_RC(sort_keys(s, key, tmp, (uint64_t)n, 32, dbits, counts, sums));
     k_load_maps<<<grid_of(n), kBlock, 0, s>>>(n, key, got.dmax, g->ext2int, g->int2ext, info);
     // out-rows: distinct edges by source, then target
-    k_load_edge_keys<<<grid_of((int64_t)len), kBlock, 0, s>>>(n, m, es, ed, g->ext2int, b, key);
+    k_load_edge_keys<<<edge_grid(len), kBlock, 0, s>>>(n, m, es, ed, g->ext2int, b, key);
     DFPR_CHECK_RC(sort_keys(s, key, tmp, len, 0, 2 * b, counts, sums));
     k_load_distinct<<<(unsigned)tiles, kBlock, 0, s>>>(key, len, counts, nullptr);
     DFPR_HIP(hipMemsetAsync(counts + tiles, 0, 8, s));
@@ -432,12 +441,12 @@ static int build_graph(dfpr_graph *g, int64_t m, const int32_t *src, const int32
         Scratch second;
         DFPR_CHECK_RC(second.take(edges * 8));
         uint64_t *x = key, *y = (uint64_t *)second.p;
-        k_load_swap<<<grid_of((int64_t)edges), kBlock, 0, s>>>(edges, b, rows[1], x);
+        k_load_swap<<<edge_grid(edges), kBlock, 0, s>>>(edges, b, rows[1], x);
         DFPR_CHECK_RC(sort_keys(s, x, y, edges, b, b, counts, sums));
         rows[0] = x;
         for (int o = 0; o < 2; o++) {
             Csr &c = g->csr[o];
-            k_load_starts<<<grid_of((int64_t)edges), kBlock, 0, s>>>(edges, b, n, rows[o], start[o]);
+            k_load_starts<<<edge_grid(edges), kBlock, 0, s>>>(edges, b, n, rows[o], start[o]);
             k_load_caps<<<grid_of((int64_t)n + 1), kBlock, 0, s>>>(n, start[o], c.cnt, c.cap, counts, o,
                                                                   info);
             scan_u64(s, counts, (uint64_t)n + 1, sums);
@@ -454,7 +463,7 @@ static int build_graph(dfpr_graph *g, int64_t m, const int32_t *src, const int32
             c.max_cap = got.max_cap[o];
             top[o] = (uint32_t)got.packed[o];
             DFPR_HIP(hipMalloc(&c.idx, c.slots * 4));
-            k_load_rows<<<grid_of((int64_t)edges), kBlock, 0, s>>>(edges, b, rows[o], start[o], c.beg,
+            k_load_rows<<<edge_grid(edges), kBlock, 0, s>>>(edges, b, rows[o], start[o], c.beg,
                                                                   c.idx);
         }
         DFPR_HIP(hipGetLastError());

@@ -1,0 +1,71 @@
+"""Loads of more input edges than a launch has threads."""
+import ctypes
+import os
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dfpr():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2401_03256_amd import dfpr as mod
+    mod.lib()
+    return mod
+
+
+def _say(msg):
+    sys.stdout.write(f"\n[case] {msg}\n")
+    sys.stdout.flush()
+
+
+class _Repeated:
+    """`a` over and over as one array of host memory, whose pages are shared."""
+
+    def __init__(self, a, times):
+        libc = ctypes.CDLL(None, use_errno=True)
+        libc.mmap.restype = ctypes.c_void_p
+        libc.mmap.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int, ctypes.c_int, ctypes.c_int,
+                              ctypes.c_long]
+        libc.munmap.argtypes = [ctypes.c_void_p, ctypes.c_size_t]
+        self.libc, self.bytes = libc, a.nbytes * times
+        fd = os.memfd_create("edges")
+        os.write(fd, a.tobytes())
+        prot, shared, private, fixed, anon = 1, 1, 2, 16, 32
+        self.at = libc.mmap(None, self.bytes, 0, private | anon, -1, 0)
+        assert self.at not in (None, ctypes.c_void_p(-1).value)
+        for k in range(times):
+            p = libc.mmap(self.at + k * a.nbytes, a.nbytes, prot, shared | fixed, fd, 0)
+            assert p == self.at + k * a.nbytes
+        os.close(fd)
+
+    def close(self):
+        self.libc.munmap(self.at, self.bytes)
+
+
+def test_more_input_edges_than_a_launch_has_threads(dfpr):
+    """2^32 + 2^24 input edges, 2^24 distinct ones 257 times."""
+    _say("2^32 + 2^24 input edges")
+    n, part, times = 1 << 20, 1 << 24, 257
+    rng = np.random.default_rng(3)
+    src = rng.integers(0, n, part, dtype=np.int32)
+    dst = rng.integers(0, n, part, dtype=np.int32)
+    many = [_Repeated(x, times) for x in (src, dst)]
+    h = ctypes.c_void_p()
+    try:
+        rc = dfpr.lib().dfpr_load_graph(n, part * times, many[0].at, many[1].at, ctypes.byref(h))
+        assert rc == 0, dfpr.lib().dfpr_last_error().decode()
+    finally:
+        for x in many:
+            x.close()
+    got = dfpr.Graph.__new__(dfpr.Graph)
+    got._h, got.n = h, n
+    want = dfpr.Graph(n, src, dst)
+    assert got.m == want.m
+    for out in (True, False):
+        for x, y in zip(got.csr(out), want.csr(out)):
+            assert np.array_equal(x, y)
