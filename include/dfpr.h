@@ -157,6 +157,9 @@ void dfpr_params_default(dfpr_params *p);
  * Internally the library renumbers the vertices by decreasing in-degree;
  * every id, rank and flag passed to or returned by any call stays in the
  * caller's numbering.
+ * Loading takes 16.5 bytes an input edge and 37 a vertex beside the graph, given
+ * back before the call returns: device memory, or pinned host memory if the
+ * device has room for the graph alone (the load is then slower).
  * *out receives a handle owned by the library (free with dfpr_free_graph).
  * Errors: DFPR_E_ARG, DFPR_E_RANGE (id outside [0, n)), DFPR_E_NOMEM,
  * DFPR_E_LIMIT (more than 2^32 - 1 edge slots). */

@@ -67,6 +67,8 @@ __host__ __device__ static inline uint64_t row_capacity(uint64_t deg)
     return deg + (deg / 8 > 2 ? deg / 8 : 2);
 }
 
+constexpr uint64_t kMaxEdgeSlots = 0xFFFFFFFFull;   // of an index array (32-bit offsets)
+
 // Free slots kept after the packed rows for rows that outgrow their slack.
 static inline uint64_t spill_reserve(uint64_t packed)
 {
@@ -87,8 +89,12 @@ static inline unsigned grid_of(int64_t items)
 // in-rows.  Bound: the radix passes, each two reads and a write of the keys;
 // on small graphs their launches.
 // A load with its allocations, against the same on one host core: R-MAT scale
-// 16 (1.1M keys) 1.1 and 22.9 ms, scale 20 9.8 and 572 ms, scale 22 35 and
+// 16 (1.1M keys) 1.2 and 22.9 ms, scale 20 9.4 and 572 ms, scale 22 34 and
 // 2443 ms, of which the copy of the edge list takes 18.
+// Memory: beside the graph, 16.5 bytes an input edge and 37 a vertex, on the
+// device or, where that has no room for it, in pinned host memory, which the
+// same kernels then work in over the bus.  What they update with atomics is in
+// the graph's own arrays, so that the rest may be host memory.
 
 // What the host needs back from the build.
 struct LoadInfo {
@@ -327,13 +333,20 @@ __global__ void k_load_rows(uint64_t len, int b, const uint64_t *key, const uint
     }
 }
 
-// Device memory of a scope.
+// Memory of a scope, device or pinned host.
 struct Scratch {
     void *p = nullptr;
-    ~Scratch() { (void)hipFree(p); }
-    int take(size_t bytes)
+    bool host = false;
+    ~Scratch()
     {
-        DFPR_HIP(hipMalloc(&p, std::max<size_t>(bytes, 256)));
+        if (host) (void)hipHostFree(p);
+        else (void)hipFree(p);
+    }
+    int take(size_t bytes, bool on_host)
+    {
+        host = on_host;
+        if (host) DFPR_HIP(hipHostMalloc(&p, bytes, hipHostMallocDefault));
+        else DFPR_HIP(hipMalloc(&p, bytes));
         return DFPR_OK;
     }
 };
@@ -372,8 +385,10 @@ static int sort_keys(hipStream_t s, uint64_t *&key, uint64_t *&tmp, uint64_t len
 static inline unsigned edge_grid(uint64_t items) { return stride_blocks(items, kBlock); }
 
 // Build the numbering and both CSRs of g from m input edges (host arrays), on
-// g->stream.  top[o] receives the first free slot of each index array.
-static int build_graph(dfpr_graph *g, int64_t m, const int32_t *src, const int32_t *dst, uint32_t top[2])
+// g->stream, with scratch on the device or in host memory.  top[o] receives the
+// first free slot of each index array.
+static int build_graph(dfpr_graph *g, int64_t m, const int32_t *src, const int32_t *dst, bool host_scratch,
+                       uint32_t top[2])
 {
     const int32_t n = g->n;
     hipStream_t s = g->stream;
@@ -382,30 +397,29 @@ static int build_graph(dfpr_graph *g, int64_t m, const int32_t *src, const int32
     const uint64_t len = (uint64_t)m + (uint64_t)n;
     const uint64_t tiles = (len + kSortTile - 1) / kSortTile;
     const uint64_t scan_len = std::max<uint64_t>(tiles * kDigits, (uint64_t)n + 1);
+    // updated with atomics: in arrays of the graph that are set after the build
+    static_assert(sizeof(LoadInfo) <= 4096 * sizeof(double), "scratch_sum holds it");
+    LoadInfo *const info = reinterpret_cast<LoadInfo *>(g->scratch_sum);
+    uint32_t *const deg = g->stamp;
     Scratch mem;
-    LoadInfo *info = nullptr;
-    int32_t *es = nullptr, *ed = nullptr;
-    uint32_t *deg = nullptr;
     uint64_t *key = nullptr, *tmp = nullptr, *counts = nullptr, *sums = nullptr;
-    uint64_t *start[2] = {nullptr, nullptr};
+    uint64_t *start = nullptr, *vertex = nullptr;
     for (int pass = 0; pass < 2; pass++) {
         Carve c{(char *)mem.p, 0};
-        c(info, 1);
-        c(deg, n);
-        c(es, m);
-        c(ed, m);
         c(key, len);
         c(tmp, len);
         c(counts, scan_len);
         c(sums, scan_u64_sums(scan_len));
-        c(start[0], (uint64_t)n + 1);
-        c(start[1], (uint64_t)n + 1);
-        if (pass == 0) DFPR_CHECK_RC(mem.take(c.at));
+        c(start, (uint64_t)n + 1);
+        c(vertex, n);
+        if (pass == 0) DFPR_CHECK_RC(mem.take(c.at, host_scratch));
     }
+    // the input edges, in tmp until they are keys
+    int32_t *const es = reinterpret_cast<int32_t *>(tmp), *const ed = es + m;
     DFPR_HIP(hipMemsetAsync(info, 0, sizeof(LoadInfo), s));
     if (m) {
-        DFPR_HIP(hipMemcpyAsync(es, src, (size_t)m * 4, hipMemcpyHostToDevice, s));
-        DFPR_HIP(hipMemcpyAsync(ed, dst, (size_t)m * 4, hipMemcpyHostToDevice, s));
+        DFPR_HIP(hipMemcpyAsync(es, src, (size_t)m * 4, hipMemcpyDefault, s));
+        DFPR_HIP(hipMemcpyAsync(ed, dst, (size_t)m * 4, hipMemcpyDefault, s));
     }
     DFPR_CHECK_RC(launch_fill_u32(g, deg, (uint64_t)n, 1));
     if (m) k_load_degrees<<<edge_grid((uint64_t)m), kBlock, 0, s>>>(n, m, es, ed, deg, info);
@@ -418,12 +432,13 @@ static int build_graph(dfpr_graph *g, int64_t m, const int32_t *src, const int32
         return set_error(DFPR_E_RANGE, "vertex id outside [0, n)");
     }
     // numbering
-    k_load_vertex_keys<<<grid_of(n), kBlock, 0, s>>>(n, deg, got.dmax, key);
+    uint64_t *vkey = vertex, *vtmp = start;
+    k_load_vertex_keys<<<grid_of(n), kBlock, 0, s>>>(n, deg, got.dmax, vkey);
     int dbits = 1;
     while ((uint64_t)got.dmax >> dbits) dbits++;
-    DFPR_CHECK_RC(sort_keys(s, key, tmp, (uint64_t)n, 32, dbits, counts, sums));
-    k_load_maps<<<grid_of(n), kBlock, 0, s>>>(n, key, got.dmax, g->ext2int, g->int2ext, info);
-    // out-rows: distinct edges by source, then target
+    DFPR_CHECK_RC(sort_keys(s, vkey, vtmp, (uint64_t)n, 32, dbits, counts, sums));
+    k_load_maps<<<grid_of(n), kBlock, 0, s>>>(n, vkey, got.dmax, g->ext2int, g->int2ext, info);
+    // distinct edges by source, then target: the out-rows
     k_load_edge_keys<<<edge_grid(len), kBlock, 0, s>>>(n, m, es, ed, g->ext2int, b, key);
     DFPR_CHECK_RC(sort_keys(s, key, tmp, len, 0, 2 * b, counts, sums));
     k_load_distinct<<<(unsigned)tiles, kBlock, 0, s>>>(key, len, counts, nullptr);
@@ -432,43 +447,33 @@ static int build_graph(dfpr_graph *g, int64_t m, const int32_t *src, const int32
     k_load_distinct<<<(unsigned)tiles, kBlock, 0, s>>>(key, len, counts, tmp);
     DFPR_HIP(hipGetLastError());
     uint64_t edges = 0;
-    DFPR_HIP(hipMemcpyAsync(&edges, counts + tiles, 8, hipMemcpyDeviceToHost, s));
+    DFPR_HIP(hipMemcpyAsync(&edges, counts + tiles, 8, hipMemcpyDefault, s));
     DFPR_HIP(hipStreamSynchronize(s));
-    // in-rows: a stable sort of the distinct edges by target, into the two
-    // halves that the sort of the out-rows no longer needs
-    uint64_t *rows[2] = {nullptr, tmp};
-    {
-        Scratch second;
-        DFPR_CHECK_RC(second.take(edges * 8));
-        uint64_t *x = key, *y = (uint64_t *)second.p;
-        k_load_swap<<<edge_grid(edges), kBlock, 0, s>>>(edges, b, rows[1], x);
-        DFPR_CHECK_RC(sort_keys(s, x, y, edges, b, b, counts, sums));
-        rows[0] = x;
-        for (int o = 0; o < 2; o++) {
-            Csr &c = g->csr[o];
-            k_load_starts<<<edge_grid(edges), kBlock, 0, s>>>(edges, b, n, rows[o], start[o]);
-            k_load_caps<<<grid_of((int64_t)n + 1), kBlock, 0, s>>>(n, start[o], c.cnt, c.cap, counts, o,
-                                                                  info);
-            scan_u64(s, counts, (uint64_t)n + 1, sums);
-            k_load_begs<<<grid_of(n), kBlock, 0, s>>>(n, counts, c.beg, o, info);
+    std::swap(key, tmp);
+    for (int o = 1; o >= 0; o--) {
+        if (o == 0) {
+            // in-rows: a stable sort of the distinct edges by target
+            k_load_swap<<<edge_grid(edges), kBlock, 0, s>>>(edges, b, key, tmp);
+            std::swap(key, tmp);
+            DFPR_CHECK_RC(sort_keys(s, key, tmp, edges, b, b, counts, sums));
         }
+        Csr &c = g->csr[o];
+        k_load_starts<<<edge_grid(edges), kBlock, 0, s>>>(edges, b, n, key, start);
+        k_load_caps<<<grid_of((int64_t)n + 1), kBlock, 0, s>>>(n, start, c.cnt, c.cap, counts, o, info);
+        scan_u64(s, counts, (uint64_t)n + 1, sums);
+        k_load_begs<<<grid_of(n), kBlock, 0, s>>>(n, counts, c.beg, o, info);
         DFPR_HIP(hipGetLastError());
         DFPR_HIP(hipMemcpyAsync(&got, info, sizeof(got), hipMemcpyDeviceToHost, s));
         DFPR_HIP(hipStreamSynchronize(s));
-        for (int o = 0; o < 2; o++) {
-            Csr &c = g->csr[o];
-            c.slots = got.packed[o] + spill_reserve(got.packed[o]);
-            if (c.slots > 0xFFFFFFFFull)
-                return set_error(DFPR_E_LIMIT, "graph needs more than 2^32-1 edge slots");
-            c.max_cap = got.max_cap[o];
-            top[o] = (uint32_t)got.packed[o];
-            DFPR_HIP(hipMalloc(&c.idx, c.slots * 4));
-            k_load_rows<<<edge_grid(edges), kBlock, 0, s>>>(edges, b, rows[o], start[o], c.beg,
-                                                                  c.idx);
-        }
+        c.slots = got.packed[o] + spill_reserve(got.packed[o]);
+        if (c.slots > kMaxEdgeSlots) return set_error(DFPR_E_LIMIT, "graph needs more than 2^32-1 edge slots");
+        c.max_cap = got.max_cap[o];
+        top[o] = (uint32_t)got.packed[o];
+        DFPR_HIP(hipMalloc(&c.idx, c.slots * 4));
+        k_load_rows<<<edge_grid(edges), kBlock, 0, s>>>(edges, b, key, start, c.beg, c.idx);
         DFPR_HIP(hipGetLastError());
-        DFPR_HIP(hipStreamSynchronize(s));
     }
+    DFPR_HIP(hipStreamSynchronize(s));
     g->m = (int64_t)edges;
     for (int k = 0; k < kBins + 2; k++) g->cls[k] = got.cls[k];
     for (int k = 0; k < kHubSteps; k++) g->hub_share[k] = (double)got.hub[k] / (double)edges;
@@ -701,7 +706,18 @@ int dfpr_load_graph(int32_t n, int64_t m, const int32_t *src, const int32_t *dst
         else e = hipMemsetAsync((char *)g->arena + zero0, 0, zero1 - zero0, g->stream);
         if (e != hipSuccess) rc = hip_fail(e, "hipMalloc");
     }
-    if (!rc) rc = build_graph(g, m, src, dst, top);
+    if (!rc) {
+        rc = build_graph(g, m, src, dst, false, top);
+        if (rc == DFPR_E_NOMEM) {
+            // the graph may still fit without the scratch
+            (void)hipGetLastError();
+            for (Csr &c : g->csr) {
+                (void)hipFree(c.idx);
+                c.idx = nullptr;
+            }
+            rc = build_graph(g, m, src, dst, true, top);
+        }
+    }
     if (!rc) {
         Ctl c0;
         std::memset(&c0, 0, sizeof(c0));

@@ -1,10 +1,13 @@
-"""Loads of more input edges than a launch has threads."""
+"""Loads at their limits: more input edges than a launch has threads, and a device
+with room for the graph but not for the load's scratch."""
 import ctypes
 import os
 import sys
 
 import numpy as np
 import pytest
+
+from paper_2401_03256_amd import synth
 
 pytestmark = pytest.mark.gpu
 
@@ -21,6 +24,38 @@ def dfpr():
 def _say(msg):
     sys.stdout.write(f"\n[case] {msg}\n")
     sys.stdout.flush()
+
+
+def _same_graph(g, h):
+    assert g.m == h.m
+    for out in (True, False):
+        for x, y in zip(g.csr(out), h.csr(out)):
+            assert np.array_equal(x, y)
+    (a, sa), (b, sb) = g.static(), h.static()
+    assert sa.iterations == sb.iterations and np.array_equal(a, b)
+
+
+def test_load_beside_other_allocations(dfpr):
+    import torch
+    _say("load with 225 MB of the device free")
+    n, src, dst = synth.rmat(19, 16, seed=21)
+    want = dfpr.Graph(n, src, dst)              # 145 MB, and 190 MB more while it loads
+    torch.cuda.empty_cache()
+    ballast = []
+    for _ in range(200):
+        free = torch.cuda.mem_get_info()[0] - (225 << 20)
+        if free < 4 << 20:
+            break
+        ballast.append(torch.empty(min(free, 16 << 30), dtype=torch.uint8, device="cuda"))
+    free = torch.cuda.mem_get_info()[0] >> 20
+    _say(f"free now {free} MB")
+    assert 200 <= free <= 232
+    try:
+        got = dfpr.Graph(n, src, dst)
+    finally:
+        del ballast
+        torch.cuda.empty_cache()
+    _same_graph(got, want)
 
 
 class _Repeated:
