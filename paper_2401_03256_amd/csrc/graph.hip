@@ -427,10 +427,7 @@ static int build_graph(dfpr_graph *g, int64_t m, const int32_t *src, const int32
     LoadInfo got;
     DFPR_HIP(hipMemcpyAsync(&got, info, sizeof(got), hipMemcpyDeviceToHost, s));
     DFPR_HIP(hipStreamSynchronize(s));
-    if (got.err) {
-        DFPR_CHECK_RC(check_ids_host(n, m, src, dst));
-        return set_error(DFPR_E_RANGE, "vertex id outside [0, n)");
-    }
+    if (got.err) return set_error(DFPR_E_RANGE, "vertex id outside [0, n)");
     // numbering
     uint64_t *vkey = vertex, *vtmp = start;
     k_load_vertex_keys<<<grid_of(n), kBlock, 0, s>>>(n, deg, got.dmax, vkey);
@@ -642,6 +639,12 @@ int dfpr_load_graph(int32_t n, int64_t m, const int32_t *src, const int32_t *dst
     *out = nullptr;
     if (n <= 0 || m < 0 || (m > 0 && (!src || !dst)))
         return set_error(DFPR_E_ARG, "need n >= 1, m >= 0 and non-NULL edge arrays");
+    // every vertex has its self-loop
+    const uint64_t least = (uint64_t)n * row_capacity(1);
+    if (least + spill_reserve(least) > kMaxEdgeSlots) {
+        DFPR_CHECK_RC(check_ids_host(n, m, src, dst));
+        return set_error(DFPR_E_LIMIT, "graph needs more than 2^32-1 edge slots");
+    }
     dfpr_graph *g = new (std::nothrow) dfpr_graph();
     if (!g) return set_error(DFPR_E_NOMEM, "out of host memory");
     g->n = n;
@@ -741,6 +744,8 @@ int dfpr_load_graph(int32_t n, int64_t m, const int32_t *src, const int32_t *dst
     }
     if (rc) {
         dfpr_free_graph(g);
+        // a bad id is the error to report, and which one
+        DFPR_CHECK_RC(check_ids_host(n, m, src, dst));
         return rc;
     }
     *out = g;

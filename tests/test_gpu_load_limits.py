@@ -1,5 +1,6 @@
-"""Loads at their limits: more input edges than a launch has threads, and a device
-with room for the graph but not for the load's scratch."""
+"""Loads at their limits: more input edges than a launch has threads, a device
+with room for the graph but not for the load's scratch, and more vertices than
+edge slots."""
 import ctypes
 import os
 import sys
@@ -56,6 +57,14 @@ def test_load_beside_other_allocations(dfpr):
         del ballast
         torch.cuda.empty_cache()
     _same_graph(got, want)
+
+
+def test_more_vertices_than_slots(dfpr):
+    _say("2^31 - 1 vertices")
+    z = np.zeros(0, np.int32)
+    with pytest.raises(dfpr.DfprError) as e:
+        dfpr.Graph(2**31 - 1, z, z)
+    assert e.value.code == dfpr.DFPR_E_LIMIT
 
 
 class _Repeated:
