@@ -12,7 +12,8 @@ One step = apply the batch to both device CSRs + one Dynamic Frontier
 update (initial marking, iterations to convergence), with the batch already
 in device memory.  value = in-edges gathered by all timed updates divided by
 the wall time of the timed steps (GTEPS).  Latency p50/p99 are over the
-timed steps.
+timed steps.  The iteration kernel is profiled afterwards in the same steps on a
+second copy of the graph: profiled calls take a launch per iteration.
 
 Prints one JSON line on stdout; progress goes to stderr.
 """
@@ -186,7 +187,7 @@ def headline_bench(args, dfpr, synth):
     log(f"static: {st0.iterations} it, {st0.ms_device:.2f} ms device "
         f"({st0.edges_processed / st0.ms_device / 1e6:.1f} GTEPS)")
 
-    def step(i):
+    def step(i, g=g):
         g.apply_batch_device(*dev[i])
         return g.dynamic_frontier_device(*dev[i], p=p)
 
@@ -204,7 +205,6 @@ def headline_bench(args, dfpr, synth):
         log(f"warmup {i}: batch {seq[i].size}, {st.iterations} it, "
             f"affected {st.affected_final}, {st.ms_device:.2f} ms; FP32 form {s32.ms_device:.2f} ms")
 
-    g.profile_reset(True)
     lat, edges, per = [], 0, {}
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -219,11 +219,20 @@ def headline_bench(args, dfpr, synth):
                                       st.edges_processed, st.ms_apply, st.ms_mark, st.ms_iter))
     torch.cuda.synchronize()
     t1 = time.perf_counter()
-    prof = g.profile()
-    g.profile_reset(False)
     elapsed = t1 - t0
     value = edges / elapsed / 1e9
     log(f"timed: {args.steps} steps in {elapsed * 1e3:.1f} ms, {value:.2f} GTEPS")
+
+    # the iteration kernel, launch by launch, over the same steps
+    twin = dfpr.Graph(n, src, dst)
+    twin.use_torch_stream()
+    twin.static(p, out=False)
+    for i in range(args.warmup):
+        step(i, twin)
+    twin.profile_reset(True)
+    iters_prof = sum(step(i, twin).iterations for i in range(args.warmup, total))
+    prof = twin.profile()
+    twin.close()
 
     # comparators (not timed): for one more batch of each size, Dynamic
     # Frontier, Naive-dynamic and Static on the same updated graph, the two
@@ -278,7 +287,6 @@ def headline_bench(args, dfpr, synth):
         str(f): round(float(np.mean([x[0] for x in v])), 3) for f, v in sorted(per.items())}
 
     achieved = prof.bytes / (prof.ms / 1e3) / 1e9 if prof.ms > 0 else 0.0
-    iters_timed = int(sum(x[1] for v in per.values() for x in v))
     tb = measured_traffic(workload)
     copy_gbs = copy_bandwidth(torch)
     log(f"achievable copy bandwidth {copy_gbs:.0f} GB/s")
@@ -295,16 +303,16 @@ def headline_bench(args, dfpr, synth):
         # measured HBM bytes (committed counter runs on these sources) over
         # the same kernel time as `achieved`
         "traffic": (None if tb is None or prof.ms <= 0 else
-                    round(tb * iters_timed / (prof.ms / 1e3) / 1e9, 1)),
+                    round(tb * iters_prof / (prof.ms / 1e3) / 1e9, 1)),
         "traffic_bytes_per_launch": (None if tb is None else
-                                     round(tb * iters_timed / max(prof.launches, 1), 1)),
+                                     round(tb * iters_prof / max(prof.launches, 1), 1)),
         # every launch of the kernel, as rocprofv3 counts them: the
         # iterations plus the few launches queued after a call converged,
         # which return at once
         "launches": prof.launches, "avg_launch_us": round(prof.ms * 1e3 / max(prof.launches, 1), 2),
         # the iterations alone (the returning launches cost ~4 us each)
-        "iterations": iters_timed,
-        "avg_iteration_us": round(prof.ms * 1e3 / max(iters_timed, 1), 2),
+        "iterations": iters_prof,
+        "avg_iteration_us": round(prof.ms * 1e3 / max(iters_prof, 1), 2),
         "algorithmic_bytes_per_launch": round(prof.bytes / max(prof.launches, 1), 1),
         "kernel_gteps": round(prof.edges / prof.ms / 1e6, 2) if prof.ms > 0 else None,
         "achievable_copy_GBps": round(copy_gbs, 1),
@@ -467,8 +475,8 @@ def grid_bench(args, dfpr, synth, side=4096, kinds=("uniform", "localised"), per
             g.apply_batch(b)
             _, st = g.dynamic_frontier(b, p=p, out=False)
             rows.append(st)
-            log(f"{kind}: batch {b.size}, {st.iterations} it ({st.loop_iterations} in the "
-                f"small-frontier loop), affected {st.affected_final}, {st.ms_device:.2f} ms")
+            log(f"{kind}: batch {b.size}, {st.iterations} it, affected {st.affected_final}, "
+                f"{st.ms_device:.2f} ms")
         ms = [r.ms_device for r in rows]
         # Naive-dynamic and Dynamic Traversal for the last batch, from the
         # same previous ranks as its Dynamic Frontier call
@@ -485,7 +493,6 @@ def grid_bench(args, dfpr, synth, side=4096, kinds=("uniform", "localised"), per
             "df_us_per_iteration": round(float(np.sum(ms) * 1e3 / np.sum([r.iterations for r in rows])), 1),
             "df_gteps": round(float(np.sum([r.edges_processed for r in rows]) / np.sum(ms) / 1e6), 2),
             "df_ms_last": round(rows[-1].ms_device, 3),
-            "df_loop_iterations_mean": round(float(np.mean([r.loop_iterations for r in rows])), 1),
             "naive_ms": round(st_nv.ms_device, 3), "naive_iterations": st_nv.iterations,
             "speedup_vs_naive": round(st_nv.ms_device / rows[-1].ms_device, 2),
             "dt_ms": round(st_dt.ms_device, 3), "dt_iterations": st_dt.iterations,
