@@ -15,7 +15,7 @@
 #include <mutex>
 
 #include "common.h"
-#include "iter.h"
+#include "engine.h"
 
 namespace dfpr {
 

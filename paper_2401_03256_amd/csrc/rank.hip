@@ -57,8 +57,7 @@
 #include <vector>
 
 #include "common.h"
-#include "iter.h"
-#include "resident.h"
+#include "engine.h"
 
 namespace dfpr {
 

@@ -452,10 +452,4 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
     if (threadIdx.x < kWave) ctl_to_mirror(a.ctl, a.mirror);
 }
 
-// Host helpers of rank.hip shared with the serving loop (serve.hip).
-uint32_t resident_grid(const dfpr_graph *g);
-uint32_t resident_hub(const dfpr_graph *g, bool f32, uint32_t G);
-uint32_t resident_lists(const dfpr_graph *g);
-int resident_args(dfpr_graph *g, int it0, int it, int base, bool full, uint32_t limit, ResArgs &P);
-
 }  // namespace dfpr

@@ -41,8 +41,7 @@
 #include <vector>
 
 #include "common.h"
-#include "iter.h"
-#include "resident.h"
+#include "engine.h"
 #include "serve_policy.h"
 
 namespace dfpr {
