@@ -960,6 +960,7 @@ static int ensure_apply_bufs(dfpr_graph *g, uint64_t B)
     ApplyBufs &ap = g->ap;
     if (B <= ap.cap) return DFPR_OK;
     const uint64_t cap = std::max<uint64_t>(B, 4096);
+    ap.cap = 0;         // until every buffer is there
     for (int o = 0; o < 2; o++) {
         for (int k = 0; k < 2; k++) {
             (void)hipFree(ap.keys[o][k]);

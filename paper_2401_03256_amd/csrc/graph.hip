@@ -48,6 +48,8 @@ int set_error(int code, const std::string &msg)
 
 int hip_fail(hipError_t e, const char *what)
 {
+    // reported here: the next look at the last error is not about it
+    (void)hipGetLastError();
     return set_error(e == hipErrorOutOfMemory ? DFPR_E_NOMEM : DFPR_E_DEVICE,
                      std::string(what) + ": " + hipGetErrorString(e));
 }
@@ -713,7 +715,6 @@ int dfpr_load_graph(int32_t n, int64_t m, const int32_t *src, const int32_t *dst
         rc = build_graph(g, m, src, dst, false, top);
         if (rc == DFPR_E_NOMEM) {
             // the graph may still fit without the scratch
-            (void)hipGetLastError();
             for (Csr &c : g->csr) {
                 (void)hipFree(c.idx);
                 c.idx = nullptr;

@@ -1,6 +1,6 @@
 """Loads at their limits: more input edges than a launch has threads, a device
 with room for the graph but not for the load's scratch, and more vertices than
-edge slots."""
+edge slots.  And a batch whose buffers the device has no room for."""
 import ctypes
 import os
 import sys
@@ -36,27 +36,60 @@ def _same_graph(g, h):
     assert sa.iterations == sb.iterations and np.array_equal(a, b)
 
 
+class _Ballast:
+    """Leaves about `mb` MB of the device free."""
+
+    def __init__(self, mb):
+        import torch
+        torch.cuda.empty_cache()
+        self.held = []
+        for _ in range(200):
+            free = torch.cuda.mem_get_info()[0] - (mb << 20)
+            if free < 4 << 20:
+                break
+            self.held.append(torch.empty(min(free, 16 << 30), dtype=torch.uint8, device="cuda"))
+        free = torch.cuda.mem_get_info()[0] >> 20
+        _say(f"free now {free} MB")
+        assert mb - 25 <= free <= mb + 7
+
+    def drop(self):
+        import torch
+        self.held = []
+        torch.cuda.empty_cache()
+
+
 def test_load_beside_other_allocations(dfpr):
-    import torch
     _say("load with 225 MB of the device free")
     n, src, dst = synth.rmat(19, 16, seed=21)
     want = dfpr.Graph(n, src, dst)              # 145 MB, and 190 MB more while it loads
-    torch.cuda.empty_cache()
-    ballast = []
-    for _ in range(200):
-        free = torch.cuda.mem_get_info()[0] - (225 << 20)
-        if free < 4 << 20:
-            break
-        ballast.append(torch.empty(min(free, 16 << 30), dtype=torch.uint8, device="cuda"))
-    free = torch.cuda.mem_get_info()[0] >> 20
-    _say(f"free now {free} MB")
-    assert 200 <= free <= 232
+    ballast = _Ballast(225)
     try:
         got = dfpr.Graph(n, src, dst)
     finally:
-        del ballast
-        torch.cuda.empty_cache()
+        ballast.drop()
     _same_graph(got, want)
+
+
+def test_batches_after_one_without_room(dfpr):
+    """A batch that fails for want of memory leaves the graph able to take others."""
+    _say("batch of 6,000,000 entries with 150 MB of the device free")
+    n, src, dst = synth.rmat(14, 16, seed=22)
+    g, h = dfpr.Graph(n, src, dst), dfpr.Graph(n, src, dst)
+    seq = synth.batch_sequence(src, dst, n, [(40, 160), (300, 1200), (5, 20)], seed=23)
+    assert g.apply_batch(seq[0]) == h.apply_batch(seq[0])
+    z = np.zeros(0, np.int32)
+    rng = np.random.default_rng(24)
+    big = synth.Batch(z, z, *rng.integers(0, n, (2, 6_000_000), dtype=np.int32))
+    ballast = _Ballast(150)
+    try:
+        with pytest.raises(dfpr.DfprError) as e:    # 32 bytes of keys an entry
+            g.apply_batch(big)
+        assert e.value.code == dfpr.DFPR_E_NOMEM
+        for b in seq[1:]:
+            assert g.apply_batch(b) == h.apply_batch(b)
+    finally:
+        ballast.drop()
+    _same_graph(g, h)
 
 
 def test_more_vertices_than_slots(dfpr):
