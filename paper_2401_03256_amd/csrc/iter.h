@@ -178,6 +178,7 @@ struct IterArgs {
     double alpha, tol, ftol;
     uint32_t sbase;             // stamp base of the call
     uint32_t sparse_limit;
+    uint32_t heavy;             // class lists: rows of more out-edges mark with plain stores
     int32_t it, max_iters;
     int32_t n_stride;
     uint32_t long_row;          // FP64 rows of more in-edges take kLongParts parts
@@ -368,11 +369,13 @@ __device__ __forceinline__ void mark_out_row(const IterArgs &a, int32_t w, uint3
 // On the class lists, a row with more out-edges than this marks them with
 // plain stores, like the full schedule does, and moves the call to the full
 // schedule from the next iteration on: its out-row alone would fill a good
-// part of the lists, and one workgroup appending them entry by entry (an
-// atomic per out-edge) stalls the whole iteration.
+// part of the lists of launches (an eighth), and one workgroup appending them
+// entry by entry (an atomic per out-edge) stalls the whole iteration.  The
+// resident loop's longer lists do not move the line: R-MAT scale 20, a batch of
+// two, 0.85 ms of iterations, and 1.24 with an eighth of its lists.
 __device__ __forceinline__ bool heavy_in_sparse(const IterArgs &a, uint32_t oc)
 {
-    return oc > a.sparse_limit / 8;
+    return oc > a.heavy;
 }
 
 // Expansion of the rows of a wave whose lanes have `deg` > 0 out-edges

@@ -1002,6 +1002,7 @@ IterArgs iter_args(dfpr_graph *g, const dfpr_params &p, uint32_t sbase)
     a.ftol = p.frontier_tol;
     a.sbase = sbase;
     a.sparse_limit = g->sparse_limit;
+    a.heavy = g->sparse_limit / 8;
     a.long_row = g->long_row;
     a.max_iters = p.max_iters;
     a.n_stride = g->n;
@@ -1154,7 +1155,7 @@ static int launch_resident(dfpr_graph *g, IterArgs a, bool df, bool f32, int it0
     a.mirror = g->ctl_host;
     const uint32_t G = full ? resident_grid(g) : (uint32_t)g->cus;
     a.hub = full && a.hub ? resident_hub(g, f32, G) : 0u;
-    a.sparse_limit = resident_lists(g);
+    if (limit == kNoLimit) a.sparse_limit = resident_lists(g);
     const bool pairs = full && !f32 && wave_units(g) >= (uint64_t)kPairUnits * kResWaves * G;
     auto *kernel = f32     ? k_resident<true, true, false>
                    : !df   ? pairs ? k_resident<false, false, true> : k_resident<false, false, false>
@@ -1205,7 +1206,7 @@ static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint
     const bool resident = device_loop ? lists
                           : p.loop != DFPR_LOOP_ITERATION && !g->prof.enabled && (full || lists);
     if (!async && resident) {
-        const uint32_t limit = device_loop ? kLoopRows : 0xFFFFFFFFu;
+        const uint32_t limit = device_loop ? kLoopRows : kNoLimit;
         while (next_it < p.max_iters) {
             bool ran = false;
             DFPR_CHECK_RC(launch_resident(g, a, df, f32, it0, next_it, base, full, limit,
@@ -1500,7 +1501,7 @@ int df_begin(dfpr_graph *g, const dfpr_params &p, int64_t nd, const int32_t *ds,
     // keep can take it: where those are the resident loop's, from 1/64 to 1/8
     // of the vertices (2048 x 2048 grid, 256 scattered changes: a call
     // 3132 -> 2737 us; 10^6-vertex random graph: 4512 -> 4373 us).
-    const bool resident = p.mode != DFPR_ASYNC && p.loop != DFPR_LOOP_ITERATION &&
+    const bool resident = p.mode != DFPR_ASYNC && p.loop == DFPR_LOOP_LAUNCHES &&
                           !g->prof.enabled && g->m <= kResEdges;
     const uint32_t plain_limit = resident ? resident_lists(g) : a.sparse_limit;
     if (small) {

@@ -65,6 +65,7 @@ constexpr int32_t kResSparse = 8;
 // pairs made a call on R-MAT scale 13 11% slower.
 constexpr uint32_t kPairUnits = 4;
 constexpr uint32_t kLoopRows = 16384;            // DFPR_LOOP_DEVICE: most rows of an iteration
+constexpr uint32_t kNoLimit = 0xFFFFFFFFu;       //   ... of the other calls
 constexpr int kResWaves = 16;
 constexpr int kResThreads = kResWaves * kWave;
 constexpr int kResMax = 256;                     // workgroups

@@ -372,7 +372,7 @@ static int launch_resident_chunk(dfpr_server *srv, int lane, int buf, std::vecto
         a.hub = resident_hub(g, sl.phase32 != 0, G);
         a.sparse_limit = resident_lists(g);
         ResArgs P;
-        DFPR_CHECK_RC(resident_args(g, sl.it0, sl.itq, sl.base, true, 0xFFFFFFFFu, P));
+        DFPR_CHECK_RC(resident_args(g, sl.it0, sl.itq, sl.base, true, kNoLimit, P));
         P.close = sl.phase32 ? 0 : 1;
         P.budget = budget_us * 100;
         P.stop = srv->stop;
