@@ -28,6 +28,7 @@ int df_phase_end(dfpr_graph *g, int res, bool call_done);
 int df_finish(dfpr_graph *g, uint32_t sbase, int res, int32_t iters, bool closed = false);
 
 // The resident loop's launches.
+bool resident_whole(const dfpr_graph *g);
 uint32_t resident_grid(const dfpr_graph *g);
 uint32_t resident_hub(const dfpr_graph *g, bool f32, uint32_t G);
 uint32_t resident_lists(const dfpr_graph *g);

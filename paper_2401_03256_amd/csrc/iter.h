@@ -181,7 +181,7 @@ struct IterArgs {
     uint32_t heavy;             // class lists: rows of more out-edges mark with plain stores
     int32_t it, max_iters;
     int32_t n_stride;
-    uint32_t long_row;          // FP64 rows of more in-edges take kLongParts parts
+    uint32_t long_row;          // launches: FP64 rows of more in-edges take kLongParts parts
     uint32_t hub;               // contributions to copy into LDS (0: none)
     struct Stage *stage;        // resident loop: the workgroup's new list entries
 };
@@ -673,7 +673,9 @@ __device__ __forceinline__ void finish_unit(const IterArgs &a, const UnitRow &ro
 // The FP32 form keeps kBlock parts: with more, its Kahan sums would round
 // differently.
 // So does every row of a graph that is too large for the resident loop when it
-// is loaded (dfpr_graph::long_row): in launches four passes are only slower.
+// is loaded (dfpr_graph::long_row): in launches four passes are only slower.  The
+// resident loop leaves the class to launches there, so that its own line is a
+// constant (as a field it cost an update pair on R-MAT scale 16 0.7%).
 // R-MAT with 2.5e6 vertices, 41.7M edges: a sweep 233.4 -> 231.3 us (228.8
 // before there were long rows), Static 15.89 -> 15.76 ms; scale 22 24.16 ->
 // 24.0 ms.
@@ -698,7 +700,7 @@ __device__ __forceinline__ void block_row(const IterArgs &a, const Hub &hub, int
     if (active) {
         cnt = a.in_cnt[v];
     }
-    const bool lng = !F32 && cnt > a.long_row;
+    const bool lng = !F32 && cnt > (COH ? kLongRow : a.long_row);
     if (active) {
         const int32_t *idx = a.in_idx + a.in_beg[v];
         auto pass = [&](uint32_t q, auto step) {
@@ -916,7 +918,7 @@ __device__ __forceinline__ void make_plan_wave(const IterArgs &a, const Ctl *ctl
         nlong = 0;
         for (uint32_t u0 = 0; u0 < nbu; u0 += kWave) {
             const unsigned long long m =
-                __ballot(u0 + lane < nbu && a.in_cnt[first + u0 + lane] > a.long_row);
+                __ballot(u0 + lane < nbu && a.in_cnt[first + u0 + lane] > kLongRow);
             if (m) nlong = u0 + kWave - __clzll((long long)m);
         }
         auto rounds = [&](uint32_t w) {

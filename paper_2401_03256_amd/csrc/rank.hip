@@ -1070,6 +1070,13 @@ static uint64_t wave_units(const dfpr_graph *g)
     return nwu;
 }
 
+// Whether whole calls on the graph iterate in the resident loop (see kResEdges),
+// and not only those on the class lists.
+bool resident_whole(const dfpr_graph *g)
+{
+    return g->m <= kResEdges && g->long_row == kLongRow;
+}
+
 // Workgroups of a resident launch whose iterations walk the full schedule:
 // enough waves for its wave units and enough sub-blocks for its long rows,
 // one workgroup per compute unit at most.
@@ -1133,6 +1140,7 @@ int resident_args(dfpr_graph *g, int it0, int it, int base, bool full, uint32_t 
     P.it_start = it;
     P.full = full ? 1 : 0;
     P.limit = limit;
+    P.blocks = g->long_row == kLongRow ? kNoLimit : 0u;
     P.spin = g->res_refuse ? 0u : kGoSpin;
     P.tag = g->res_tag + 1;
     P.ext2int = g->ext2int;
@@ -1202,7 +1210,7 @@ static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint
     // DFPR_LOOP_ITERATION and, unless small frontiers are asked for, profiled
     // calls keep a launch per iteration.
     const bool device_loop = p.loop == DFPR_LOOP_DEVICE;
-    const bool full = !device_loop && g->m <= kResEdges;
+    const bool full = !device_loop && resident_whole(g);
     const bool resident = device_loop ? lists
                           : p.loop != DFPR_LOOP_ITERATION && !g->prof.enabled && (full || lists);
     if (!async && resident) {
@@ -1502,7 +1510,7 @@ int df_begin(dfpr_graph *g, const dfpr_params &p, int64_t nd, const int32_t *ds,
     // of the vertices (2048 x 2048 grid, 256 scattered changes: a call
     // 3132 -> 2737 us; 10^6-vertex random graph: 4512 -> 4373 us).
     const bool resident = p.mode != DFPR_ASYNC && p.loop == DFPR_LOOP_LAUNCHES &&
-                          !g->prof.enabled && g->m <= kResEdges;
+                          !g->prof.enabled && resident_whole(g);
     const uint32_t plain_limit = resident ? resident_lists(g) : a.sparse_limit;
     if (small) {
         b.nd = nd;

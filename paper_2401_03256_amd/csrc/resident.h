@@ -97,6 +97,7 @@ struct ResArgs {
     int it_start;       // first iteration of this launch
     int full;           // the launch keeps going on the full schedule
     uint32_t limit;     // class list rows of an iteration above which it hands over
+    uint32_t blocks;    //   ... and rows of the workgroup class
     uint32_t spin;      // polls of workgroup 0 before the launch gives up starting
     uint32_t tag;       // first of its tags
     int close;          // end the call too, if it converges or reaches the cap
@@ -250,7 +251,8 @@ __device__ __forceinline__ void resident_body(IterArgs a, const ResArgs &P, uint
         uint32_t rows = 0;
 #pragma unroll
         for (int b = 0; b < kBins; b++) rows += rs.state[1 + b];
-        if (stop || (dense ? !P.full : rows > P.limit)) break;     // uniform over the launch
+        if (stop || (dense ? !P.full : rows > P.limit || rs.state[kBins] > P.blocks))
+            break;      // uniform over the launch
         const int src = P.base ^ ((it - P.it0) & 1);
         a.it = it;
         a.Rc = src ? P.R[1] : P.R[0];

@@ -513,10 +513,13 @@ static int run(dfpr_server *srv, dfpr_server_stats *st)
             for (int i = 0; i < srv->max_slots; i++)
                 if (slots[i].req >= 0 && slot_lane[i] == lane) cs.push_back(&slots[i]);
             if (cs.empty()) continue;
-            // a graph that asks for a launch per iteration asks for its chunk
+            // a graph that asks for a launch per iteration, or takes it, does
+            // so for its chunk
             bool each = false;
-            for (const Slot *s : cs)
-                each |= srv->graphs[srv->reqs[s->req].gid].p.loop == DFPR_LOOP_ITERATION;
+            for (const Slot *s : cs) {
+                const GraphEntry &ge = srv->graphs[srv->reqs[s->req].gid];
+                each |= ge.p.loop == DFPR_LOOP_ITERATION || !resident_whole(ge.g);
+            }
             if (L.n == 0 && lane == 1 && active_in(0) == 0 && resident_ok && !each) {
                 budget_us = !waiting ? kBudgetMost : admissible() ? kBudgetAdmit : kBudgetArrivals;
                 rc = launch(lane, cs, 0);
