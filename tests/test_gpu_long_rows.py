@@ -67,3 +67,31 @@ def test_long_rows_above_the_resident_line(dfpr):
     c, sc = g.dynamic_frontier(b, R, dfpr.params(frontier_tol=1e-13, loop=dfpr.LOOP_ITERATION))
     assert marks[0] and sa.iterations == sc.iterations and np.array_equal(a, c)
     assert np.array_equal(marks, g.affected())
+
+
+def test_long_rows_of_a_graph_that_shrank(dfpr):
+    """Loaded above the line and below it after a batch: the parts of its rows
+    stay, and whole calls stay with launches."""
+    from paper_2401_03256_amd import synth
+    n, hub = 2_500_000, 9000
+    rng = np.random.default_rng(2)
+    src = np.concatenate([rng.integers(0, n, 37_900_000, dtype=np.int32), np.arange(1, hub + 1, dtype=np.int32)])
+    dst = np.concatenate([rng.integers(0, n, 37_900_000, dtype=np.int32), np.zeros(hub, np.int32)])
+    g = dfpr.Graph(n, src, dst)
+    drop = g.m - 40_000_000 + 1000
+    sys.stdout.write(f"\n[case] {g.m} edges, {drop} deleted\n")
+    sys.stdout.flush()
+    assert 1000 < drop < 2_000_000
+    e = np.unique(src[:2 * drop].astype(np.int64) * n + dst[:2 * drop])
+    e = e[e // n != e % n][:drop]
+    z = np.zeros(0, np.int32)
+    assert g.apply_batch(synth.Batch((e // n).astype(np.int32), (e % n).astype(np.int32), z, z)) == (drop, 0)
+    assert g.m < 40_000_000
+    R, st = g.static()
+    want, _ = g.static(dfpr.params(loop=dfpr.LOOP_ITERATION))
+    assert st.converged and np.array_equal(R, want)
+    b = synth.Batch(z, z, np.array([5, 77], np.int32), np.array([n - 1, 0], np.int32))
+    g.apply_batch(b)
+    a, sa = g.dynamic_frontier(b, R, dfpr.params(frontier_tol=1e-13))
+    c, sc = g.dynamic_frontier(b, R, dfpr.params(frontier_tol=1e-13, loop=dfpr.LOOP_ITERATION))
+    assert sa.iterations == sc.iterations and np.array_equal(a, c)
