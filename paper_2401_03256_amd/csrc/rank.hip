@@ -1229,7 +1229,8 @@ static int run_loop(dfpr_graph *g, const dfpr_params &p, bool df, bool f32, uint
                 stop = true;
                 break;
             }
-            gsz = df && !c.dense ? sparse_grid(g, c) : (uint32_t)g->grid;
+            // a frontier with rows of the workgroup class is about to grow
+            gsz = df && !c.dense && !c.live[kBins - 1] ? sparse_grid(g, c) : (uint32_t)g->grid;
             wide = DFPR_WIDE && (!df || c.dense);
             if (steps < kResSteps) break;     // handed over
         }
@@ -1601,8 +1602,12 @@ static int df_end(dfpr_graph *g, uint32_t sbase, int res, const Close &close, do
 //     and 0.23 / 1.54 / 4.42 / 8.09 ms; FP32 form, 8550: 5.9 and 5.3 ms
 //   G(n, m), 3e6 vertices, 45e6 edges, 5 / 480 / 4800 changes: 0.26 / 3.06 /
 //     3.57 and 0.62 / 2.94 / 3.52 ms; 6e6 vertices, 510: 14.0 and 14.6 ms
+// With rows of the workgroup class, which a first frontier soon holds, it does
+// not help (R-MAT scale 22, 7 changes, 8.49 and 8.51 ms), and they belong to the
+// launches there (ResArgs::blocks).
 static bool first_lists(const dfpr_graph *g, int64_t tot)
 {
+    if (g->cls[1] > 0) return false;
     const double mean = (double)g->m / g->n;
     return (double)tot * mean * mean <= (double)g->sparse_limit / 2;
 }
