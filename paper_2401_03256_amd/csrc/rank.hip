@@ -406,10 +406,14 @@ __device__ inline void mark_one(const IterArgs &a, int32_t x, bool append,
 // snapshot of iteration 0.  A call that is over with it (an id outside [0, n),
 // or no iteration allowed) has no iteration that would leave the control block
 // in the host's copy, so it goes there from here.
-__global__ __launch_bounds__(kBlock) void k_mark_initial(IterArgs a, int64_t nd, const int32_t *dd,
-                                                         const int32_t *light,
-                                                         const int32_t *heavy, int dense, int snap,
-                                                         uint32_t plain_limit)
+// Bound by the latency of scattered stamps, so the waves in flight count.  A SIMD
+// has 800 scalar registers and a wave gets 16 on top of its own for the trap
+// handler: above 80 an eighth of the 2048 workgroups runs after the others.
+// Capped at 80 against the 84 the snapshot's code brings it to: 2^22-vertex R-MAT,
+// 694000 changes, 798 -> 567 us; 3000 x 3000 grid, 459000 changes, 384 -> 236 us.
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80)))
+void k_mark_initial(IterArgs a, int64_t nd, const int32_t *dd, const int32_t *light,
+                    const int32_t *heavy, int dense, int snap, uint32_t plain_limit)
 {
     __shared__ unsigned long long s_new, s_deg;
     __shared__ HeavyShared hs;
