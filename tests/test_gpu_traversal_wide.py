@@ -67,3 +67,24 @@ def test_search_matches_oracle(dfpr, name):
         assert np.abs(got - o.dynamic_traversal(b, R)[0]).max() <= 1e-9
         inv = synth.Batch(b.ins_src, b.ins_dst, b.del_src, b.del_dst)
         assert g.apply_batch(inv) == tuple(o.apply_batch(inv))
+
+
+@pytest.mark.parametrize("n", [63, 65535, 65536, 65537])
+def test_flags_of_small_and_larger_graphs(dfpr, n):
+    """Flags come through pinned memory up to 65536 vertices, by a copy above."""
+    sys.stdout.write(f"\n[case] flags {n}\n")
+    sys.stdout.flush()
+    src, dst = synth.gnm(n, 4 * n, seed=n)
+    g, o = dfpr.Graph(n, src, dst), oracle.OracleGraph(n, src, dst)
+    assert not g.affected().any()
+    g.static()
+    for seed in (1, 2):
+        b = synth.random_batch(src, dst, n, 2, 3, seed=seed)
+        o.apply_batch(b)
+        g.apply_batch(b)
+        assert np.array_equal(g.mark_affected(b), o.mark_initial(b))
+        assert np.array_equal(g.mark_reachable(b), o.mark_reachable(b))
+        g.dynamic_traversal(b)
+        assert np.array_equal(g.affected(), o.mark_reachable(b))
+        inv = synth.Batch(b.ins_src, b.ins_dst, b.del_src, b.del_dst)
+        assert g.apply_batch(inv) == tuple(o.apply_batch(inv))
