@@ -847,7 +847,8 @@ __global__ void k_caps(int32_t n, const uint32_t *cap, uint64_t *caps)
         caps[r] = r < n ? (uint64_t)cap[r] : 0;
 }
 
-// Grown capacity for each row left for the re-layout (in both tables).
+// Grown capacity for each row left for the re-layout, in the table to lay out
+// by or, once that has its memory, in the rows' own.
 __global__ void k_ovf_caps(uint32_t count, const uint32_t *list, const int32_t *need,
                            const uint64_t *keys, uint64_t *caps, uint32_t *cap)
 {
@@ -856,8 +857,8 @@ __global__ void k_ovf_caps(uint32_t count, const uint32_t *list, const int32_t *
     const uint64_t d = (uint64_t)need[i];
     const uint32_t r = key_row(keys[list[i]]);
     const uint64_t c = d + (d / 8 > 2 ? d / 8 : 2);
-    caps[r] = c;
-    cap[r] = (uint32_t)c;
+    if (caps) caps[r] = c;
+    if (cap) cap[r] = (uint32_t)c;
 }
 
 // exclusive scan of caps[0 .. len) in place, 3 phases, 2048 per workgroup
@@ -1140,7 +1141,7 @@ static int relayout(dfpr_graph *g, int o, uint32_t novf, const uint64_t *sorted_
     uint64_t *const caps = caps_buf.p, *const sums = sums_buf.p;
     k_caps<<<grid_for(len), kBlock, 0, s>>>(n, c.cap, caps);
     k_ovf_caps<<<grid_for(novf), kBlock, 0, s>>>(novf, g->ap.ovf_list[o], g->ap.ovf_need[o],
-                                                 sorted_keys, caps, c.cap);
+                                                 sorted_keys, caps, nullptr);
     std::vector<int32_t> need(novf);
     DFPR_HIP(hipMemcpyAsync(need.data(), g->ap.ovf_need[o], (size_t)novf * 4,
                             hipMemcpyDeviceToHost, s));
@@ -1152,6 +1153,9 @@ static int relayout(dfpr_graph *g, int o, uint32_t novf, const uint64_t *sorted_
     if (slots > 0xFFFFFFFFull) return set_error(DFPR_E_LIMIT, "graph needs more than 2^32-1 edge slots");
     int32_t *nidx = nullptr;
     DFPR_HIP(hipMalloc(&nidx, slots * 4));
+    // not before: a call that ends here leaves rows and capacities as they are
+    k_ovf_caps<<<grid_for(novf), kBlock, 0, s>>>(novf, g->ap.ovf_list[o], g->ap.ovf_need[o],
+                                                 sorted_keys, nullptr, c.cap);
     k_move_rows<<<4096, kBlock, 0, s>>>(n, c.beg, c.cnt, c.idx, caps, nidx);
     DFPR_HIP(hipGetLastError());
     const unsigned long long top = packed;

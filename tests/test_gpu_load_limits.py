@@ -92,6 +92,36 @@ def test_batches_after_one_without_room(dfpr):
     _same_graph(g, h)
 
 
+def test_relayout_without_room(dfpr):
+    """A batch whose rows need the index array laid out anew and find no memory for it
+    leaves the rows' capacities with the old array; the same batch later completes it."""
+    _say("450,000 insertions into 3000 rows with 100 MB of the device free")
+    n, m = 40_000, 30_000_000                   # 135 MB of slots an orientation
+    rng = np.random.default_rng(25)
+    src, dst = rng.integers(0, n, (2, m), dtype=np.int32)
+    g, h = dfpr.Graph(n, src, dst), dfpr.Graph(n, src, dst)
+    z = np.zeros(0, np.int32)
+    rows = np.repeat(np.arange(3000, dtype=np.int32), 150)
+    add = synth.Batch(z, z, rng.integers(0, n, rows.size, dtype=np.int32), rows)
+    loops = np.arange(rows.size, dtype=np.int32) % n
+    assert g.apply_batch(synth.Batch(loops, loops, z, z)) == (0, 0)     # its buffers
+    ballast = _Ballast(100)
+    try:
+        with pytest.raises(dfpr.DfprError) as e:
+            g.apply_batch(add)
+        assert e.value.code == dfpr.DFPR_E_NOMEM
+        for k in range(0, rows.size, 150 * 300):        # one more of every 300th row
+            g.apply_batch(synth.Batch(z, z, add.ins_src[k:k + 1], add.ins_dst[k:k + 1]))
+    except dfpr.DfprError as e:
+        assert e.code == dfpr.DFPR_E_NOMEM
+    finally:
+        ballast.drop()
+    g.apply_batch(add)
+    h.apply_batch(add)
+    (a, _), (b, _) = g.static(), h.static()
+    assert np.array_equal(a, b)
+
+
 def test_more_vertices_than_slots(dfpr):
     _say("2^31 - 1 vertices")
     z = np.zeros(0, np.int32)
